@@ -78,7 +78,11 @@ extern "C" {
 
 typedef struct slos_plan_s *slos_plan_t;
 
-/* Tuning options; a zero field takes its default. */
+/* Tuning options; a zero field takes its default.  With every tiling option
+ * (all but comp_from_layer and max_batch) at zero, a plan computes its layers
+ * of up to a few million states from predecessor tables, the first of them in
+ * one launch; a tiling option asks for the tiled kernels on every layer.  The
+ * amplitudes are the same bit for bit. */
 typedef struct slos_options {
     int32_t leaf_max;        /* max states per leaf tile, <= 65536 (default 16384 for
                                 c64, 8192 for c128, 4096 with SLOS_KEEP_LAYERS); a
@@ -493,7 +497,8 @@ int slos_source_postselect(slos_source_t source, const double *probs, const int3
  * records a HIP event on its stream before layer 1, after every layer k and
  * after the final FP64 sum; slos_plan_layer_ms then waits for the last event
  * and writes ms[k-1] = duration of layer k (k = 1..n) and ms[n] = duration of
- * the sum reduction (0 if it did not run).  `count` must be >= n + 1.  Events
+ * the sum reduction (0 if it did not run as a launch of its own).  Small layers
+ * that share one launch count at the first of them (the others read 0).  `count` must be >= n + 1.  Events
  * are owned by the plan.  Leave it off under stream capture.
  */
 int slos_plan_set_timing(slos_plan_t plan, int on);

@@ -1,0 +1,99 @@
+// Table-driven layers (flat.hip): the layers small enough that each state's
+// predecessor ranks are kept as a table.  Not part of the public ABI.
+#pragma once
+
+#include "slos_internal.h"
+
+// Table entries are (mode << 24) | rank.  A padded entry names mode m, whose
+// coefficient is held at zero, and the state after the last of layer k - 1,
+// taken as zero: it adds nothing, whatever the layer's values are.
+#define SLOS_FLAT_PAD(m, Nprev) ((uint32_t)(m) << 24 | (uint32_t)(Nprev))
+// Layers of at most this many states are table-driven.  Measured on one layer
+// (microseconds, tiled against table-driven): 657,800 states 27 against 11
+// (c64), 1,081,575 31 against 15 (c64) and 37 against 18 (c128), 2,220,075 38
+// against 24 and 53 against 31, 3,124,550 55 against 42 and 78 against 53;
+// 4,686,825 66 against 70 (c64; c128 99 against 84, but its table alone is
+// 170 MB), 6,906,900 83 against 100.  Also keeps every rank within 24 bits.
+#define SLOS_FLAT_MAX_STATES 3200000u
+// Largest layer that every workgroup of the first launch computes for itself,
+// and the LDS its two layers may take.  One instance: m=13, n=6 (6,188 states
+// in layer 5) 12.1 us a pass with that layer in the first launch, 15.6 without;
+// ten instances at m=15, n=6 (11,628 states) 24.9 us with, 16.0 without, the
+// workgroups then outnumbering the CUs.
+#define SLOS_HEAD_MAX_STATES 12288u
+#define SLOS_HEAD_MAX_STATES_MANY 6144u
+#define SLOS_HEAD_LDS_MAX (144u * 1024u)
+// Workgroups of that launch: one output of its last layer per thread for one
+// instance; several instances share 256 in all, one per CU (64 instances at
+// m=12, n=6: 13.6 us, against 20.4 with 512 and 63 with 1024).
+#define SLOS_HEAD_MAX_GROUPS 512
+#define SLOS_HEAD_MAX_GROUPS_MANY 256
+#define SLOS_FLAT_THREADS 256
+#define SLOS_FLAT_VMAX 256u             // slots of a table-driven layer's recorded maximum
+
+// Layers 1..h+1 in one launch: 1..h in LDS by every workgroup, h+1 to Y.
+struct HeadParams {
+    const void *U;
+    void *Y;                     // layer h + 1
+    void *keep;                  // kept layers 1..h are stored here too, or NULL
+    const uint32_t *pred;
+    const double *scale;         // normalisation of every output when h + 1 is the last layer
+    double *partials;            // one FP64 partial of sum P per workgroup
+    double *sum_p;               // the sum itself, by one workgroup or with `count`; or NULL
+    uint32_t *count;             // zero: the last workgroup to end sums the partials; or NULL
+    uint32_t *zero;              // words the later launches of the pass need cleared
+    float *vm;                   // per workgroup: max |Re| + |Im| over its part of layer h + 1, or NULL
+    uint64_t u_stride, y_stride, keep_stride;             // bytes per instance (blockIdx.y)
+    uint64_t partials_stride, zero_stride, vm_stride, count_stride;  // elements per instance
+    uint64_t keep_off[SLOS_MAX_PHOTONS + 1];              // bytes
+    uint64_t off[SLOS_MAX_PHOTONS + 1];                   // layer k's table, in entries
+    uint32_t N[SLOS_MAX_PHOTONS + 1];
+    uint32_t cap[2];             // elements of the even and the odd LDS buffer (a zero follows each layer)
+    uint32_t nzero;
+    int m, h;
+    int comp_from;               // first compensated layer
+    uint8_t col[SLOS_MAX_PHOTONS + 1];
+};
+
+// One layer, one output per thread.
+struct FlatParams {
+    const void *X;
+    void *Y;
+    const void *U;
+    const uint32_t *pred;        // this layer's table, term-major
+    const double *scale;
+    double *partials;            // one FP64 partial of sum P per workgroup
+    const uint32_t *vmax_in;     // float bits of the maxima whose largest bounds |Re| + |Im| over X
+    uint32_t *vmax_out;          // SLOS_FLAT_VMAX cleared slots for this layer's maximum, or NULL
+    uint64_t x_stride, y_stride, u_stride;     // bytes per instance (blockIdx.y)
+    uint64_t partials_stride, vin_stride, vout_stride;
+    uint32_t nvmax;
+    uint32_t N, Nprev, cmax;
+    int m, col;
+};
+
+// Device-side construction of the tables of layers 1..kf.
+struct FlatTables {
+    const uint64_t *binom;       // binom[a * bstride + b] = C(a, b)
+    int bstride;
+    int m, kf;
+    uint32_t *pred;
+    uint64_t off[SLOS_MAX_PHOTONS + 1];
+    uint32_t N[SLOS_MAX_PHOTONS + 1];
+    uint32_t leaf_cap[SLOS_MAX_PHOTONS + 1];  // the tiled kernel's leaf size of each layer
+    double *scale;               // of layer kf, or NULL
+    double norm_t;
+    uint32_t *succ;              // mode-major: succ[succ_off[k] + j * N[k - 1] + y] = rank of y + e_j, or NULL
+    uint64_t succ_off[SLOS_MAX_PHOTONS + 1];
+};
+
+struct FlatLaunch {
+    const HeadParams *head;      // exactly one of the three is set
+    const FlatParams *flat;
+    const FlatTables *tables;
+    int c64, mode, compensated;
+    int batch;
+    int grid;                    // head: workgroups per instance
+    int threads;                 // head: workgroup size
+};
+int slos_launch_flat(const FlatLaunch &l, void *stream);

@@ -19,148 +19,12 @@
 // whole small instances per workgroup, one leaf per wave.
 #include <hip/hip_runtime.h>
 
+#include "accum.h"
+#include "flat.h"
 #include "slos_internal.h"
 
 namespace {
 
-template <typename T> struct Cx;
-template <> struct Cx<float> { using type = float2; };
-template <> struct Cx<double> { using type = double2; };
-
-__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
-
-// acc += u * v (complex), four fused multiply-adds
-template <typename C>
-__device__ __forceinline__ void cmac(C &acc, const C u, const C v)
-{
-    acc.x = fma_(u.x, v.x, acc.x);
-    acc.x = fma_(-u.y, v.y, acc.x);
-    acc.y = fma_(u.x, v.y, acc.y);
-    acc.y = fma_(u.y, v.x, acc.y);
-}
-
-// ---- compensated complex64 accumulation ---------------------------------
-// SLOS_COMP_TWOSUM: every real product a*b is split exactly into p + pe with an
-// FMA (two-product) and added to the running sum s with Knuth's two-sum; both
-// rounding errors go to a second float c.  Ten operations per product.
-__device__ __forceinline__ void acc_exact(float &s, float &c, float a, float b)
-{
-#pragma clang fp contract(off)
-    float p = a * b;
-    float pe = __builtin_fmaf(a, b, -p);
-    float t = s + p;
-    float bb = t - s;
-    float e = (s - (t - bb)) + (p - bb);
-    s = t;
-    c = c + (e + pe);
-}
-
-struct CompAcc {
-    float2 s, c;
-};
-
-__device__ __forceinline__ void cmac_comp(CompAcc &a, const float2 u, const float2 v)
-{
-    acc_exact(a.s.x, a.c.x, u.x, v.x);
-    acc_exact(a.s.x, a.c.x, -u.y, v.y);
-    acc_exact(a.s.y, a.c.y, u.x, v.y);
-    acc_exact(a.s.y, a.c.y, u.y, v.x);
-}
-
-// Default compensated mode: biased FMA accumulation.  The sum starts at a
-// power of two sigma >= 4 * sum_i |a_i b_i| (a bound known before the sum).  Every partial sum then stays within [3/4, 5/4] sigma, so
-// for t = fma(a, b, s) the difference s - t is exact (Sterbenz) and
-// fma(a, b, s - t) is the FMA's rounding error, correct to one rounding of a
-// number below ulp(sigma).  Those errors go to a second float c, and the
-// result is (s - sigma) + c, where s - sigma is exact again.  The error-free
-// transformation is the two-sum of s and a*b computed with the FMA; the bias
-// makes its short form exact.  Four operations per real product; the error is
-// within one rounding of the result plus O(terms * 2^-46 * sigma).
-__device__ __forceinline__ void acc_biased(float &s, float &c, float a, float b)
-{
-#pragma clang fp contract(off)
-    const float t = __builtin_fmaf(a, b, s);
-    const float d = s - t;
-    c = c + __builtin_fmaf(a, b, d);
-    s = t;
-}
-
-// 8 * 2^floor(log2 b) (> 4b), at least 2^-117
-__device__ __forceinline__ float bias_for(float b)
-{
-    const float f = __uint_as_float(__float_as_uint(b) & 0x7F800000u);
-    return 8.0f * fmaxf(f, 0x1p-120f);
-}
-
-template <typename T, int COMP> struct Acc;
-template <typename T> struct Acc<T, SLOS_COMP_NONE> {
-    using C = typename Cx<T>::type;
-    C a;
-    __device__ __forceinline__ void zero() { a = C{0, 0}; }
-    __device__ __forceinline__ void start(float) {}
-    __device__ __forceinline__ void mac(const C u, const C v) { cmac(a, u, v); }
-    __device__ __forceinline__ C value() const { return a; }
-    __device__ __forceinline__ double re() const { return (double)a.x; }
-    __device__ __forceinline__ double im() const { return (double)a.y; }
-};
-template <> struct Acc<float, SLOS_COMP_TWOSUM> {
-    CompAcc a;
-    __device__ __forceinline__ void zero() { a.s = float2{0.f, 0.f}; a.c = float2{-0.f, -0.f}; }
-    __device__ __forceinline__ void start(float) {}
-    __device__ __forceinline__ void mac(const float2 u, const float2 v) { cmac_comp(a, u, v); }
-    __device__ __forceinline__ float2 value() const { return float2{a.s.x + a.c.x, a.s.y + a.c.y}; }
-    __device__ __forceinline__ double re() const { return (double)a.s.x + (double)a.c.x; }
-    __device__ __forceinline__ double im() const { return (double)a.s.y + (double)a.c.y; }
-};
-template <> struct Acc<float, SLOS_COMP_BIASED> {
-    float sr, si, cr, ci, sigma;
-    // the error sums start at -0, the identity of IEEE addition, so the first
-    // term's addition folds away
-    __device__ __forceinline__ void zero()
-    {
-        sr = si = sigma = 0.f;
-        cr = ci = -0.f;
-    }
-    __device__ __forceinline__ void start(float bias)
-    {
-        sigma = bias;
-        sr = bias;
-        si = bias;
-    }
-    __device__ __forceinline__ void mac(const float2 u, const float2 v)
-    {
-        acc_biased(sr, cr, u.x, v.x);
-        acc_biased(sr, cr, -u.y, v.y);
-        acc_biased(si, ci, u.x, v.y);
-        acc_biased(si, ci, u.y, v.x);
-    }
-    __device__ __forceinline__ float2 value() const { return float2{(sr - sigma) + cr, (si - sigma) + ci}; }
-    __device__ __forceinline__ double re() const { return (double)(sr - sigma) + (double)cr; }
-    __device__ __forceinline__ double im() const { return (double)(si - sigma) + (double)ci; }
-};
-
-// FP64 mode: each term's complex64 factors are widened to FP64, where their
-// products are exact (24-bit significands), and the products are summed with
-// FP64 FMAs: one FP64 rounding per real product, four FMAs and up to four
-// conversions per complex term (the FP64 FMA issues at the FP32 rate here).
-template <> struct Acc<float, SLOS_COMP_F64> {
-    double r, i;
-    __device__ __forceinline__ void zero() { r = i = 0.0; }
-    __device__ __forceinline__ void start(float) {}
-    __device__ __forceinline__ void mac(const float2 uf, const float2 v)
-    {
-        const double2 u{(double)uf.x, (double)uf.y};
-        const double vr = (double)v.x, vi = (double)v.y;
-        r = __builtin_fma(u.x, vr, r);
-        r = __builtin_fma(-u.y, vi, r);
-        i = __builtin_fma(u.x, vi, i);
-        i = __builtin_fma(u.y, vr, i);
-    }
-    __device__ __forceinline__ float2 value() const { return float2{(float)r, (float)i}; }
-    __device__ __forceinline__ double re() const { return r; }
-    __device__ __forceinline__ double im() const { return i; }
-};
 
 // cache-policy operand of the global-to-LDS copy: 0 = default, bit 1 =
 // non-temporal
@@ -533,7 +397,7 @@ __device__ __forceinline__ void tile_compute(const TileIn<T, RT> &in, const Laye
             const double f = L.fac_hi * in.lf[i];
             const double ar = acc[i].re() * f;
             const double ai = acc[i].im() * f;
-            const double pr = ar * ar + ai * ai;
+            const double pr = prob(ar, ai);
             psum += pr;
             if (MODE == SLOS_MODE_AMPL) {
                 T *y = (T *)((char *)Yb + in.off[i]);
@@ -666,7 +530,12 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? (RR == 2 ? 6 : 3) : (RR <= 2 
         for (int j = lane; j < p.m; j += 64) l1 += (float)(fabs(u_lds[j].x) + fabs(u_lds[j].y));
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) l1 += __shfl_xor(l1, o, 64);
-        const float vin = p.vmax_in ? __uint_as_float(*p.vmax_in) : 1.0f;
+        float vin = p.vmax_in ? 0.f : 1.f;
+        if (p.vmax_in) {
+            for (uint32_t i = lane; i < p.nvmax; i += 64) vin = fmaxf(vin, __uint_as_float(p.vmax_in[i]));
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) vin = fmaxf(vin, __shfl_xor(vin, o, 64));
+        }
         sigma = bias_for(l1 * vin * 1.001f);
     }
 
@@ -916,6 +785,26 @@ __global__ __launch_bounds__(256) void reduce_stage2(const double *__restrict__ 
     if (threadIdx.x == 0) *out = s;
 }
 
+// Few partials: one workgroup per instance sums them in one launch (per thread
+// strided, over lanes, then over waves in order).
+constexpr int64_t kReduceOnce = 4096;
+__global__ __launch_bounds__(1024) void reduce_once(const double *__restrict__ part, int64_t count,
+                                                    double *__restrict__ out, int64_t stride)
+{
+    __shared__ double sh[16];
+    part += (int64_t)blockIdx.x * stride;
+    double s = 0.0;
+    for (int64_t i = threadIdx.x; i < count; i += blockDim.x) s += part[i];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < (int)(blockDim.x >> 6); ++w) s += sh[w];
+        out[blockIdx.x] = s;
+    }
+}
+
 __global__ void zero_u32_kernel(uint32_t *buf, int count)
 {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += gridDim.x * blockDim.x) buf[i] = 0u;
@@ -982,6 +871,7 @@ hipError_t launch_mode(const LayerParams &p, const LayerLaunch &l, hipStream_t s
 
 int slos_launch_layer(const LayerParams &p, const LayerLaunch &l, void *stream)
 {
+    if (l.flat) return slos_launch_flat(*l.flat, stream);
     hipStream_t s = (hipStream_t)stream;
     if (l.c64) {
         if (l.compensated == SLOS_COMP_BIASED) return (int)launch_mode<float, SLOS_COMP_BIASED>(p, l, s);
@@ -995,6 +885,11 @@ int slos_launch_layer(const LayerParams &p, const LayerLaunch &l, void *stream)
 int slos_launch_reduce(const double *partials, int64_t count, double *stage, double *out, void *stream, int batch,
                        int64_t stride)
 {
+    if (count <= kReduceOnce) {
+        const int threads = (int)std::max<int64_t>(64, std::min<int64_t>(1024, (count + 63) / 64 * 64));
+        hipLaunchKernelGGL(reduce_once, dim3(batch), dim3(threads), 0, (hipStream_t)stream, partials, count, out, stride);
+        return (int)hipGetLastError();
+    }
     hipLaunchKernelGGL(reduce_stage1, dim3(kReduceBlocks, batch), dim3(256), 0, (hipStream_t)stream, partials, count,
                        stage, stride);
     hipError_t e = hipGetLastError();

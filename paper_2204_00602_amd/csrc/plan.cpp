@@ -21,6 +21,7 @@
 #include <thread>
 #include <vector>
 
+#include "flat.h"
 #include "slos_ext.h"
 
 namespace {
@@ -183,12 +184,10 @@ struct slos_plan_s {
     // device
     int device = -1;
     uint64_t *d_binom = nullptr;
-    LeafRec *d_leaves = nullptr;
-    std::vector<uint64_t> leaf_off;   // per layer offset into d_leaves
+    LeafRec *d_leaves = nullptr;      // ps_leaves
     unsigned char *d_desc = nullptr;  // leaf descriptors of all layers
     std::vector<uint64_t> desc_off;   // per layer byte offset into d_desc
     std::vector<int> desc_wide;       // per layer: wide descriptors
-    InnerType *d_types = nullptr;
     uint32_t *d_pred = nullptr;
     double *d_lowfac = nullptr;
     void *d_vac = nullptr;            // A_0 = [1]
@@ -202,7 +201,13 @@ struct slos_plan_s {
     uint64_t buf_stride[2] = {0, 0};  // elements per instance in d_buf[b]
     uint64_t g_stride = 0;            // elements per instance in d_g[b]
     uint64_t bpart_stride = 0;        // double2 per instance in d_bpart
-    uint32_t *d_tickets = nullptr;    // SLOS_XCDS ticket counters per layer
+    uint32_t *d_tickets = nullptr;    // SLOS_XCDS ticket counters per layer, then the first launch's maxima
+    // table-driven layers (flat.hip): 1..flat_kf, of which 1..flat_h + 1 are the
+    // first launch; 0 when a tiling option asks for the tiled kernels throughout
+    int flat_kf = 0, flat_h = 0;
+    std::vector<uint64_t> flat_off;   // per layer: first entry of its predecessor table
+    double *d_scale = nullptr;        // normalisation of every output (when the last layer is table-driven), then
+    uint32_t *d_flat = nullptr;       // the predecessor tables, in one allocation
     double *d_cdf = nullptr;          // block prefix of the last slos_cdf input (nb + 1), run prefixes, chunk sums, search tree
     int64_t *d_pk_ends = nullptr;     // C(K+n-1, n) for K = 1..m
     double *d_ps_partials = nullptr;  // post-selection partial sums + reduction stage
@@ -231,7 +236,6 @@ struct slos_plan_s {
     std::vector<PsType> ps_type_list;
     std::map<std::pair<int, int>, uint32_t> ps_type_of;
     bool ps_pass = false;             // gen_leaves is building ps_leaves
-    uint64_t ps_leaf_off = 0;         // ps_leaves in d_leaves
     size_t sel_cap = 0;
     // differentiation (SLOS_KEEP_LAYERS plans)
     std::vector<std::vector<BwdUnit>> units;   // per layer
@@ -252,6 +256,20 @@ struct slos_plan_s {
     hipGraphExec_t graph = nullptr;   // slos_plan_capture
 
     size_t elem() const { return c64 ? 8 : 16; }
+    // words of the ticket area of one instance: a line per layer and XCD, the
+    // first launch's maxima, and its count of ended workgroups
+    uint64_t ticket_words() const
+    {
+        return (uint64_t)(n + 1) * SLOS_XCDS * SLOS_TICKET_STRIDE + SLOS_HEAD_MAX_GROUPS + SLOS_TICKET_STRIDE;
+    }
+    // states per leaf of layer k: small layers get smaller leaves so that they
+    // still spread over about SLOS_TARGET_LEAVES workgroups
+    uint64_t leaf_cap(int k) const
+    {
+        return std::min<uint64_t>((uint64_t)opts.leaf_max,
+                                  std::max<uint64_t>(SLOS_MIN_LEAF, Nk[k] / SLOS_TARGET_LEAVES));
+    }
+    bool last_flat() const { return n > 0 && flat_kf == n; }
 
     uint32_t inner_type(int q, int K)
     {
@@ -464,6 +482,29 @@ struct slos_plan_s {
         }
     }
 
+    // Which layers are table-driven: all up to the first of more than
+    // SLOS_FLAT_MAX_STATES states, and of these the first launch keeps in LDS
+    // what fits its limits (N_k does not decrease with k).
+    void choose_flat()
+    {
+        while (flat_kf < n && Nk[flat_kf + 1] <= SLOS_FLAT_MAX_STATES) ++flat_kf;
+        const uint64_t most = batch_cap > 1 ? SLOS_HEAD_MAX_STATES_MANY : SLOS_HEAD_MAX_STATES;
+        while (flat_h + 1 < flat_kf && Nk[flat_h + 1] <= most &&
+               (Nk[flat_h] + Nk[flat_h + 1]) * elem() <= SLOS_HEAD_LDS_MAX)
+            ++flat_h;
+    }
+
+    // workgroup size and workgroups per instance of the first launch: one output
+    // of layer h + 1 per thread, at most about two workgroups per CU in all
+    void head_shape(int batch, int &threads, int &grid) const
+    {
+        const uint64_t No = Nk[flat_h + 1];
+        const uint64_t want = std::min<uint64_t>(1024, std::max(Nk[flat_h], No));
+        threads = (int)((want + 63) / 64 * 64);
+        const uint64_t most = batch > 1 ? std::max(1, SLOS_HEAD_MAX_GROUPS_MANY / batch) : SLOS_HEAD_MAX_GROUPS;
+        grid = (int)std::min<uint64_t>((No + threads - 1) / threads, most);
+    }
+
     void free_device()
     {
         auto f = [](void *p) {
@@ -473,7 +514,6 @@ struct slos_plan_s {
         f(d_leaves);
         f(d_desc);
         d_desc = nullptr;
-        f(d_types);
         f(d_pred);
         f(d_lowfac);
         f(d_vac);
@@ -483,6 +523,9 @@ struct slos_plan_s {
         f(d_partials);
         f(d_tickets);
         d_tickets = nullptr;
+        f(d_scale);
+        d_scale = nullptr;
+        d_flat = nullptr;
         f(d_cdf);
         d_cdf = nullptr;
         f(d_pk_ends);
@@ -519,7 +562,6 @@ struct slos_plan_s {
         d_photons = nullptr;
         d_binom = nullptr;
         d_leaves = nullptr;
-        d_types = nullptr;
         d_pred = nullptr;
         d_lowfac = nullptr;
         d_vac = nullptr;
@@ -555,10 +597,59 @@ int alloc_dev(void **dst, size_t bytes, const char *what)
     return SLOS_OK;
 }
 
+int clear_dev(void *p, size_t bytes)
+{
+    const hipError_t e = hipMemset(p, 0, bytes);  // plan time, never captured
+    return e == hipSuccess ? SLOS_OK : hip_fail(e, "counter reset");
+}
+
 int check_plan(slos_plan_t p)
 {
     if (!p) return fail(SLOS_ERR_INVALID_ARG, "plan is NULL");
     if (p->host_only) return fail(SLOS_ERR_INVALID_ARG, "plan was built with SLOS_HOST_ONLY");
+    return SLOS_OK;
+}
+
+int launch_flat(const FlatLaunch &l, void *stream)
+{
+    LayerLaunch ll{};
+    ll.flat = &l;
+    return slos_launch_layer(LayerParams{}, ll, stream);
+}
+
+// The tables of the table-driven layers, filled by a kernel.
+int build_flat(slos_plan_t p)
+{
+    FlatTables t{};
+    t.binom = p->d_binom;
+    t.bstride = p->B.stride;
+    t.m = p->m;
+    t.kf = p->flat_kf;
+    t.norm_t = p->norm_t;
+    uint64_t entries = 0;
+    p->flat_off.assign(p->flat_kf + 1, 0);
+    for (int k = 0; k <= p->flat_kf; ++k) {
+        t.N[k] = (uint32_t)p->Nk[k];
+        if (k == 0) continue;
+        p->flat_off[k] = t.off[k] = entries;
+        t.leaf_cap[k] = (uint32_t)p->leaf_cap(k);
+        entries += p->Nk[k] * (uint64_t)std::min(p->m, k);
+    }
+    int rc;
+    // the normalisation of every output, then the tables
+    const uint64_t nscale = p->last_flat() ? p->Nk[p->n] : 0;
+    if ((rc = alloc_dev((void **)&p->d_scale, nscale * sizeof(double) + entries * sizeof(uint32_t), "predecessor tables")))
+        return rc;
+    p->d_flat = (uint32_t *)(p->d_scale + nscale);
+    t.pred = p->d_flat;
+    t.scale = nscale ? p->d_scale : nullptr;
+    FlatLaunch l{};
+    l.tables = &t;
+    const int le = launch_flat(l, nullptr);
+    if (le) return hip_fail((hipError_t)le, "table kernel");
+    // the plan may be used from any stream
+    const hipError_t e = hipStreamSynchronize(nullptr);
+    if (e != hipSuccess) return hip_fail(e, "table kernel");
     return SLOS_OK;
 }
 
@@ -640,6 +731,9 @@ int slos_plan_ex(int m, int n, const int32_t *input_state, int flags, const slos
 
     slos_options_t o{};
     if (opts) o = *opts;
+    // an option that shapes the tiling asks for the tiled kernels on every layer
+    const bool tiled = o.leaf_max || o.block_threads || o.grid_blocks || o.outputs_per_lane || o.xcd_chunk ||
+                       o.ticket_leaves || o.wide_descriptors || o.leaf_order || o.low_block_max;
     // defaults: the fastest settings of a coordinate-descent search at
     // m=24, n=12 on gfx950 (a c128 low block of an 8192-state leaf takes
     // enough LDS to halve the resident workgroups, hence the smaller leaves)
@@ -713,12 +807,8 @@ int slos_plan_ex(int m, int n, const int32_t *input_state, int flags, const slos
         p->leaves.resize(n + 1);
         p->low_max.assign(n + 1, 0);
         for (int k = 1; k <= n; ++k) {
-            // small layers get smaller leaves so that they still spread over
-            // about SLOS_TARGET_LEAVES workgroups
-            const uint64_t cap = std::min<uint64_t>((uint64_t)o.leaf_max,
-                                                    std::max<uint64_t>(SLOS_MIN_LEAF, p->Nk[k] / SLOS_TARGET_LEAVES));
             std::vector<uint8_t> hm;
-            p->gen_leaves(k, m - 1, k, cap, hm, p->leaves[k]);
+            p->gen_leaves(k, m - 1, k, p->leaf_cap(k), hm, p->leaves[k]);
             for (const LeafRec &L : p->leaves[k])
                 p->low_max[k] = std::max(p->low_max[k], p->types[L.tab].low_size);
             // grouped order by default (depth 1: leaves that share the block
@@ -761,6 +851,7 @@ int slos_plan_ex(int m, int n, const int32_t *input_state, int flags, const slos
         *out = p;
         return SLOS_OK;
     }
+    if (!tiled && n > 0) p->choose_flat();
 
     int ndev = 0;
     hipError_t e = hipGetDeviceCount(&ndev);
@@ -771,15 +862,6 @@ int slos_plan_ex(int m, int n, const int32_t *input_state, int flags, const slos
     (void)hipGetDevice(&p->device);
 
     // upload tables
-    std::vector<LeafRec> all;
-    p->leaf_off.assign(n + 2, 0);
-    for (int k = 1; k <= n; ++k) {
-        p->leaf_off[k] = all.size();
-        all.insert(all.end(), p->leaves[k].begin(), p->leaves[k].end());
-    }
-    p->leaf_off[n + 1] = all.size();
-    p->ps_leaf_off = all.size();
-    all.insert(all.end(), p->ps_leaves.begin(), p->ps_leaves.end());
     std::vector<unsigned char> descs;
     p->desc_off.assign(n + 2, 0);
     p->desc_wide.assign(n + 1, 0);
@@ -787,6 +869,8 @@ int slos_plan_ex(int m, int n, const int32_t *input_state, int flags, const slos
         std::vector<uint64_t> deltas;
         std::vector<uint8_t> modes;
         for (int k = 1; k <= n; ++k) {
+            p->desc_off[k] = descs.size();
+            if (k <= p->flat_kf && !(p->keep && k == n)) continue;  // table-driven: no descriptors
             // narrow unless a leaf has more than 16 groups or a 64-bit delta
             int wide = p->opts.wide_descriptors > 0 ? 1 : 0;
             for (const LeafRec &L : p->leaves[k]) {
@@ -798,7 +882,6 @@ int slos_plan_ex(int m, int n, const int32_t *input_state, int flags, const slos
                 if (wide) break;
             }
             p->desc_wide[k] = wide;
-            p->desc_off[k] = descs.size();
             const size_t rec = wide ? sizeof(LeafDescWide) : sizeof(LeafDescNarrow);
             descs.resize(descs.size() + rec * p->leaves[k].size());
             unsigned char *dst = descs.data() + p->desc_off[k];
@@ -831,11 +914,11 @@ int slos_plan_ex(int m, int n, const int32_t *input_state, int flags, const slos
         return fail(SLOS_ERR_OOM, "host allocation failed while building leaf descriptors");
     }
     if ((rc = dev_upload(&p->d_binom, p->B.t.data(), p->B.t.size(), "binomial table")) ||
-        (rc = dev_upload(&p->d_leaves, all.data(), all.size(), "leaf table")) ||
-        (rc = dev_upload(&p->d_desc, descs.data(), descs.size(), "leaf descriptors")) ||
-        (rc = dev_upload(&p->d_types, p->types.data(), p->types.size(), "inner types")) ||
-        (rc = dev_upload(&p->d_pred, p->pred.data(), p->pred.size(), "inner predecessor table")) ||
-        (rc = dev_upload(&p->d_lowfac, p->lowfac.data(), p->lowfac.size(), "inner factorial table"))) {
+        (rc = dev_upload(&p->d_leaves, p->ps_leaves.data(), p->ps_leaves.size(), "post-selection leaves")) ||
+        (!descs.empty() &&  // no tiled layers: nothing reads their tables
+         ((rc = dev_upload(&p->d_desc, descs.data(), descs.size(), "leaf descriptors")) ||
+          (rc = dev_upload(&p->d_pred, p->pred.data(), p->pred.size(), "inner predecessor table")) ||
+          (rc = dev_upload(&p->d_lowfac, p->lowfac.data(), p->lowfac.size(), "inner factorial table"))))) {
         p->free_device();
         delete p;
         return rc;
@@ -900,11 +983,14 @@ int slos_plan_ex(int m, int n, const int32_t *input_state, int flags, const slos
             }
     }
     p->n_partials = n > 0 ? (int64_t)p->leaves[n].size() * (p->opts.block_threads / 64) : 1;
+    if (p->last_flat())
+        p->n_partials = std::max<int64_t>(SLOS_HEAD_MAX_GROUPS,
+                                          (int64_t)((p->Nk[n] + SLOS_FLAT_THREADS - 1) / SLOS_FLAT_THREADS));
     if ((rc = alloc_dev((void **)&p->d_partials,
                         (size_t)(p->n_partials + SLOS_REDUCE_STAGE) * p->batch_cap * sizeof(double), "partial sums")) ||
         (rc = alloc_dev((void **)&p->d_tickets,
-                        (size_t)(n + 1) * SLOS_XCDS * SLOS_TICKET_STRIDE * p->batch_cap * sizeof(uint32_t),
-                        "ticket counters"))) {
+                        (size_t)p->ticket_words() * p->batch_cap * sizeof(uint32_t), "ticket counters")) ||
+        (rc = clear_dev(p->d_tickets, (size_t)p->ticket_words() * p->batch_cap * sizeof(uint32_t)))) {
         p->free_device();
         delete p;
         return rc;
@@ -980,6 +1066,11 @@ int slos_plan_ex(int m, int n, const int32_t *input_state, int flags, const slos
             delete p;
             return rc;
         }
+    }
+    if (p->flat_kf > 0 && (rc = build_flat(p))) {
+        p->free_device();
+        delete p;
+        return rc;
     }
     *out = p;
     return SLOS_OK;
@@ -1081,10 +1172,41 @@ static int run_forward(slos_plan_t p, int batch, const void *U, void *out, doubl
     const size_t es = p->elem();
     const int wpb = p->opts.block_threads / 64;
     hipStream_t hs = (hipStream_t)stream;
-    const uint64_t tstride = (uint64_t)(n + 1) * SLOS_XCDS * SLOS_TICKET_STRIDE;
+    const uint64_t tstride = p->ticket_words();
+    const uint64_t tline = (uint64_t)SLOS_XCDS * SLOS_TICKET_STRIDE;  // one layer's counters
     const ForwardScratch sc = over ? *over : ForwardScratch{p->d_vac, {p->d_buf[0], p->d_buf[1]}, p->d_partials,
                                                             p->d_tickets};
-    {
+    const bool biased = p->comp && !(p->flags & (SLOS_COMP_KNUTH | SLOS_COMP_FP64));
+    auto comp_of = [&](int k) -> int {
+        if (!p->comp || k < p->opts.comp_from_layer) return SLOS_COMP_NONE;
+        return (p->flags & SLOS_COMP_KNUTH) ? SLOS_COMP_TWOSUM : biased ? SLOS_COMP_BIASED : SLOS_COMP_F64;
+    };
+    // where layer k is read and written (one instance), and the bytes between instances
+    auto layer_at = [&](int k, uint64_t &stride) -> void * {
+        if (k == n) {
+            stride = out_bytes;
+            return out;
+        }
+        if (p->keep) {
+            stride = p->keep_stride * es;
+            return (char *)p->d_keep + p->keep_off[k] * es;
+        }
+        stride = k == 0 ? 0 : p->buf_stride[k & 1] * es;  // every instance reads the one vacuum
+        return k == 0 ? sc.vac : sc.buf[k & 1];
+    };
+    // the recorded maximum of layer k (biased compensation): SLOS_FLAT_VMAX
+    // values from a table-driven layer, one from a tiled one
+    auto vmax_slot = [&](int k) {
+        return sc.tickets + (uint64_t)k * tline + (k <= p->flat_kf ? 0 : SLOS_VMAX_SLOT);
+    };
+    auto needs_vmax = [&](int k) { return biased && k < n && k + 1 >= p->opts.comp_from_layer; };
+    uint32_t *head_vm = sc.tickets + (uint64_t)(n + 1) * tline;
+    // the first launch's count of ended workgroups is zero between passes (not
+    // in the static scratch, which other plans write over)
+    uint32_t *head_count = over ? nullptr : head_vm + SLOS_HEAD_MAX_GROUPS;
+    int64_t n_part = p->n_partials;  // partials of sum P per instance that this pass writes (0: the sum itself)
+    int head_grid = 0;
+    if (!p->flat_kf) {
         int e = slos_launch_zero_u32(sc.tickets, (int)(tstride * batch), stream);
         if (e) return hip_fail((hipError_t)e, "ticket reset kernel");
     }
@@ -1093,44 +1215,114 @@ static int run_forward(slos_plan_t p, int batch, const void *U, void *out, doubl
         if (e != hipSuccess) return hip_fail(e, "timing event");
         p->timed_reduce = false;
     }
-    for (int k = 1; k <= n; ++k) {
-        LayerParams lp{};
-        if (p->keep) {
-            lp.X = (const char *)p->d_keep + p->keep_off[k - 1] * es;
-            lp.Y = k == n ? out : (void *)((char *)p->d_keep + p->keep_off[k] * es);
-            lp.x_stride = p->keep_stride * es;
-            lp.y_stride = k == n ? out_bytes : p->keep_stride * es;
-        } else {
-            lp.X = k == 1 ? sc.vac : sc.buf[(k - 1) & 1];
-            lp.Y = k == n ? out : sc.buf[k & 1];
-            lp.x_stride = k == 1 ? 0 : p->buf_stride[(k - 1) & 1] * es;  // every instance reads the one vacuum
-            lp.y_stride = k == n ? out_bytes : p->buf_stride[k & 1] * es;
+    auto record = [&](int k) -> hipError_t { return p->timing ? hipEventRecord(p->events[k], hs) : hipSuccess; };
+    int k0 = 1;
+    if (p->flat_kf) {
+        // layers 1..h + 1
+        const int h = p->flat_h;
+        HeadParams hp{};
+        FlatLaunch fl{};
+        hp.U = U;
+        hp.u_stride = (uint64_t)p->m * p->m * es;
+        hp.Y = layer_at(h + 1, hp.y_stride);
+        hp.pred = p->d_flat;
+        hp.m = p->m;
+        hp.h = h;
+        hp.comp_from = p->opts.comp_from_layer;
+        for (int k = 0; k <= h + 1; ++k) {
+            hp.N[k] = (uint32_t)p->Nk[k];
+            if (k == 0) continue;
+            hp.off[k] = p->flat_off[k];
+            hp.col[k] = (uint8_t)p->photons[k - 1];
+            if (p->keep && k < n) hp.keep_off[k] = p->keep_off[k] * es;
         }
+        hp.cap[0] = hp.cap[1] = 1;
+        for (int k = 0; k <= h; ++k) hp.cap[k & 1] = std::max(hp.cap[k & 1], hp.N[k] + 1);
+        if (p->keep) {
+            hp.keep = p->d_keep;
+            hp.keep_stride = p->keep_stride * es;
+        }
+        hp.zero_stride = hp.vm_stride = tstride;
+        if (h + 2 <= n && (biased || p->flat_kf < n)) {
+            hp.zero = sc.tickets + (uint64_t)(h + 2) * tline;
+            hp.nzero = (uint32_t)((uint64_t)(n - h - 1) * tline);
+        }
+        hp.vm = needs_vmax(h + 1) ? (float *)head_vm : nullptr;
+        hp.scale = p->d_scale;
+        hp.partials = sc.partials;
+        hp.partials_stride = (uint64_t)p->n_partials;
+        hp.sum_p = sum_p;
+        p->head_shape(batch, fl.threads, head_grid);
+        fl.head = &hp;
+        fl.grid = head_grid;
+        fl.batch = batch;
+        fl.c64 = p->c64;
+        fl.mode = h + 1 == n ? last_mode : SLOS_MODE_MID;
+        fl.compensated = p->comp ? comp_of(std::max(h + 1, p->opts.comp_from_layer)) : SLOS_COMP_NONE;
+        if (h + 1 == n) {
+            hp.count = sum_p && head_grid > 1 ? head_count : nullptr;
+            hp.count_stride = tstride;
+            n_part = head_grid > 1 && !hp.count ? head_grid : 0;
+        }
+        int e = launch_flat(fl, stream);
+        if (e) return hip_fail((hipError_t)e, "first layers");
+        for (int k = 1; k <= h + 1; ++k)  // one launch: its time is counted at its first layer
+            if ((e = (int)record(k))) return hip_fail((hipError_t)e, "timing event");
+        k0 = h + 2;
+    }
+    for (int k = k0; k <= p->flat_kf; ++k) {
+        FlatParams fp{};
+        FlatLaunch fl{};
+        fp.X = layer_at(k - 1, fp.x_stride);
+        fp.Y = layer_at(k, fp.y_stride);
+        fp.U = U;
+        fp.u_stride = (uint64_t)p->m * p->m * es;
+        fp.pred = p->d_flat + p->flat_off[k];
+        fp.N = (uint32_t)p->Nk[k];
+        fp.Nprev = (uint32_t)p->Nk[k - 1];
+        fp.cmax = (uint32_t)std::min(p->m, k);
+        fp.m = p->m;
+        fp.col = p->photons[k - 1];
+        fp.scale = p->d_scale;
+        fp.partials = sc.partials;
+        fp.partials_stride = (uint64_t)p->n_partials;
+        fl.compensated = comp_of(k);
+        if (fl.compensated == SLOS_COMP_BIASED) {
+            fp.vmax_in = k == k0 ? head_vm : vmax_slot(k - 1);
+            fp.nvmax = k == k0 ? (uint32_t)head_grid : SLOS_FLAT_VMAX;
+            fp.vin_stride = tstride;
+        }
+        fp.vmax_out = needs_vmax(k) ? vmax_slot(k) : nullptr;
+        fp.vout_stride = tstride;
+        fl.flat = &fp;
+        fl.batch = batch;
+        fl.c64 = p->c64;
+        fl.mode = k == n ? last_mode : SLOS_MODE_MID;
+        if (k == n) n_part = (int64_t)((p->Nk[n] + SLOS_FLAT_THREADS - 1) / SLOS_FLAT_THREADS);
+        int e = launch_flat(fl, stream);
+        if (e) return hip_fail((hipError_t)e, "table-driven layer");
+        if ((e = (int)record(k))) return hip_fail((hipError_t)e, "timing event");
+    }
+    for (int k = std::max(p->flat_kf + 1, 1); k <= n; ++k) {
+        LayerParams lp{};
+        lp.X = layer_at(k - 1, lp.x_stride);
+        lp.Y = layer_at(k, lp.y_stride);
         lp.u_stride = (uint64_t)p->m * p->m * es;
         lp.partials_stride = (uint64_t)p->n_partials;
         lp.ticket_stride = tstride;
         lp.U = U;
-        lp.leaves = p->d_leaves + p->leaf_off[k];
         lp.desc = p->d_desc + p->desc_off[k];
         lp.nleaves = p->leaves[k].size();
-        lp.types = p->d_types;
         lp.pred = p->d_pred;
         lp.lowfac = p->d_lowfac;
-        lp.binom = p->d_binom;
-        lp.bstride = p->B.stride;
         lp.m = p->m;
         lp.k = k;
         lp.col = p->photons[k - 1];
-        lp.norm_t = p->norm_t;
         lp.partials = sc.partials;
         LayerLaunch ll{};
         ll.c64 = p->c64;
         ll.mode = k == n ? last_mode : SLOS_MODE_MID;
-        ll.compensated = (p->comp && k >= p->opts.comp_from_layer)
-                             ? ((p->flags & SLOS_COMP_KNUTH)  ? SLOS_COMP_TWOSUM
-                                : (p->flags & SLOS_COMP_FP64) ? SLOS_COMP_F64
-                                                              : SLOS_COMP_BIASED)
-                             : SLOS_COMP_NONE;
+        ll.compensated = comp_of(k);
         ll.rr = p->opts.outputs_per_lane;
         ll.batch = batch;
         ll.threads = p->opts.block_threads;
@@ -1149,28 +1341,27 @@ static int run_forward(slos_plan_t p, int batch, const void *U, void *out, doubl
         lp.xcd_chunk = (uint32_t)std::max<uint64_t>(
             1, std::min<uint64_t>((uint64_t)p->opts.xcd_chunk, lp.nleaves / (4 * SLOS_XCDS)));
         lp.tickets = sc.tickets + (size_t)k * SLOS_XCDS * SLOS_TICKET_STRIDE;
-        const bool comp_k = ll.compensated == SLOS_COMP_BIASED;
-        const bool comp_next = k < n && p->comp && !(p->flags & (SLOS_COMP_KNUTH | SLOS_COMP_FP64)) &&
-                               k + 1 >= p->opts.comp_from_layer;
-        lp.vmax_in = (comp_k && k >= 2)
-                         ? sc.tickets + (size_t)(k - 1) * SLOS_XCDS * SLOS_TICKET_STRIDE + SLOS_VMAX_SLOT
-                         : nullptr;
-        lp.vmax_out = comp_next ? lp.tickets + SLOS_VMAX_SLOT : nullptr;
+        // the maxima of a layer written by the first launch are one per workgroup
+        const bool after_head = p->flat_kf && k == k0;
+        if (ll.compensated == SLOS_COMP_BIASED && k >= 2) {
+            lp.vmax_in = after_head ? head_vm : vmax_slot(k - 1);
+            lp.nvmax = after_head ? (uint32_t)head_grid : k - 1 <= p->flat_kf ? SLOS_FLAT_VMAX : 1u;
+        }
+        lp.vmax_out = needs_vmax(k) ? vmax_slot(k) : nullptr;
         lp.ticket_leaves = (uint32_t)p->opts.ticket_leaves;
 
         int e = slos_launch_layer(lp, ll, stream);
         if (e) return hip_fail((hipError_t)e, "layer kernel");
         if (p->timing && (e = (int)hipEventRecord(p->events[k], hs)))
             return hip_fail((hipError_t)e, "timing event");
-        if (k == n && sum_p) {
-            e = slos_launch_reduce(sc.partials, p->n_partials, sc.partials + p->n_partials * p->batch_cap, sum_p,
-                                   stream, batch, p->n_partials);
-            if (e) return hip_fail((hipError_t)e, "sum reduction kernel");
-            if (p->timing) {
-                if ((e = (int)hipEventRecord(p->events[n + 1], hs)))
-                    return hip_fail((hipError_t)e, "timing event");
-                p->timed_reduce = true;
-            }
+    }
+    if (sum_p && n_part > 0) {
+        int e = slos_launch_reduce(sc.partials, n_part, sc.partials + p->n_partials * p->batch_cap, sum_p, stream, batch,
+                                   p->n_partials);
+        if (e) return hip_fail((hipError_t)e, "sum reduction kernel");
+        if (p->timing) {
+            if ((e = (int)hipEventRecord(p->events[n + 1], hs))) return hip_fail((hipError_t)e, "timing event");
+            p->timed_reduce = true;
         }
     }
     return SLOS_OK;
@@ -1433,7 +1624,7 @@ int slos_amplitudes_noalloc(slos_plan_t p, const void *U, void *out, double *sum
     const size_t b_buf1 = p->buf_stride[1] ? round256(p->buf_stride[1] * es + SLOS_BUFFER_SLACK) : 0;
     // (the reduction stage follows the partials of max_batch instances)
     const size_t b_part = round256((size_t)(p->n_partials * p->batch_cap + SLOS_REDUCE_STAGE) * sizeof(double));
-    const size_t b_tick = round256((size_t)(n + 1) * SLOS_XCDS * SLOS_TICKET_STRIDE * sizeof(uint32_t));
+    const size_t b_tick = round256((size_t)p->ticket_words() * sizeof(uint32_t));
     const size_t need = b_vac + b_buf0 + b_buf1 + b_part + b_tick;
     if (need > SLOS_STATIC_SCRATCH_BYTES)
         return fail(SLOS_ERR_SIZE_OVERFLOW,
@@ -1453,7 +1644,7 @@ int slos_amplitudes_noalloc(slos_plan_t p, const void *U, void *out, double *sum
     sc.buf[1] = b_buf1 ? c + b_vac + b_buf0 : nullptr;
     sc.partials = (double *)(c + b_vac + b_buf0 + b_buf1);
     sc.tickets = (uint32_t *)(c + b_vac + b_buf0 + b_buf1 + b_part);
-    if (n > 0) {
+    if (n > 0 && !p->flat_kf) {
         // the area keeps whatever the last call left: A_0 = [1] is written afresh
         // (the ticket counters are zeroed by the pass itself, and the partials
         // and the reduction stage are written before they are read)
@@ -1577,7 +1768,7 @@ int slos_postselect(slos_plan_t p, const void *probs, const int32_t *group_of_mo
     ps.run = (M + threads - 1) / threads;
     ps.partials = p->d_ps_partials;
     if (p->n > 0) {
-        ps.leaves = p->d_leaves + p->ps_leaf_off;
+        ps.leaves = p->d_leaves;
         ps.nleaves = p->ps_leaves.size();
         ps.type_off = p->d_ps_type_off;
         ps.types = p->d_ps_types;

@@ -110,18 +110,13 @@ struct LayerParams {
     const void *X;          // A_{k-1} (device)
     void *Y;                // A_k, a or P (device)
     const void *U;          // m x m, row = output mode (device)
-    const LeafRec *leaves;  // leaves of layer k (device)
     const void *desc;       // LeafDescNarrow or LeafDescWide array of layer k (device)
     uint64_t nleaves;
-    const InnerType *types;
     const uint32_t *pred;
     const double *lowfac;
-    const uint64_t *binom;  // binom[a * bstride + b] = C(a, b)
-    int bstride;
     int m;
     int k;                  // layer index (photons in the output states)
     int col;                // input mode i_k of the photon added at this layer
-    double norm_t;          // 1 / sqrt(prod_i t_i!)
     double *partials;       // one FP64 partial sum of P per leaf (last layer)
     uint32_t low_max;       // largest low block of the layer (elements)
     uint32_t lds_wave_bytes;// LDS bytes of one low-block staging slice
@@ -136,10 +131,11 @@ struct LayerParams {
     uint32_t *tickets;
     uint32_t ticket_leaves;  // consecutive leaves per ticket
     // Compensated layers: max over A_{k-1} of |Re x| + |Im x| as float bits
-    // (NULL: the vacuum, 1), and where this layer records the same for A_k
+    // (NULL: the vacuum, 1; nvmax values, whose largest counts), and where this layer records the same for A_k
     // (NULL: not recorded).  Both live in the zeroed ticket area.
     const uint32_t *vmax_in;
     uint32_t *vmax_out;
+    uint32_t nvmax;          // maxima at vmax_in (the first launch leaves one per workgroup)
     // Many unitaries through one plan: instance b = blockIdx.y reads X + b *
     // x_stride and U + b * u_stride, writes Y + b * y_stride (bytes), and uses
     // partials + b * partials_stride and tickets (with the vmax slots) +
@@ -149,7 +145,10 @@ struct LayerParams {
     uint64_t ticket_stride;
 };
 
+struct FlatLaunch;  // flat.h
+
 struct LayerLaunch {
+    const FlatLaunch *flat;  // a launch of the table-driven layers instead (the rest is unused)
     int c64;          // 1: complex64, 0: complex128
     int mode;         // SlosLayerMode
     int compensated;  // c64 only: SLOS_COMP_NONE / _BIASED / _TWOSUM
