@@ -15,6 +15,7 @@
 // order.
 #include <hip/hip_runtime.h>
 
+#include "flat.h"
 #include "slos_internal.h"
 
 namespace {
@@ -520,6 +521,7 @@ static hipError_t allow_lds(K kernel, bool &done)
 
 int slos_launch_bwd_layer(const BwdParams &p, int c64, int grid, void *stream, int batch)
 {
+    if (p.flat) return slos_launch_flat_bwd(*p.flat, c64, batch, stream);
     static bool a32 = false, a64 = false;
     hipError_t e = c64 ? allow_lds(bwd_layer_kernel<float>, a32) : allow_lds(bwd_layer_kernel<double>, a64);
     if (e != hipSuccess) return (int)e;

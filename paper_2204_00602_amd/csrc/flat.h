@@ -4,6 +4,12 @@
 
 #include "slos_internal.h"
 
+#if defined(__HIPCC__)
+#define SLOS_HD __host__ __device__
+#else
+#define SLOS_HD
+#endif
+
 // Table entries are (mode << 24) | rank.  A padded entry names mode m, whose
 // coefficient is held at zero, and the state after the last of layer k - 1,
 // taken as zero: it adds nothing, whatever the layer's values are.
@@ -83,7 +89,8 @@ struct FlatTables {
     uint32_t leaf_cap[SLOS_MAX_PHOTONS + 1];  // the tiled kernel's leaf size of each layer
     double *scale;               // of layer kf, or NULL
     double norm_t;
-    uint32_t *succ;              // mode-major: succ[succ_off[k] + j * N[k - 1] + y] = rank of y + e_j, or NULL
+    uint32_t *succ;              // mode-major: succ[succ_off[k] + j * N[k - 1] + y] = rank of y + e_j
+    int kb;                      // layers with a successor table: 1..kb
     uint64_t succ_off[SLOS_MAX_PHOTONS + 1];
 };
 
@@ -97,3 +104,84 @@ struct FlatLaunch {
     int threads;                 // head: workgroup size
 };
 int slos_launch_flat(const FlatLaunch &l, void *stream);
+
+// ---- adjoint of the table-driven layers (flat_bwd.hip) -------------------------
+
+#define SLOS_BWD_LDS_MAX (149u * 1024u)
+// Reverse layers of at most this many terms (states of layer k - 1 times modes)
+// run in the one-workgroup tail: 52,416 terms (m=12, n=6, layer 6) take it 9.8
+// us, and a launch of their own at least 5 with a seed or loss launch before it.
+#define SLOS_BWD_TAIL_TERMS 60000u
+#define SLOS_BWD_THREADS 512     // of a reverse layer
+#define SLOS_BWD_TAIL_THREADS 1024
+// Modes whose gradient sums a thread of the tail keeps in registers.
+#define SLOS_BWD_TAIL_MODES 12
+
+// One reverse layer: g_{k-1} and, per workgroup, the gradient partials of every mode.
+struct FlatBwdParams {
+    const void *gk;              // g_k, or dL/da with `scale` (then g_n = scale * dL/da)
+    const double *scale;
+    void *gkm1;
+    const void *Akm1;
+    const void *U;
+    const uint32_t *succ;        // mode-major, N entries per mode
+    void *partials;              // double2 [workgroups][m]
+    uint64_t gk_stride, gkm1_stride, a_stride, u_stride, partials_stride;  // bytes per instance (blockIdx.y)
+    uint32_t N;                  // states of layer k - 1
+    int m, col;
+};
+
+// Reverse layers t..1 and the assembly of G_U, one workgroup per instance.
+struct TailParams {
+    const void *gt;              // g_t, or dL/da with `scale`; unused with a loss
+    const double *scale;
+    const void *keep;            // kept layers
+    const void *U;
+    void *GU;
+    const uint32_t *succ;
+    const void *partials;        // of the layers above t: double2 [rows[k]][m] at part_off[k]
+    // squared-error loss on target outputs as the source of g_n (t = n), or a = NULL
+    const void *a;
+    const int64_t *ranks;
+    const double *target_scale;
+    const double *p_target;
+    double *loss;
+    int64_t count;
+    uint64_t gt_stride, keep_stride, u_stride, gu_stride, partials_stride;  // bytes per instance (blockIdx.x)
+    uint64_t a_stride;           // elements
+    uint64_t keep_off[SLOS_MAX_PHOTONS + 1];   // bytes
+    uint64_t succ_off[SLOS_MAX_PHOTONS + 1];   // entries
+    uint64_t part_off[SLOS_MAX_PHOTONS + 1];   // double2
+    uint32_t rows[SLOS_MAX_PHOTONS + 1];
+    uint32_t N[SLOS_MAX_PHOTONS + 1];
+    uint32_t cap[2];             // elements of the even and the odd LDS buffer
+    int m, n, t;
+    int wave_rows;               // sum of slos_tail_waves over its layers
+    uint8_t col[SLOS_MAX_PHOTONS + 1];
+};
+
+struct FlatBwdLaunch {
+    const FlatBwdParams *layer;  // exactly one is set
+    const TailParams *tail;
+    int per_thread;              // layer: states per thread (1, 2 or 4)
+};
+int slos_launch_flat_bwd(const FlatBwdLaunch &l, int c64, int batch, void *stream);
+
+// states of a workgroup of one reverse layer, and LDS bytes of the tail
+static inline uint32_t slos_bwd_rows(uint64_t N, int per_thread)
+{
+    return (uint32_t)((N + (uint64_t)per_thread * SLOS_BWD_THREADS - 1) / ((uint64_t)per_thread * SLOS_BWD_THREADS));
+}
+// the g buffers hold four layers' partial sums per thread at the end
+static inline uint64_t slos_tail_lds(uint64_t cap0, uint64_t cap1, int m, int n, int t, int wave_rows, uint64_t es)
+{
+    const uint64_t g = (cap0 + cap1) * es, red = t < n ? 4u * (uint64_t)SLOS_BWD_TAIL_THREADS * 16u : 0u;
+    return (g > red ? g : red) + 16u * ((uint64_t)t * (m + 16) + (uint64_t)(n + 1 + wave_rows) * m);
+}
+// waves of the tail that have a state of a layer of N states: four lanes a
+// state up to SLOS_BWD_TAIL_THREADS states, else one
+SLOS_HD static inline int slos_tail_waves(uint32_t N)
+{
+    const uint32_t w = N <= SLOS_BWD_TAIL_THREADS ? (N + 15u) / 16u : SLOS_BWD_TAIL_THREADS / 64u;
+    return (int)(w < SLOS_BWD_TAIL_THREADS / 64u ? w : SLOS_BWD_TAIL_THREADS / 64u);
+}

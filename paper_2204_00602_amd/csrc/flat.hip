@@ -432,7 +432,7 @@ __device__ __forceinline__ void unrank_photons(const FlatTables &p, int k, uint6
 
 // Predecessor (and successor) tables: blockIdx.y < kf is layer blockIdx.y + 1's
 // predecessor table (and, for the last one, its normalisation), the others the
-// successor tables of the same layers.
+// successor tables of layers 1..kb.
 __global__ __launch_bounds__(256) void table_kernel(FlatTables p)
 {
     const bool succ = (int)blockIdx.y >= p.kf;
@@ -562,7 +562,7 @@ int slos_launch_flat(const FlatLaunch &l, void *stream)
         const FlatTables &t = *l.tables;
         uint32_t most = 1;
         for (int k = 1; k <= t.kf; ++k) most = std::max(most, t.N[k]);
-        hipLaunchKernelGGL(table_kernel, dim3((most + 255) / 256, t.kf * (t.succ ? 2 : 1)), dim3(256), 0, s, t);
+        hipLaunchKernelGGL(table_kernel, dim3((most + 255) / 256, t.kf + t.kb), dim3(256), 0, s, t);
         return (int)hipGetLastError();
     }
     if (!l.c64) return (int)launch_comp<double, SLOS_COMP_NONE>(l, s);

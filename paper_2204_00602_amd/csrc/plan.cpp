@@ -205,6 +205,10 @@ struct slos_plan_s {
     // table-driven layers (flat.hip): 1..flat_kf, of which 1..flat_h + 1 are the
     // first launch; 0 when a tiling option asks for the tiled kernels throughout
     int flat_kf = 0, flat_h = 0;
+    int bwd_kb = 0, bwd_t = 0;        // table-driven reverse layers 1..bwd_kb, of which 1..bwd_t are the tail launch
+    std::vector<uint64_t> bwd_succ_off;  // per layer: first entry of its successor table
+    std::vector<int> bwd_pt;          // per layer: states per thread
+    uint32_t *d_bwd_succ = nullptr;   // successor tables of the table-driven reverse layers
     std::vector<uint64_t> flat_off;   // per layer: first entry of its predecessor table
     double *d_scale = nullptr;        // normalisation of every output (when the last layer is table-driven), then
     uint32_t *d_flat = nullptr;       // the predecessor tables, in one allocation
@@ -270,6 +274,11 @@ struct slos_plan_s {
                                   std::max<uint64_t>(SLOS_MIN_LEAF, Nk[k] / SLOS_TARGET_LEAVES));
     }
     bool last_flat() const { return n > 0 && flat_kf == n; }
+    // rows of gradient partials of reverse layer k
+    uint64_t bwd_rows(int k) const
+    {
+        return k <= bwd_kb ? slos_bwd_rows(Nk[k - 1], bwd_pt[k]) : units[k].size();
+    }
 
     uint32_t inner_type(int q, int K)
     {
@@ -439,7 +448,6 @@ struct slos_plan_s {
 
     void build_units(int k)
     {
-        if ((int)unit_chunk.size() <= k) unit_chunk.resize(k + 1, 128u);
         uint32_t ch = 128;
         while (ch < 1024 && (Nk[k - 1] / ch) * (uint64_t)batch_cap > 8192) ch *= 2;
         unit_chunk[k] = ch;
@@ -492,6 +500,28 @@ struct slos_plan_s {
         while (flat_h + 1 < flat_kf && Nk[flat_h + 1] <= most &&
                (Nk[flat_h] + Nk[flat_h + 1]) * elem() <= SLOS_HEAD_LDS_MAX)
             ++flat_h;
+    }
+
+    // Reverse layers from tables: those whose layer k - 1 has a table-driven
+    // size; of these the tail takes what fits one workgroup's LDS and time.
+    void choose_flat_bwd()
+    {
+        bwd_kb = std::min(n, flat_kf + 1);
+        int rows = 0;
+        while (bwd_t < bwd_kb) {
+            const int k = bwd_t + 1;
+            const uint64_t cap[2] = {Nk[k & 1 ? k - 1 : k], Nk[k & 1 ? k : k - 1]};
+            rows += slos_tail_waves((uint32_t)Nk[k - 1]);
+            if (slos_tail_lds(cap[0], cap[1], m, n, k, rows, elem()) > SLOS_BWD_LDS_MAX) break;
+            if (k > 1 && Nk[k - 1] * (uint64_t)m > SLOS_BWD_TAIL_TERMS) break;
+            bwd_t = k;
+        }
+        if (bwd_t == 0) bwd_kb = 0;
+        bwd_pt.assign(n + 1, 1);
+        for (int k = bwd_t + 1; k <= bwd_kb; ++k) {
+            const uint64_t groups = (Nk[k - 1] * (uint64_t)batch_cap + 255) / 256;
+            bwd_pt[k] = groups >= 8192 ? 4 : groups >= 4096 ? 2 : 1;
+        }
     }
 
     // workgroup size and workgroups per instance of the first launch: one output
@@ -638,9 +668,19 @@ int build_flat(slos_plan_t p)
     int rc;
     // the normalisation of every output, then the tables
     const uint64_t nscale = p->last_flat() ? p->Nk[p->n] : 0;
-    if ((rc = alloc_dev((void **)&p->d_scale, nscale * sizeof(double) + entries * sizeof(uint32_t), "predecessor tables")))
+    uint64_t nsucc = 0;
+    p->bwd_succ_off.assign(p->n + 2, 0);
+    for (int k = 1; k <= p->bwd_kb; ++k) {
+        p->bwd_succ_off[k] = t.succ_off[k] = nsucc;
+        nsucc += p->Nk[k - 1] * (uint64_t)p->m;
+    }
+    if ((rc = alloc_dev((void **)&p->d_scale, nscale * sizeof(double) + (entries + nsucc) * sizeof(uint32_t),
+                        "predecessor tables")))
         return rc;
     p->d_flat = (uint32_t *)(p->d_scale + nscale);
+    p->d_bwd_succ = p->d_flat + entries;
+    t.kb = p->bwd_kb;
+    t.succ = p->d_bwd_succ;
     t.pred = p->d_flat;
     t.scale = nscale ? p->d_scale : nullptr;
     FlatLaunch l{};
@@ -825,9 +865,12 @@ int slos_plan_ex(int m, int n, const int32_t *input_state, int flags, const slos
             p->ps_pass = false;
             p->low_cap = saved;
         }
+        if (!tiled && n > 0 && !p->host_only) p->choose_flat();
+        if (p->keep && p->flat_kf) p->choose_flat_bwd();
         if (p->keep) {
             p->units.resize(n + 1);
-            for (int k = 1; k <= n; ++k) p->build_units(k);
+            p->unit_chunk.assign(n + 1, 128u);
+            for (int k = p->bwd_kb + 1; k <= n; ++k) p->build_units(k);
         }
         // one wave must be able to hold its low block in LDS
         const size_t es_ = (dt == SLOS_C64) ? 8 : 16;
@@ -851,7 +894,6 @@ int slos_plan_ex(int m, int n, const int32_t *input_state, int flags, const slos
         *out = p;
         return SLOS_OK;
     }
-    if (!tiled && n > 0) p->choose_flat();
 
     int ndev = 0;
     hipError_t e = hipGetDeviceCount(&ndev);
@@ -870,7 +912,7 @@ int slos_plan_ex(int m, int n, const int32_t *input_state, int flags, const slos
         std::vector<uint8_t> modes;
         for (int k = 1; k <= n; ++k) {
             p->desc_off[k] = descs.size();
-            if (k <= p->flat_kf && !(p->keep && k == n)) continue;  // table-driven: no descriptors
+            if (k <= p->flat_kf) continue;  // table-driven: no descriptors
             // narrow unless a leaf has more than 16 groups or a 64-bit delta
             int wide = p->opts.wide_descriptors > 0 ? 1 : 0;
             for (const LeafRec &L : p->leaves[k]) {
@@ -1047,7 +1089,8 @@ int slos_plan_ex(int m, int n, const int32_t *input_state, int flags, const slos
             p->unit_off[k] = allu.size();
             p->bpart_off[k] = bp;
             allu.insert(allu.end(), p->units[k].begin(), p->units[k].end());
-            bp += (uint64_t)p->units[k].size() * (uint64_t)m;
+            // the tail keeps its layers' sums to itself
+            if (k > p->bwd_t) bp += p->bwd_rows(k) * (uint64_t)m;
         }
         p->bpart_off[n + 1] = bp;
         uint64_t gmax = *std::max_element(p->Nk.begin(), p->Nk.end());
@@ -1410,16 +1453,109 @@ int slos_plan_layer_ms(slos_plan_t p, float *ms, int count)
     return SLOS_OK;
 }
 
-// The reverse layers n..1 from g_n (already in d_g[n & 1]) and the assembly of
-// G_U; n >= 1.
-static int run_reverse(slos_plan_t p, int batch, const void *U, void *grad_U, void *stream)
+// Where the reverse pass takes g_n from: dL/da (grad_a), the squared-error loss
+// on targets (a), or d_g[n & 1], filled before.
+struct ReverseSource {
+    const void *grad_a = nullptr;
+    const void *a = nullptr;
+    const int64_t *ranks = nullptr;
+    const double *scales = nullptr;
+    const double *p_target = nullptr;
+    double *loss = nullptr;
+    int64_t count = 0;
+};
+
+// The table-driven reverse layers bwd_kb..1 and G_U; `src` is used where layer
+// n is among them.
+static int run_reverse_flat(slos_plan_t p, int batch, const void *U, void *grad_U, void *stream, const ReverseSource &src)
+{
+    const int n = p->n, m = p->m, t = p->bwd_t;
+    const int c64 = p->c64 ? 1 : 0;
+    const size_t es = p->elem();
+    const uint64_t mm = (uint64_t)m * m;
+    BwdParams route{};
+    FlatBwdLaunch fl{};
+    route.flat = &fl;
+    int e;
+    for (int k = p->bwd_kb; k > t; --k) {
+        FlatBwdParams fp{};
+        const bool seed = k == n && src.grad_a;
+        fp.gk = seed ? src.grad_a : p->d_g[k & 1];
+        fp.gk_stride = (seed ? p->Nk[n] : p->g_stride) * es;
+        fp.scale = seed ? p->d_scale : nullptr;
+        fp.gkm1 = p->d_g[(k - 1) & 1];
+        fp.gkm1_stride = p->g_stride * es;
+        fp.Akm1 = (const char *)p->d_keep + p->keep_off[k - 1] * es;
+        fp.a_stride = p->keep_stride * es;
+        fp.U = U;
+        fp.u_stride = mm * es;
+        fp.succ = p->d_bwd_succ + p->bwd_succ_off[k];
+        fp.partials = (char *)p->d_bpart + p->bpart_off[k] * 16;
+        fp.partials_stride = p->bpart_stride * 16;
+        fp.N = (uint32_t)p->Nk[k - 1];
+        fp.m = m;
+        fp.col = p->photons[k - 1];
+        fl.layer = &fp;
+        fl.per_thread = p->bwd_pt[k];
+        if ((e = slos_launch_bwd_layer(route, c64, 1, stream, batch)))
+            return hip_fail((hipError_t)e, "table-driven reverse layer");
+    }
+    TailParams tp{};
+    const bool whole = t == n;  // the tail forms g_n itself
+    tp.gt = whole && src.grad_a ? src.grad_a : p->d_g[t & 1];
+    tp.gt_stride = (whole && src.grad_a ? p->Nk[n] : p->g_stride) * es;
+    tp.scale = whole && src.grad_a ? p->d_scale : nullptr;
+    if (whole && src.a) {
+        tp.a = src.a;
+        tp.a_stride = p->Nk[n];
+        tp.ranks = src.ranks;
+        tp.target_scale = src.scales;
+        tp.p_target = src.p_target;
+        tp.loss = src.loss;
+        tp.count = src.count;
+    }
+    tp.keep = p->d_keep;
+    tp.keep_stride = p->keep_stride * es;
+    tp.U = U;
+    tp.u_stride = mm * es;
+    tp.GU = grad_U;
+    tp.gu_stride = mm * es;
+    tp.succ = p->d_bwd_succ;
+    tp.partials = p->d_bpart;
+    tp.partials_stride = p->bpart_stride * 16;
+    tp.m = m;
+    tp.n = n;
+    tp.t = t;
+    for (int k = 1; k <= t; ++k) tp.wave_rows += slos_tail_waves((uint32_t)p->Nk[k - 1]);
+    for (int k = 1; k <= n; ++k) {
+        tp.col[k] = (uint8_t)p->photons[k - 1];
+        tp.keep_off[k - 1] = p->keep_off[k - 1] * es;
+        tp.succ_off[k] = k <= t ? p->bwd_succ_off[k] : 0;
+        tp.part_off[k] = p->bpart_off[k];
+        tp.rows[k] = k > t ? (uint32_t)p->bwd_rows(k) : 0;
+    }
+    tp.cap[0] = tp.cap[1] = 1;
+    for (int k = 0; k <= t; ++k) {
+        tp.N[k] = (uint32_t)p->Nk[k];
+        tp.cap[k & 1] = std::max(tp.cap[k & 1], tp.N[k]);
+    }
+    fl.layer = nullptr;
+    fl.tail = &tp;
+    if ((e = slos_launch_bwd_layer(route, c64, 1, stream, batch))) return hip_fail((hipError_t)e, "reverse tail");
+    return SLOS_OK;
+}
+
+// The reverse layers n..1 and the assembly of G_U; n >= 1.  g_n is in d_g[n & 1]
+// unless layer n is table-driven, which takes it from `src`.
+static int run_reverse(slos_plan_t p, int batch, const void *U, void *grad_U, void *stream,
+                       const ReverseSource &src = ReverseSource{})
 {
     const int n = p->n, m = p->m;
     const int c64 = p->c64 ? 1 : 0;
     const size_t es = p->elem();
     const uint64_t mm = (uint64_t)m * m;
     int e;
-    for (int k = n; k >= 1; --k) {
+    for (int k = n; k > p->bwd_kb; --k) {
         BwdParams bp{};
         bp.gk = p->d_g[k & 1];
         bp.gkm1 = p->d_g[(k - 1) & 1];
@@ -1448,6 +1584,7 @@ static int run_reverse(slos_plan_t p, int batch, const void *U, void *grad_U, vo
                 return hip_fail((hipError_t)e, "reverse layer");
         }
     }
+    if (p->bwd_kb) return run_reverse_flat(p, batch, U, grad_U, stream, src);
     // every layer's column sums and G_U in one launch
     ColsumLayers cl{};
     for (int k = 1; k <= n; ++k) {
@@ -1486,6 +1623,11 @@ static int run_backward(slos_plan_t p, int batch, const void *U, const void *gra
     if (!grad_a) return fail(SLOS_ERR_INVALID_ARG, "grad_a must be a device pointer");
     const int n = p->n;
     if (n == 0) return zero_grad_u(p, batch, grad_U, stream);
+    if (p->last_flat() && p->bwd_kb == n) {
+        ReverseSource src;
+        src.grad_a = grad_a;
+        return run_reverse(p, batch, U, grad_U, stream, src);
+    }
     const size_t rec = p->desc_wide[n] ? sizeof(LeafDescWide) : sizeof(LeafDescNarrow);
     // g_n = c_S g_a
     int e;
@@ -1568,6 +1710,16 @@ int slos_sq_loss_backward_many(slos_plan_t p, int batch, const void *U, const vo
         return fail(SLOS_ERR_INVALID_ARG, "a (and ranks, scales, p_target when count > 0) must be device pointers");
     const int n = p->n;
     if (n == 0) return fail(SLOS_ERR_INVALID_ARG, "n = 0: the vacuum has no adjoint layers");
+    if (p->bwd_t == n) {
+        ReverseSource src;
+        src.a = a;
+        src.ranks = ranks;
+        src.scales = scales;
+        src.p_target = p_target;
+        src.loss = loss;
+        src.count = count;
+        return run_reverse(p, batch, U, grad_U, stream, src);
+    }
     int e = slos_launch_sq_loss_seed(a, p->Nk[n], ranks, scales, count, p_target, p->d_g[n & 1], p->g_stride, loss,
                                      batch, p->c64 ? 1 : 0, stream);
     if (e) return hip_fail((hipError_t)e, "squared-loss seed kernel");

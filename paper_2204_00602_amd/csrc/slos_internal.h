@@ -205,7 +205,10 @@ struct BwdUnit {
 };
 static_assert(sizeof(BwdUnit) == 40, "BwdUnit must stay 40 bytes");
 
+struct FlatBwdLaunch;  // flat.h
+
 struct BwdParams {
+    const FlatBwdLaunch *flat;  // host only: a launch of the table-driven reverse layers instead (the rest is unused)
     const void *gk;          // g_k (layer k), plan dtype
     void *gkm1;              // g_{k-1}
     const void *Akm1;        // kept A_{k-1}
