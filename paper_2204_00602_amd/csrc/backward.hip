@@ -300,36 +300,20 @@ __device__ __forceinline__ Cd cmul(Cd a, Cd b) { return Cd{a.x * b.x - a.y * b.y
 __device__ __forceinline__ Cd cadd(Cd a, Cd b) { return Cd{a.x + b.x, a.y + b.y}; }
 __device__ __forceinline__ Cd cconj(Cd a) { return Cd{a.x, -a.y}; }
 
-// 2x2 MZI block B and its derivatives dB/da, dB/db, from e^{ia} and e^{ib}
-__device__ void mzi_block_e(Cd ea, Cd eb, Cd B[4], Cd dA[4], Cd dBb[4])
+// MZI block B = diag(1, e^{ib}) M, M = BS PS_0(a) BS = 1/2 [[e^{ia} - 1, i (e^{ia} + 1)],
+// [i (e^{ia} + 1), 1 - e^{ia}]], row-major in v[0..3], with e^{ib} in v[4].
+struct MziBlock {
+    Cd v[5];
+};
+__device__ __forceinline__ MziBlock mzi_block(Cd ea, Cd eb)
 {
-    const double r = 0.70710678118654752440;  // cos(pi/4) = sin(pi/4)
-    // BS * BS-like products written out: BS = r [[1, i], [i, 1]]
-    // M = BS PS0(a) BS = r^2 [[e^{ia} - 1, i(e^{ia} + 1)], [i(e^{ia} + 1), -e^{ia} + 1]]
-    const double h = r * r;
-    const Cd m00{h * (ea.x - 1.0), h * ea.y};
-    const Cd m01{-h * ea.y, h * (ea.x + 1.0)};   // i h (e^{ia} + 1)
-    const Cd m10 = m01;
-    const Cd m11{h * (1.0 - ea.x), -h * ea.y};
-    // B = diag(1, e^{ib}) M
-    B[0] = m00;
-    B[1] = m01;
-    B[2] = cmul(eb, m10);
-    B[3] = cmul(eb, m11);
-    // dM/da: d e^{ia} = i e^{ia}
-    const Cd iea{-ea.y, ea.x};
-    const Cd d00{h * iea.x, h * iea.y};
-    const Cd d01{-h * iea.y, h * iea.x};          // i h (i e^{ia})
-    const Cd d11{-h * iea.x, -h * iea.y};
-    dA[0] = d00;
-    dA[1] = d01;
-    dA[2] = cmul(eb, d01);
-    dA[3] = cmul(eb, d11);
-    const Cd ieb{-eb.y, eb.x};
-    dBb[0] = Cd{0.0, 0.0};
-    dBb[1] = Cd{0.0, 0.0};
-    dBb[2] = cmul(ieb, m10);
-    dBb[3] = cmul(ieb, m11);
+    MziBlock b;
+    b.v[0] = Cd{0.5 * (ea.x - 1.0), 0.5 * ea.y};
+    b.v[1] = Cd{-0.5 * ea.y, 0.5 * (ea.x + 1.0)};
+    b.v[2] = cmul(eb, b.v[1]);
+    b.v[3] = cmul(eb, Cd{0.5 * (1.0 - ea.x), -0.5 * ea.y});
+    b.v[4] = eb;
+    return b;
 }
 
 __device__ __forceinline__ Cd cexp_i(double a)
@@ -339,156 +323,203 @@ __device__ __forceinline__ Cd cexp_i(double a)
     return Cd{c, s};
 }
 
-// The phase factors e^{i phi} of one phase set: staged in LDS by all lanes at
-// once when E is given (the sweeps then need no sincos on their critical path),
-// else computed where they are used.
-struct PhaseFactors {
+// The MZI blocks of one phase set, prepared by all threads before the sweep as
+// far as LDS reaches: whole blocks, else the phase factors e^{i phi}, else
+// nothing (sincos on the sweep's chain).
+enum MeshStage { kMeshNone = 0, kMeshFactors = 1, kMeshBlocks = 2 };
+struct MeshBlocks {
     const double *ph;
-    Cd *E;  // 2 * nmzi entries, or nullptr
-    __device__ void stage(int nmzi, int lane, int nlanes)
+    Cd *lds;
+    int stage;
+    __device__ void prepare(int nmzi, int tid, int nt)
     {
-        if (!E) return;
-        for (int i = lane; i < 2 * nmzi; i += nlanes) E[i] = cexp_i(ph[i]);
-        __syncthreads();
+        if (stage == kMeshBlocks) {
+            for (int k = tid; k < nmzi; k += nt)
+                ((MziBlock *)lds)[k] = mzi_block(cexp_i(ph[2 * k]), cexp_i(ph[2 * k + 1]));
+        } else if (stage == kMeshFactors) {
+            for (int i = tid; i < 2 * nmzi; i += nt) lds[i] = cexp_i(ph[i]);
+        }
     }
-    __device__ void block(int k, Cd B[4], Cd dA[4], Cd dB[4]) const
+    __device__ __forceinline__ MziBlock block(int k) const
     {
-        if (E) mzi_block_e(E[2 * k], E[2 * k + 1], B, dA, dB);
-        else mzi_block_e(cexp_i(ph[2 * k]), cexp_i(ph[2 * k + 1]), B, dA, dB);
+        if (stage == kMeshBlocks) return ((const MziBlock *)lds)[k];
+        if (stage == kMeshFactors) return mzi_block(lds[2 * k], lds[2 * k + 1]);
+        return mzi_block(cexp_i(ph[2 * k]), cexp_i(ph[2 * k + 1]));
     }
 };
 
-// One wave per phase set (m <= 64).  The MZIs of one mesh column act on
-// disjoint row pairs, so a whole column is applied (and differentiated) in one
-// step: lane l serves the column's MZI i = l / gc on matrix columns
+// One workgroup per phase set (m <= 64).  Matrix columns are independent, so
+// each wave takes cw of them through the whole mesh by itself, in its own part
+// of LDS: no barrier inside the sweep.  The MZIs of one mesh column act on
+// disjoint row pairs, so the wave applies (and differentiates) a whole mesh
+// column per step: lane l serves MZI i = l / gc on its wave's matrix columns
 // l % gc, l % gc + gc, .., with gc = 64 / (most MZIs in a column) rounded down
-// to a power of two (8 at m = 12), and a barrier separates the m column steps.
-__device__ __forceinline__ int mesh_lanes_per_mzi(int m)
+// to a power of two (8 at m = 12).
+struct MeshLanes {
+    int gc, waves, cw;
+};
+__host__ __device__ inline MeshLanes mesh_lanes(int m, int max_waves)
 {
     const int most = m / 2 > 0 ? m / 2 : 1;
-    int gc = 1;
-    while (gc * 2 * most <= 64) gc *= 2;
-    return gc;
+    MeshLanes l{1, 1, m};
+    while (l.gc * 2 * most <= 64) l.gc *= 2;
+    l.waves = (m + l.gc - 1) / l.gc;
+    if (l.waves > max_waves) l.waves = max_waves;
+    l.cw = (m + l.waves - 1) / l.waves;
+    return l;
+}
+
+// Every lane's LDS accesses of a step are done before the next step's: a wave
+// runs its LDS instructions in order, the fence keeps the compiler to it.
+__device__ __forceinline__ void wave_step()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// X <- T X, one mesh column
+__device__ __forceinline__ void mesh_apply(Cd *X, const MziBlock &B, int p0, int cw, int nc, int g, int gc)
+{
+    for (int c = g; c < nc; c += gc) {
+        const Cd x0 = X[p0 * cw + c], x1 = X[(p0 + 1) * cw + c];
+        X[p0 * cw + c] = cadd(cmul(B.v[0], x0), cmul(B.v[1], x1));
+        X[(p0 + 1) * cw + c] = cadd(cmul(B.v[2], x0), cmul(B.v[3], x1));
+    }
+}
+
+// The whole mesh on this wave's columns of X; each step's block is read while
+// the one before still computes.
+__device__ __forceinline__ void mesh_forward_sweep(Cd *X, const MeshBlocks &mb, int m, int nmzi, int i, int cw, int nc,
+                                                   int g, int gc)
+{
+    int k0 = 0;
+    MziBlock B = mb.block(min(i, nmzi - 1));
+    for (int col = 0; col < m; ++col) {
+        const int cnt = (m - col % 2) / 2;
+        const MziBlock nb = mb.block(min(k0 + cnt + i, nmzi - 1));
+        if (i < cnt) mesh_apply(X, B, col % 2 + 2 * i, cw, nc, g, gc);
+        k0 += cnt;
+        B = nb;
+        wave_step();
+    }
 }
 
 template <typename T>
-__global__ __launch_bounds__(64) void mesh_forward_kernel(int m, int nmzi, const double *__restrict__ phases,
-                                                          typename Cb<T>::type *__restrict__ Uout, int stage)
+__global__ __launch_bounds__(1024) void mesh_forward_kernel(int m, int nmzi, const double *__restrict__ phases,
+                                                            typename Cb<T>::type *__restrict__ Uout, int stage,
+                                                            MeshLanes ml)
 {
     using C = typename Cb<T>::type;
-    extern __shared__ Cd Ush[];  // m x m, then 2 nmzi phase factors when staged
-    const int b = blockIdx.x;
-    PhaseFactors pf{phases + (size_t)b * 2 * nmzi, stage ? Ush + m * m : nullptr};
-    pf.stage(nmzi, threadIdx.x, blockDim.x);
-    const int lane = threadIdx.x, gc = mesh_lanes_per_mzi(m), i = lane / gc, g = lane % gc;
-    for (int e = lane; e < m * m; e += 64) Ush[e] = Cd{e / m == e % m ? 1.0 : 0.0, 0.0};
+    extern __shared__ Cd Ush[];  // per wave m x cw, then the prepared blocks
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    MeshBlocks mb{phases + (size_t)b * 2 * nmzi, Ush + ml.waves * m * ml.cw, stage};
+    mb.prepare(nmzi, tid, blockDim.x);
+    const int gc = ml.gc, cw = ml.cw, i = lane / gc, g = lane % gc;
+    const int c0 = wv * cw, nc = min(cw, m - c0);  // this wave's matrix columns (none if nc <= 0)
+    Cd *X = Ush + wv * m * cw;
+    for (int e = lane; e < m * cw; e += 64) X[e] = Cd{e / cw == c0 + e % cw ? 1.0 : 0.0, 0.0};
     __syncthreads();
-    int k0 = 0;
-    for (int col = 0; col < m; ++col) {
-        const int cnt = (m - col % 2) / 2;
-        if (i < cnt) {
-            const int p0 = col % 2 + 2 * i;
-            Cd B[4], dA[4], dB[4];
-            pf.block(k0 + i, B, dA, dB);
-            for (int c = g; c < m; c += gc) {
-                const Cd x0 = Ush[p0 * m + c], x1 = Ush[(p0 + 1) * m + c];
-                Ush[p0 * m + c] = cadd(cmul(B[0], x0), cmul(B[1], x1));
-                Ush[(p0 + 1) * m + c] = cadd(cmul(B[2], x0), cmul(B[3], x1));
-            }
-        }
-        k0 += cnt;
-        __syncthreads();
-    }
-    for (int e = lane; e < m * m; e += 64) {
-        const Cd v = Ush[e];
-        Uout[(size_t)b * m * m + e] = C{(T)v.x, (T)v.y};
+    mesh_forward_sweep(X, mb, m, nmzi, i, cw, nc, g, gc);
+    for (int e = lane; e < m * cw; e += 64) {
+        const int r = e / cw, c = e % cw;
+        if (c < nc) Uout[((size_t)b * m + r) * m + c0 + c] = C{(T)X[e].x, (T)X[e].y};
     }
 }
 
 // Reverse sweep: with U = L_k T_k R_k, P = L_k^H G_U and Q = L_k^H U = T_k R_k,
 //   dL/dphi = Re sum conj(P) o (dT_k T_k^H Q),
 // then P <- T_k^H P and Q <- T_k^H Q move to the previous column (the MZIs of a
-// column commute, so they share P and Q).  Each MZI's sum over matrix columns
-// is per lane, then a reduction over its gc lanes in a fixed order.
+// column commute, so they share P and Q).  On the MZI's rows, with BS unitary,
+//   dT/da T^H = 1/2 [[i, e^{-ib}], [-e^{ib}, i]],   dT/db T^H = diag(0, i),
+// so a matrix column (p0, p1), (q0, q1) contributes
+//   a: 1/2 [-Im(p0* q0 + p1* q1) + Re(e^{-ib} p0* q1 - e^{ib} p1* q0)],  b: -Im(p1* q1).
+// Each MZI's sum is over its gc lanes, then over the waves, in a fixed order:
+// after the sweep, from one term per lane in LDS where they fit (lane_sums), so
+// that no cross-lane move is on the sweep's chain.
+// m=12, 64 phase sets: bound by the chain of 2 m steps of LDS reads, complex
+// products and LDS writes; with one wave on all matrix columns, a barrier per
+// step, and the 2x2 derivative products formed in full it took 20 us.
 template <typename T>
-__global__ __launch_bounds__(64) void mesh_backward_kernel(int m, int nmzi, const double *__restrict__ phases,
-                                                           const typename Cb<T>::type *__restrict__ GU,
-                                                           double *__restrict__ gphases, int stage)
+__global__ __launch_bounds__(1024) void mesh_backward_kernel(int m, int nmzi, const double *__restrict__ phases,
+                                                             const typename Cb<T>::type *__restrict__ GU,
+                                                             double *__restrict__ gphases, int stage, MeshLanes ml, int lane_sums)
 {
-    extern __shared__ Cd sh[];  // P (m x m), Q (m x m), then 2 nmzi phase factors when staged
-    Cd *P = sh;
-    Cd *Q = sh + m * m;
-    const int b = blockIdx.x;
-    PhaseFactors pf{phases + (size_t)b * 2 * nmzi, stage ? sh + 2 * m * m : nullptr};
-    pf.stage(nmzi, threadIdx.x, blockDim.x);
-    const int lane = threadIdx.x, gc = mesh_lanes_per_mzi(m), i = lane / gc, g = lane % gc;
+    extern __shared__ Cd sh[];  // per wave P and Q (m x cw each), the prepared blocks, the waves' sums
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int gc = ml.gc, cw = ml.cw, W = ml.waves, i = lane / gc, g = lane % gc;
+    Cd *blocks = sh + 2 * W * m * cw;
+    MeshBlocks mb{phases + (size_t)b * 2 * nmzi, blocks, stage};
+    double *part = (double *)(blocks + (stage == kMeshBlocks ? 5 * nmzi : stage == kMeshFactors ? 2 * nmzi : 0));
+    mb.prepare(nmzi, tid, blockDim.x);
+    const int c0 = wv * cw, nc = min(cw, m - c0);
+    Cd *P = sh + wv * 2 * m * cw, *Q = P + m * cw;
     // Q = U (rebuilt here), P = G_U
-    for (int e = lane; e < m * m; e += 64) {
-        Q[e] = Cd{e / m == e % m ? 1.0 : 0.0, 0.0};
-        const auto v = GU[(size_t)b * m * m + e];
-        P[e] = Cd{(double)v.x, (double)v.y};
+    for (int e = lane; e < m * cw; e += 64) {
+        const int r = e / cw, c = e % cw;
+        Q[e] = Cd{r == c0 + c ? 1.0 : 0.0, 0.0};
+        Cd v{0.0, 0.0};
+        if (c < nc) {
+            const auto u = GU[((size_t)b * m + r) * m + c0 + c];
+            v = Cd{(double)u.x, (double)u.y};
+        }
+        P[e] = v;
     }
     __syncthreads();
-    int k0 = 0;
-    for (int col = 0; col < m; ++col) {
-        const int cnt = (m - col % 2) / 2;
-        if (i < cnt) {
-            const int p0 = col % 2 + 2 * i;
-            Cd B[4], dA[4], dB[4];
-            pf.block(k0 + i, B, dA, dB);
-            for (int c = g; c < m; c += gc) {
-                const Cd x0 = Q[p0 * m + c], x1 = Q[(p0 + 1) * m + c];
-                Q[p0 * m + c] = cadd(cmul(B[0], x0), cmul(B[1], x1));
-                Q[(p0 + 1) * m + c] = cadd(cmul(B[2], x0), cmul(B[3], x1));
-            }
-        }
-        k0 += cnt;
-        __syncthreads();
-    }
+    mesh_forward_sweep(Q, mb, m, nmzi, i, cw, nc, g, gc);
+    int k0 = nmzi;
+    MziBlock B = mb.block(min(nmzi - (m - (m - 1) % 2) / 2 + i, nmzi - 1));
+    double *out = gphases + (size_t)b * 2 * nmzi;
     // columns in reverse
     for (int col = m - 1; col >= 0; --col) {
         const int cnt = (m - col % 2) / 2;
         k0 -= cnt;
         double va = 0.0, vb = 0.0;
+        const MziBlock nb = mb.block(max(k0 - (m - (col + 1) % 2) / 2 + i, 0) % nmzi);
         if (i < cnt) {
             const int p0 = col % 2 + 2 * i;
-            Cd B[4], dA[4], dB[4];
-            pf.block(k0 + i, B, dA, dB);
-            // D = dT T^H restricted to rows p0, p0+1 (2x2): D = dB B^H
-            Cd Da[4], Db[4];
-            for (int r = 0; r < 2; ++r)
-                for (int s2 = 0; s2 < 2; ++s2) {
-                    Da[2 * r + s2] =
-                        cadd(cmul(dA[2 * r], cconj(B[2 * s2])), cmul(dA[2 * r + 1], cconj(B[2 * s2 + 1])));
-                    Db[2 * r + s2] =
-                        cadd(cmul(dB[2 * r], cconj(B[2 * s2])), cmul(dB[2 * r + 1], cconj(B[2 * s2 + 1])));
-                }
-            for (int c = g; c < m; c += gc) {
-                const Cd q0 = Q[p0 * m + c], q1 = Q[(p0 + 1) * m + c];
-                const Cd pp0 = P[p0 * m + c], pp1 = P[(p0 + 1) * m + c];
-                const Cd ya0 = cadd(cmul(Da[0], q0), cmul(Da[1], q1));
-                const Cd ya1 = cadd(cmul(Da[2], q0), cmul(Da[3], q1));
-                const Cd yb0 = cadd(cmul(Db[0], q0), cmul(Db[1], q1));
-                const Cd yb1 = cadd(cmul(Db[2], q0), cmul(Db[3], q1));
-                va += pp0.x * ya0.x + pp0.y * ya0.y + pp1.x * ya1.x + pp1.y * ya1.y;
-                vb += pp0.x * yb0.x + pp0.y * yb0.y + pp1.x * yb1.x + pp1.y * yb1.y;
+            const Cd eb = B.v[4], h0 = cconj(B.v[0]), h1 = cconj(B.v[1]), h2 = cconj(B.v[2]), h3 = cconj(B.v[3]);
+            for (int c = g; c < nc; c += gc) {
+                const Cd q0 = Q[p0 * cw + c], q1 = Q[(p0 + 1) * cw + c];
+                const Cd x0 = P[p0 * cw + c], x1 = P[(p0 + 1) * cw + c];
+                const double i0 = x0.x * q0.y - x0.y * q0.x, i1 = x1.x * q1.y - x1.y * q1.x;
+                const double re = (x0.x * q1.x + x0.y * q1.y) - (x1.x * q0.x + x1.y * q0.y);
+                const double im = (x0.x * q1.y - x0.y * q1.x) + (x1.x * q0.y - x1.y * q0.x);
+                va += 0.5 * ((eb.x * re + eb.y * im) - (i0 + i1));
+                vb -= i1;
                 // P <- T^H P, Q <- T^H Q on rows p0, p0+1
-                Q[p0 * m + c] = cadd(cmul(cconj(B[0]), q0), cmul(cconj(B[2]), q1));
-                Q[(p0 + 1) * m + c] = cadd(cmul(cconj(B[1]), q0), cmul(cconj(B[3]), q1));
-                P[p0 * m + c] = cadd(cmul(cconj(B[0]), pp0), cmul(cconj(B[2]), pp1));
-                P[(p0 + 1) * m + c] = cadd(cmul(cconj(B[1]), pp0), cmul(cconj(B[3]), pp1));
+                Q[p0 * cw + c] = cadd(cmul(h0, q0), cmul(h2, q1));
+                Q[(p0 + 1) * cw + c] = cadd(cmul(h1, q0), cmul(h3, q1));
+                P[p0 * cw + c] = cadd(cmul(h0, x0), cmul(h2, x1));
+                P[(p0 + 1) * cw + c] = cadd(cmul(h1, x0), cmul(h3, x1));
             }
         }
-        // sum over the gc lanes of each MZI (aligned groups of a power of two)
-        for (int o = gc / 2; o > 0; o >>= 1) {
-            va += __shfl_xor(va, o, 64);
-            vb += __shfl_xor(vb, o, 64);
+        if (lane_sums) {
+            // one term per lane, added after the sweep
+            if (i < cnt) ((double2 *)part)[(size_t)(wv * gc + g) * nmzi + k0 + i] = double2{va, vb};
+        } else {
+            // sum over the gc lanes of each MZI (aligned groups of a power of two)
+            for (int o = gc / 2; o > 0; o >>= 1) {
+                va += __shfl_xor(va, o, 64);
+                vb += __shfl_xor(vb, o, 64);
+            }
+            if (i < cnt && g == 0) {
+                double *to = W > 1 ? part + (size_t)wv * 2 * nmzi : out;
+                to[2 * (k0 + i)] = va;
+                to[2 * (k0 + i) + 1] = vb;
+            }
         }
-        if (i < cnt && g == 0) {
-            gphases[(size_t)b * 2 * nmzi + 2 * (k0 + i)] = va;
-            gphases[(size_t)b * 2 * nmzi + 2 * (k0 + i) + 1] = vb;
-        }
+        B = nb;
+        wave_step();
+    }
+    const int rows = lane_sums ? W * gc : W;
+    if (rows > 1) {
         __syncthreads();
+        for (int e = tid; e < 2 * nmzi; e += blockDim.x) {
+            double s = part[e];
+            for (int w = 1; w < rows; ++w) s += part[(size_t)w * 2 * nmzi + e];
+            out[e] = s;
+        }
     }
 }
 
@@ -573,21 +604,57 @@ int slos_launch_sq_loss(const void *a, uint64_t M, const int64_t *ranks, int64_t
     return (int)hipGetLastError();
 }
 
+// What the mesh kernels keep in LDS: the waves' matrices (mats of m x cw), the
+// blocks or factors prepared ahead, and the waves' sums; fewer waves, then less
+// prepared, where that does not fit.
+struct MeshShape {
+    MeshLanes ml;
+    int stage;
+    int lane_sums;
+    size_t lds;
+};
+static MeshShape mesh_shape(int m, int nmzi, int mats, bool sums)
+{
+    MeshShape s{};
+    if (sums) {
+        // the mesh adjoint with a term per lane, all blocks prepared
+        s.ml = mesh_lanes(m, 16);
+        if (s.ml.gc > s.ml.cw) s.ml.gc = s.ml.cw;  // idle lanes add nothing: no terms for them
+        s.stage = kMeshBlocks;
+        s.lane_sums = s.ml.waves * s.ml.gc > 1;
+        s.lds = ((size_t)mats * s.ml.waves * m * s.ml.cw + 5 * (size_t)nmzi) * sizeof(Cd) +
+                (size_t)s.ml.waves * s.ml.gc * nmzi * 2 * sizeof(double);
+        if (s.lane_sums && s.lds <= SLOS_LDS_DYNAMIC_MAX) return s;
+        s.lane_sums = 0;
+    }
+    for (int waves = 16; waves >= 1; waves /= 2) {
+        s.ml = mesh_lanes(m, waves);
+        const size_t mat = (size_t)mats * s.ml.waves * m * s.ml.cw * sizeof(Cd);
+        const size_t part = sums && s.ml.waves > 1 ? (size_t)s.ml.waves * 2 * nmzi * sizeof(double) : 0;
+        for (s.stage = kMeshBlocks; s.stage >= kMeshNone; --s.stage) {
+            const int per = s.stage == kMeshBlocks ? 5 : s.stage == kMeshFactors ? 2 : 0;
+            s.lds = mat + part + (size_t)per * nmzi * sizeof(Cd);
+            // sincos on the chain only where one wave's matrices leave no room
+            if (s.lds <= SLOS_LDS_DYNAMIC_MAX && (s.stage > kMeshNone || waves == 1)) return s;
+        }
+    }
+    s.stage = kMeshNone;
+    return s;
+}
+
 int slos_launch_mesh_forward(int m, int batch, const double *phases, void *U, int c64, void *stream)
 {
     const int nmzi = m * (m - 1) / 2;
-    const size_t mat = (size_t)m * m * sizeof(Cd), fac = 2 * (size_t)nmzi * sizeof(Cd);
-    const int stage = mat + fac <= SLOS_LDS_DYNAMIC_MAX;  // phase factors in LDS when they fit
-    const size_t lds = mat + (stage ? fac : 0);
+    const MeshShape sh = mesh_shape(m, nmzi, 1, false);
     static bool a32 = false, a64 = false;
     hipError_t e = c64 ? allow_lds(mesh_forward_kernel<float>, a32) : allow_lds(mesh_forward_kernel<double>, a64);
     if (e != hipSuccess) return (int)e;
     if (c64)
-        hipLaunchKernelGGL(mesh_forward_kernel<float>, dim3(batch), dim3(64), lds, (hipStream_t)stream, m, nmzi,
-                           phases, (float2 *)U, stage);
+        hipLaunchKernelGGL(mesh_forward_kernel<float>, dim3(batch), dim3(64 * sh.ml.waves), sh.lds, (hipStream_t)stream, m,
+                           nmzi, phases, (float2 *)U, sh.stage, sh.ml);
     else
-        hipLaunchKernelGGL(mesh_forward_kernel<double>, dim3(batch), dim3(64), lds, (hipStream_t)stream, m, nmzi,
-                           phases, (double2 *)U, stage);
+        hipLaunchKernelGGL(mesh_forward_kernel<double>, dim3(batch), dim3(64 * sh.ml.waves), sh.lds, (hipStream_t)stream,
+                           m, nmzi, phases, (double2 *)U, sh.stage, sh.ml);
     return (int)hipGetLastError();
 }
 
@@ -595,17 +662,15 @@ int slos_launch_mesh_backward(int m, int batch, const double *phases, const void
                               void *stream)
 {
     const int nmzi = m * (m - 1) / 2;
-    const size_t mat = 2 * (size_t)m * m * sizeof(Cd), fac = 2 * (size_t)nmzi * sizeof(Cd);
-    const int stage = mat + fac <= SLOS_LDS_DYNAMIC_MAX;
-    const size_t lds = mat + (stage ? fac : 0);
+    const MeshShape sh = mesh_shape(m, nmzi, 2, true);
     static bool a32 = false, a64 = false;
     hipError_t e = c64 ? allow_lds(mesh_backward_kernel<float>, a32) : allow_lds(mesh_backward_kernel<double>, a64);
     if (e != hipSuccess) return (int)e;
     if (c64)
-        hipLaunchKernelGGL(mesh_backward_kernel<float>, dim3(batch), dim3(64), lds, (hipStream_t)stream, m, nmzi,
-                           phases, (const float2 *)GU, gphases, stage);
+        hipLaunchKernelGGL(mesh_backward_kernel<float>, dim3(batch), dim3(64 * sh.ml.waves), sh.lds, (hipStream_t)stream,
+                           m, nmzi, phases, (const float2 *)GU, gphases, sh.stage, sh.ml, sh.lane_sums);
     else
-        hipLaunchKernelGGL(mesh_backward_kernel<double>, dim3(batch), dim3(64), lds, (hipStream_t)stream, m, nmzi,
-                           phases, (const double2 *)GU, gphases, stage);
+        hipLaunchKernelGGL(mesh_backward_kernel<double>, dim3(batch), dim3(64 * sh.ml.waves), sh.lds, (hipStream_t)stream,
+                           m, nmzi, phases, (const double2 *)GU, gphases, sh.stage, sh.ml, sh.lane_sums);
     return (int)hipGetLastError();
 }
