@@ -393,12 +393,16 @@ typedef struct slos_batch_s *slos_batch_t;
  * int32 in total), with at most 16 photons.  flags: SLOS_C64 or SLOS_C128.
  * opts: leaf_max (default 1024), block_threads (64 to 1024; the larger give
  * the big instances more waves), grid_blocks (workgroups, default 1024),
- * outputs_per_lane (default 2); other fields are ignored.
- * The whole batch runs in one kernel launch.  An instance whose last layer has
- * at least four tiles per wave runs on a whole workgroup (its waves share each
- * layer, a barrier between layers); every other instance runs on a single
- * wave.  The host assigns both kinds largest-first to the least loaded
- * workgroup or wave, so no workgroup waits on another.
+ * outputs_per_lane (default 2), low_block_max; other fields are ignored.
+ * The whole batch runs in one kernel launch.  With these options at 0 it runs
+ * from tables of each mode count's predecessors, built on the device at plan
+ * time (4 bytes per state and entry, 12 MB for all of m 6..14, n <= 7); an
+ * option set, an instance of more than 3,200,000 outputs or tables beyond 512
+ * MiB select the tiled kernel.  In both, the large instances run on whole
+ * workgroups (a barrier between layers) and the others on single waves, dealt
+ * out largest-first to the least loaded workgroup or wave, so no workgroup
+ * waits on another; from tables, the last layer of an instance that would end
+ * last is divided among workgroups.
  */
 int slos_batch_plan(int count, const int32_t *ms, const int32_t *inputs, int flags, const slos_options_t *opts,
                     slos_batch_t *out);

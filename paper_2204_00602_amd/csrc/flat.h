@@ -87,7 +87,9 @@ struct FlatTables {
     uint64_t off[SLOS_MAX_PHOTONS + 1];
     uint32_t N[SLOS_MAX_PHOTONS + 1];
     uint32_t leaf_cap[SLOS_MAX_PHOTONS + 1];  // the tiled kernel's leaf size of each layer
-    double *scale;               // of layer kf, or NULL
+    double *scale;               // normalisation of the states of the layers in scale_on (bit k), at scale_off[k]
+    uint64_t scale_off[SLOS_MAX_PHOTONS + 1];
+    uint64_t scale_on;
     double norm_t;
     uint32_t *succ;              // mode-major: succ[succ_off[k] + j * N[k - 1] + y] = rank of y + e_j
     int kb;                      // layers with a successor table: 1..kb
@@ -104,6 +106,65 @@ struct FlatLaunch {
     int threads;                 // head: workgroup size
 };
 int slos_launch_flat(const FlatLaunch &l, void *stream);
+
+// ---- batches of table-driven instances (flat_batch.hip) --------------------------
+
+#define SLOS_FB_THREADS 1024
+#define SLOS_FB_GRID 256          // workgroups: one per CU
+#define SLOS_FB_WAVES (SLOS_FB_THREADS / 64)
+#define SLOS_FB_MAX_ENTRIES (uint64_t(1) << 27)  // 512 MiB of tables
+#define SLOS_FB_MAX_PARTS 16
+// Cycles of a compute unit that the host deals instances out by, per state and
+// entry of its table unless said otherwise, c64 / c128.  Fitted to 256 equal
+// instances of 12 types from (8, 6) to (14, 7) on workgroups, and to 4096 of
+// (6, 3) .. (10, 4) on waves.
+#define SLOS_FB_WG_CYCLES(c64) ((c64) ? 0.234 : 0.4)      // workgroup, layer read from LDS
+#define SLOS_FB_BLOCK_CYCLES(c64) ((c64) ? 0.5 : 0.9)     // workgroup, layer staged in blocks
+#define SLOS_FB_LAYER_CYCLES(c64) ((c64) ? 2850.0 : 4500.0)  // workgroup, per layer
+#define SLOS_FB_WAVE_CYCLES(c64) ((c64) ? 4.66 : 8.0)     // wave among sixteen busy ones
+#define SLOS_FB_WAVE_LAYER_CYCLES(c64) ((c64) ? 1700.0 : 2500.0)
+
+// The tables of one mode count.
+struct FlatModes {
+    uint64_t off[SLOS_BATCH_MAX_N + 1];        // layer k's predecessor table, in entries
+    uint64_t scale_off[SLOS_BATCH_MAX_N + 1];  // sqrt(prod s_j!) of its states, where some instance ends there
+    uint32_t N[SLOS_BATCH_MAX_N + 1];
+    uint32_t m;
+};
+struct FlatInst {
+    uint64_t U_off, out_off;      // elements
+    double norm_t;                // 1 / sqrt(prod t_i!)
+    uint32_t modes;               // index of its FlatModes
+    uint32_t n;
+    uint8_t col[SLOS_BATCH_MAX_N];
+};
+// What a workgroup runs: an instance, or part `part` of `parts` of its last
+// layer (with the layers below); the parts' sums of P go to partials[slot ..].
+struct FlatItem {
+    uint32_t inst, part, parts, slot, count;
+};
+struct FlatBatchParams {
+    const void *U;
+    void *out;
+    double *sum_p;                // per instance, or NULL
+    const FlatInst *inst;
+    const FlatModes *modes;
+    const uint32_t *pred;
+    const double *scale;
+    const FlatItem *items;
+    double *partials;
+    uint32_t *counts;                     // zero between launches
+    const uint32_t *wg_start, *wg_list;   // items that a workgroup runs with all its waves, first
+    const uint32_t *wv_start, *wv_list;   // then each wave its own
+    void *scratch;                // per workgroup two layers of scratch_stride elements, for layers beyond the LDS
+    const uint32_t *wg_scr;       // per workgroup: its place in the scratch
+    uint64_t scratch_stride;
+    const uint64_t *binom;        // binom[a * bstride + b] = C(a, b)
+    int bstride;
+    uint32_t lds_elems;           // elements of LDS for the layers and U's columns
+    uint32_t wave_elems;          // the same of one wave
+};
+int slos_launch_flat_batch(const FlatBatchParams &p, int c64, int grid, void *stream);
 
 // ---- adjoint of the table-driven layers (flat_bwd.hip) -------------------------
 

@@ -17,123 +17,9 @@
 // padded with entries that stand for a zero coefficient and a zero state.
 #include <algorithm>
 
-#include "accum.h"
-#include "flat.h"
+#include "flat_dev.h"
 
 namespace {
-
-constexpr int kChunk = 8;  // table entries of a state in flight together
-
-struct Entries {
-    uint32_t e[kChunk];
-};
-
-// The first CM entries (CM <= kChunk) of state s, which is in bounds.
-template <int CM>
-__device__ __forceinline__ void load_entries(Entries &r, const uint32_t *__restrict__ pred, uint32_t N, uint32_t s)
-{
-#pragma unroll
-    for (int i = 0; i < CM; ++i) r.e[i] = (pred + (size_t)i * N)[s];
-}
-
-// Entries c0 .. c0 + kChunk - 1 of state s, those from cmax on padded.
-__device__ __forceinline__ void load_chunk(Entries &r, const uint32_t *__restrict__ pred, uint32_t N, uint32_t cmax,
-                                           uint32_t c0, uint32_t s, uint32_t pad)
-{
-#pragma unroll
-    for (int i = 0; i < kChunk; ++i) {
-        r.e[i] = pad;
-        if (c0 + i < cmax) r.e[i] = (pred + (size_t)(c0 + i) * N)[s];
-    }
-}
-
-// acc += the first CM terms; all loads are issued before the sums.  X holds
-// layer k - 1: in LDS with a zero after its last state, which padded entries
-// name (GLOBAL = false), or in memory, where they are taken as zero here.
-// Padded entries name mode m, whose coefficient is zero.
-template <typename T, int COMP, int CM, bool GLOBAL>
-__device__ __forceinline__ void add_terms(Acc<T, COMP> &acc, const Entries &en, const typename Cx<T>::type *X,
-                                          uint32_t Nprev, const typename Cx<T>::type *u)
-{
-    using C = typename Cx<T>::type;
-    C v[CM], uj[CM];
-#pragma unroll
-    for (int i = 0; i < CM; ++i) {
-        const uint32_t r = en.e[i] & SLOS_PRED_MASK;
-        v[i] = X[GLOBAL ? min(r, Nprev - 1u) : r];
-        uj[i] = u[en.e[i] >> 24];
-    }
-#pragma unroll
-    for (int i = 0; i < CM; ++i) {
-        if (GLOBAL && (en.e[i] & SLOS_PRED_MASK) >= Nprev) v[i] = C{0, 0};
-        acc.mac(uj[i], v[i]);
-    }
-}
-
-// The sum of state s; CM = min(cmax, kChunk), its first CM entries loaded.
-template <typename T, int COMP, int CM, bool GLOBAL>
-__device__ __forceinline__ Acc<T, COMP> state_sum(const Entries &first, const uint32_t *__restrict__ pred, uint32_t N,
-                                                  uint32_t cmax, uint32_t s, const typename Cx<T>::type *X,
-                                                  uint32_t Nprev, const typename Cx<T>::type *u, int m, float sigma)
-{
-    Acc<T, COMP> acc;
-    acc.zero();
-    acc.start(sigma);
-    add_terms<T, COMP, CM, GLOBAL>(acc, first, X, Nprev, u);
-    if constexpr (CM == kChunk) {
-        for (uint32_t c0 = kChunk; c0 < cmax; c0 += kChunk) {  // states of more than kChunk occupied modes
-            Entries en;
-            load_chunk(en, pred, N, cmax, c0, s, SLOS_FLAT_PAD(m, Nprev));
-            add_terms<T, COMP, kChunk, GLOBAL>(acc, en, X, Nprev, u);
-        }
-    }
-    return acc;
-}
-
-// f(CM as an integral constant), CM = min(cmax, kChunk)
-template <int CM> struct Terms {
-    static constexpr int value = CM;
-};
-template <typename F>
-__device__ __forceinline__ void with_terms(uint32_t cmax, F &&f)
-{
-    switch (cmax) {
-    case 1: f(Terms<1>{}); break;
-    case 2: f(Terms<2>{}); break;
-    case 3: f(Terms<3>{}); break;
-    case 4: f(Terms<4>{}); break;
-    case 5: f(Terms<5>{}); break;
-    case 6: f(Terms<6>{}); break;
-    case 7: f(Terms<7>{}); break;
-    default: f(Terms<kChunk>{}); break;
-    }
-}
-
-__device__ __forceinline__ float wave_max(float v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
-__device__ __forceinline__ double wave_sum(double v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-// Store one output of the pass's layer: A_k as it is, or (last layer) a(S) or
-// P(S) with the FP64 normalisation f; returns P(S) for the sum.
-template <typename T, int MODE, int COMP>
-__device__ __forceinline__ double store_last(const Acc<T, COMP> &acc, double f, void *Y, uint32_t s)
-{
-    using C = typename Cx<T>::type;
-    const double ar = acc.re() * f, ai = acc.im() * f;
-    const double pr = prob(ar, ai);
-    if (MODE == SLOS_MODE_AMPL) ((C *)Y)[s] = C{(T)ar, (T)ai};
-    else ((T *)Y)[s] = (T)pr;
-    return pr;
-}
 
 // The sum of the workgroups' FP64 partials, formed by the workgroup that ends
 // last: each publishes its partial and counts itself in, and the one that finds
@@ -431,7 +317,7 @@ __device__ __forceinline__ void unrank_photons(const FlatTables &p, int k, uint6
 }
 
 // Predecessor (and successor) tables: blockIdx.y < kf is layer blockIdx.y + 1's
-// predecessor table (and, for the last one, its normalisation), the others the
+// predecessor table (and its normalisation where scale_on asks for it), the others the
 // successor tables of layers 1..kb.
 __global__ __launch_bounds__(256) void table_kernel(FlatTables p)
 {
@@ -469,7 +355,7 @@ __global__ __launch_bounds__(256) void table_kernel(FlatTables p)
             if (r < k) up -= B(d[r] + r - 1, r);
         }
         for (int c = lo; c < cmax; ++c) out[(size_t)c * N] = SLOS_FLAT_PAD(p.m, p.N[k - 1]);
-        if (k == p.kf && p.scale) {
+        if (p.scale_on >> k & 1u) {
             // sqrt(prod s_j!) / sqrt(prod t_i!), in the tiled kernel's two factors
             double fh = 1.0, fl = 1.0;
             int run = 0;
@@ -481,7 +367,7 @@ __global__ __launch_bounds__(256) void table_kernel(FlatTables p)
                 run = r > 1 && d[r - 1] == d[r - 2] ? run + 1 : 1;
                 fl *= (double)run;
             }
-            p.scale[s] = (sqrt(fh) * p.norm_t) * sqrt(fl);
+            p.scale[p.scale_off[k] + s] = (sqrt(fh) * p.norm_t) * sqrt(fl);
         }
         return;
     }

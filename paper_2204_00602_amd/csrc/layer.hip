@@ -957,6 +957,7 @@ static void launch_batch(const BatchParams &p, int c64, int rr, dim3 g, dim3 b, 
 // 1024 (more waves on the cooperative instances) take the 1024-thread one.
 int slos_launch_batch(const BatchParams &p, int c64, int rr, int threads, int grid, void *stream)
 {
+    if (p.flat) return slos_launch_flat_batch(*p.flat, c64, grid, stream);
     const size_t lds = ((size_t)p.lds_wave_bytes + 256 * (c64 ? 8 : 16)) * (size_t)(threads / 64);
     const hipStream_t s = (hipStream_t)stream;
     if (threads <= 256) launch_batch<256>(p, c64, rr, dim3(grid), dim3(threads), lds, s);

@@ -682,7 +682,8 @@ int build_flat(slos_plan_t p)
     t.kb = p->bwd_kb;
     t.succ = p->d_bwd_succ;
     t.pred = p->d_flat;
-    t.scale = nscale ? p->d_scale : nullptr;
+    t.scale = p->d_scale;
+    if (nscale) t.scale_on = uint64_t(1) << p->n;  // at scale_off 0
     FlatLaunch l{};
     l.tables = &t;
     const int le = launch_flat(l, nullptr);
@@ -2219,12 +2220,43 @@ struct slos_batch_s {
     void *d_scratch = nullptr;
     void *d_vac = nullptr;
     hipGraphExec_t exec = nullptr;
+    // table-driven batches (flat_batch.hip); the lists and the scratch above are shared
+    bool flat = false;
+    std::vector<FlatInst> finst;
+    std::vector<FlatModes> fmodes;
+    uint32_t fb_elems = 0, fb_wave_elems = 0;
+    std::vector<uint32_t> fb_scr;        // per workgroup: its place in the scratch
+    std::vector<FlatItem> fitems;
+    uint32_t fb_slots = 0, fb_counts = 0;  // partial sums and counters of the instances in parts
+    FlatItem *d_fitems = nullptr;
+    uint64_t *d_fbinom = nullptr;
+    double *d_fpartials = nullptr;       // then the counters
+    FlatInst *d_finst = nullptr;
+    FlatModes *d_fmodes = nullptr;
+    uint32_t *d_fb_scr = nullptr;
+    double *d_fscale = nullptr;          // normalisations, then the predecessor tables
+    uint32_t *d_fpred = nullptr;
 
     void free_device()
     {
         auto f = [](void *q) {
             if (q) (void)hipFree(q);
         };
+        f(d_finst);
+        f(d_fmodes);
+        f(d_fb_scr);
+        f(d_fscale);
+        f(d_fbinom);
+        d_fbinom = nullptr;
+        f(d_fitems);
+        f(d_fpartials);
+        d_fitems = nullptr;
+        d_fpartials = nullptr;
+        d_finst = nullptr;
+        d_fmodes = nullptr;
+        d_fb_scr = nullptr;
+        d_fscale = nullptr;
+        d_fpred = nullptr;
         f(d_inst);
         f(d_wg_start);
         f(d_wg_list);
@@ -2246,6 +2278,33 @@ struct slos_batch_s {
         d_lowfac = nullptr;
         d_scratch = d_vac = nullptr;
         exec = nullptr;
+    }
+
+    FlatBatchParams flat_params(const void *U, void *out, double *sum_p) const
+    {
+        FlatBatchParams fp{};
+        fp.U = U;
+        fp.out = out;
+        fp.sum_p = sum_p;
+        fp.inst = d_finst;
+        fp.modes = d_fmodes;
+        fp.items = d_fitems;
+        fp.binom = d_fbinom;
+        fp.bstride = builder.B.stride;
+        fp.partials = d_fpartials;
+        fp.counts = (uint32_t *)(d_fpartials + fb_slots);
+        fp.pred = d_fpred;
+        fp.scale = d_fscale;
+        fp.wg_start = d_wg_start;
+        fp.wg_list = d_wg_list;
+        fp.wv_start = d_wv_start;
+        fp.wv_list = d_wv_list;
+        fp.scratch = d_scratch;
+        fp.wg_scr = d_fb_scr;
+        fp.scratch_stride = scratch_stride;
+        fp.lds_elems = fb_elems;
+        fp.wave_elems = fb_wave_elems;
+        return fp;
     }
 
     BatchParams params(const void *U, void *out, double *sum_p) const
@@ -2273,6 +2332,238 @@ struct slos_batch_s {
     }
 };
 
+// Deal instances (or items) out largest first, each to the least loaded workgroup (those
+// with wg_cost >= 0, at that cost) or wave slot (the others, at wv_cost; a
+// slot's load starts at its workgroup's).
+static void deal_instances(slos_batch_s &b, int G, int W, const std::vector<double> &wg_cost,
+                           const std::vector<double> &wv_cost)
+{
+    const int count = (int)wg_cost.size();
+    std::vector<int> order(count);
+    for (int i = 0; i < count; ++i) order[i] = i;
+    auto key = [&](int i) { return wg_cost[i] >= 0 ? wg_cost[i] * W : wv_cost[i]; };
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return key(x) > key(y); });
+    std::vector<std::vector<uint32_t>> lists(G), wlists((size_t)G * W);
+    typedef std::pair<double, uint32_t> Slot;
+    std::priority_queue<Slot, std::vector<Slot>, std::greater<Slot>> wgs, heap;
+    std::vector<double> load(G, 0.0);
+    for (int g = 0; g < G; ++g) wgs.push(Slot(0.0, (uint32_t)g));
+    for (int i : order) {
+        if (wg_cost[i] < 0) continue;
+        Slot sl = wgs.top();
+        wgs.pop();
+        lists[sl.second].push_back((uint32_t)i);
+        load[sl.second] = sl.first += wg_cost[i];
+        wgs.push(sl);
+    }
+    for (int g = 0; g < G; ++g)
+        for (int w = 0; w < W; ++w) heap.push(Slot(load[g], (uint32_t)(g * W + w)));
+    for (int i : order) {
+        if (wg_cost[i] >= 0) continue;
+        Slot sl = heap.top();
+        heap.pop();
+        wlists[sl.second].push_back((uint32_t)i);
+        sl.first += wv_cost[i];
+        heap.push(sl);
+    }
+    b.grid = G;
+    b.wg_start.assign(G + 1, 0);
+    for (int g = 0; g < G; ++g) {
+        b.wg_start[g + 1] = b.wg_start[g] + (uint32_t)lists[g].size();
+        b.wg_list.insert(b.wg_list.end(), lists[g].begin(), lists[g].end());
+    }
+    b.wv_start.assign((size_t)G * W + 1, 0);
+    for (size_t sl = 0; sl < (size_t)G * W; ++sl) {
+        b.wv_start[sl + 1] = b.wv_start[sl] + (uint32_t)wlists[sl].size();
+        b.wv_list.insert(b.wv_list.end(), wlists[sl].begin(), wlists[sl].end());
+    }
+}
+
+// Host side of a table-driven batch: false if an instance or the tables are too
+// large for it (the tiled batch kernel then runs the batch): single instances of
+// more states are faster tiled, and tables are limited to 512 MiB.
+static bool plan_flat_batch(slos_batch_s &b, const int32_t *ms, const int32_t *inputs, std::vector<FlatTables> &tables,
+                            uint64_t &entries, uint64_t &nscale)
+{
+    const Binom &B = b.builder.B;
+    const uint32_t es = b.c64 ? 8 : 16;
+    b.fb_elems = SLOS_LDS_DYNAMIC_MAX / es;
+    b.fb_wave_elems = b.fb_elems / SLOS_FB_WAVES;
+    b.out_off.assign(b.count + 1, 0);
+    b.u_off.assign(b.count + 1, 0);
+    b.finst.resize(b.count);
+    std::map<int, std::pair<int, uint64_t>> need;  // per mode count: most photons, and the photon numbers ended at
+    int64_t pos = 0;
+    for (int i = 0; i < b.count; ++i) {
+        const int m = ms[i];
+        FlatInst &I = b.finst[i];
+        I = FlatInst{};
+        double tf = 1.0;
+        for (int j = 0; j < m; ++j) {
+            for (int c = 0; c < inputs[pos + j]; ++c) I.col[I.n++] = (uint8_t)j;
+            for (int v = 2; v <= inputs[pos + j]; ++v) tf *= v;
+        }
+        I.norm_t = 1.0 / std::sqrt(tf);
+        const int n = (int)I.n;
+        const uint64_t M = B(m + n - 1, n);
+        if (M > SLOS_FLAT_MAX_STATES || (uint64_t)n * (m + 1) + 2 > b.fb_elems) return false;
+        b.u_off[i + 1] = b.u_off[i] + (int64_t)m * m;
+        b.out_off[i + 1] = b.out_off[i] + (int64_t)M;
+        I.U_off = (uint64_t)b.u_off[i];
+        I.out_off = (uint64_t)b.out_off[i];
+        auto &nd = need[m];
+        nd.first = std::max(nd.first, n);
+        nd.second |= uint64_t(1) << n;
+        pos += m;
+    }
+    entries = nscale = 0;
+    std::map<int, uint32_t> modes_of;
+    for (auto &kv : need) {
+        FlatTables t{};
+        FlatModes f{};
+        t.m = kv.first;
+        f.m = (uint32_t)t.m;
+        t.kf = kv.second.first;
+        t.bstride = B.stride;
+        t.norm_t = 1.0;
+        t.scale_on = kv.second.second & ~uint64_t(1);
+        for (int k = 0; k <= t.kf; ++k) {
+            f.N[k] = t.N[k] = (uint32_t)B(t.m + k - 1, k);
+            if (k == 0) continue;
+            f.off[k] = t.off[k] = entries;
+            entries += (uint64_t)t.N[k] * std::min(t.m, k);
+            t.leaf_cap[k] = (uint32_t)b.opts.leaf_max;
+            if (t.scale_on >> k & 1u) {
+                f.scale_off[k] = t.scale_off[k] = nscale;
+                nscale += t.N[k];
+            }
+        }
+        modes_of[t.m] = (uint32_t)b.fmodes.size();
+        b.fmodes.push_back(f);
+        tables.push_back(t);
+    }
+    if (entries > SLOS_FB_MAX_ENTRIES) return false;
+    // Costs: a workgroup's terms go through all its lanes, a wave's share them
+    // with fifteen others, and each layer adds a chain.
+    struct Cost {
+        double wg = 0.0, last = 0.0, wv = -1.0;  // on a workgroup, its last layer there, on a wave (< 0: too large)
+        bool spills = false;
+    };
+    std::vector<Cost> cost(b.count);
+    uint64_t stride = 0;
+    double total = 0.0;
+    for (int i = 0; i < b.count; ++i) {
+        FlatInst &I = b.finst[i];
+        Cost &c = cost[i];
+        I.modes = modes_of[ms[i]];
+        const FlatModes &f = b.fmodes[I.modes];
+        const int n = (int)I.n, mu = ms[i] + 1;
+        double slots = 0.0;
+        for (int k = 1; k <= n; ++k) slots += (double)f.N[k] * std::min(ms[i], k);
+        // layers beyond the LDS (the rule of run_instance)
+        const uint64_t room = b.fb_elems - (uint64_t)n * mu;
+        int kl = 0;
+        while (kl + 1 < n && (uint64_t)f.N[kl] + f.N[kl + 1] + 2 <= room) ++kl;
+        c.spills = kl + 1 < n;
+        c.wg = SLOS_FB_LAYER_CYCLES(b.c64) * n;
+        for (int k = 1; k <= n; ++k) {
+            c.last = (f.N[k - 1] + 1 > room ? SLOS_FB_BLOCK_CYCLES(b.c64) : SLOS_FB_WG_CYCLES(b.c64)) * f.N[k] *
+                     std::min(ms[i], k);
+            c.wg += c.last;
+        }
+        const uint64_t lds = (uint64_t)n * mu + (n > 0 ? f.N[n - 1] : 1u) + (n > 1 ? f.N[n - 2] : 0u) + 2u;
+        if (n == 0 || lds <= b.fb_wave_elems) c.wv = SLOS_FB_WAVE_CYCLES(b.c64) * slots + SLOS_FB_WAVE_LAYER_CYCLES(b.c64) * n;
+        total += c.wv < 0 ? c.wg : std::min(c.wg, c.wv / SLOS_FB_WAVES);
+    }
+    // A wave is the cheaper place for every instance that fits one (16 of (9, 5)
+    // take 21 us on a compute unit's waves, 107 us one after the other on the
+    // whole of it), unless it would end last there.
+    const double mean = total / SLOS_FB_GRID;
+    for (int i = 0; i < b.count; ++i) {
+        Cost &c = cost[i];
+        if (c.wv > 1.2 * mean && c.wg < c.wv) c.wv = -1.0;
+        if (c.wv < 0 && c.spills) stride = std::max<uint64_t>(stride, b.fmodes[b.finst[i].modes].N[b.finst[i].n - 1]);
+    }
+    // An instance is cut into parts while one part takes clearly longer than the
+    // mean load of a workgroup and the cut saves a fair share of that (64 uneven
+    // instances in c64: 88 us whole, 42 in parts; each part repeats the layers
+    // below the last, so 256 equal ones of (13, 7) take 82 us whole, 117 in parts).
+    std::vector<double> wg, wv;
+    std::vector<int> wave_item;  // wave instances come after the items
+    for (int i = 0; i < b.count; ++i) {
+        const Cost &c = cost[i];
+        if (c.wv >= 0) continue;
+        uint32_t parts = 1;
+        while (parts < SLOS_FB_MAX_PARTS && c.wg - c.last + c.last / parts > 1.2 * mean &&
+               c.last / parts - c.last / (2 * parts) > 0.1 * c.wg)
+            parts *= 2;
+        const uint32_t slot = b.fb_slots, cnt = b.fb_counts;
+        if (parts > 1) {
+            b.fb_slots += parts;
+            b.fb_counts += 1;
+        }
+        for (uint32_t q = 0; q < parts; ++q) {
+            b.fitems.push_back(FlatItem{(uint32_t)i, q, parts, slot, cnt});
+            wg.push_back(c.wg - c.last + c.last / parts);
+            wv.push_back(0.0);
+        }
+    }
+    const size_t nitems = b.fitems.size();
+    for (int i = 0; i < b.count; ++i)
+        if (cost[i].wv >= 0) {
+            wave_item.push_back(i);
+            wg.push_back(-1.0);
+            wv.push_back(cost[i].wv);
+        }
+    const int G = (int)std::min<size_t>(SLOS_FB_GRID, wg.size());
+    deal_instances(b, G, SLOS_FB_WAVES, wg, wv);
+    for (uint32_t &w : b.wv_list) w = (uint32_t)wave_item[w - nitems];
+    b.scratch_stride = (stride + 31) / 32 * 32;
+    b.fb_scr.assign(G, 0);
+    uint32_t places = 0;
+    for (int g = 0; g < G; ++g) {
+        bool any = false;
+        for (uint32_t e = b.wg_start[g]; e < b.wg_start[g + 1]; ++e) any = any || cost[b.fitems[b.wg_list[e]].inst].spills;
+        if (any) b.fb_scr[g] = places++;
+    }
+    b.scratch_elems = (uint64_t)places * 2 * b.scratch_stride;
+    return true;
+}
+
+// Device side: the schedule, the instances, and the tables, which kernels fill.
+static int upload_flat_batch(slos_batch_t b, std::vector<FlatTables> &tables, uint64_t entries, uint64_t nscale)
+{
+    int rc;
+    if ((rc = dev_upload(&b->d_finst, b->finst.data(), b->finst.size(), "batch instances")) ||
+        (rc = dev_upload(&b->d_fmodes, b->fmodes.data(), b->fmodes.size(), "batch tables")) ||
+        (rc = dev_upload(&b->d_fb_scr, b->fb_scr.data(), b->fb_scr.size(), "batch schedule")) ||
+        (rc = dev_upload(&b->d_wg_start, b->wg_start.data(), b->wg_start.size(), "batch schedule")) ||
+        (rc = dev_upload(&b->d_wg_list, b->wg_list.data(), b->wg_list.size(), "batch schedule")) ||
+        (rc = dev_upload(&b->d_wv_start, b->wv_start.data(), b->wv_start.size(), "batch schedule")) ||
+        (rc = dev_upload(&b->d_wv_list, b->wv_list.data(), b->wv_list.size(), "batch schedule")) ||
+        (rc = dev_upload(&b->d_fitems, b->fitems.data(), b->fitems.size(), "batch items")) ||
+        (rc = alloc_dev(&b->d_scratch, (size_t)b->scratch_elems * (b->c64 ? 8 : 16), "batch scratch")) ||
+        (rc = alloc_dev((void **)&b->d_fpartials, (size_t)b->fb_slots * 8 + (size_t)b->fb_counts * 4, "batch sums")) ||
+        (rc = clear_dev(b->d_fpartials, (size_t)b->fb_slots * 8 + (size_t)b->fb_counts * 4)) ||
+        (rc = alloc_dev((void **)&b->d_fscale, nscale * sizeof(double) + entries * sizeof(uint32_t), "batch tables")) ||
+        (rc = dev_upload(&b->d_fbinom, b->builder.B.t.data(), b->builder.B.t.size(), "binomial table")))
+        return rc;
+    b->d_fpred = (uint32_t *)(b->d_fscale + nscale);
+    hipError_t e = hipSuccess;
+    for (FlatTables &t : tables) {
+        if (t.kf == 0) continue;
+        t.binom = b->d_fbinom;
+        t.pred = b->d_fpred;
+        t.scale = b->d_fscale;
+        FlatLaunch l{};
+        l.tables = &t;
+        if ((e = (hipError_t)launch_flat(l, nullptr)) != hipSuccess) break;
+    }
+    // the batch may be used from any stream
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    return e == hipSuccess ? SLOS_OK : hip_fail(e, "batch tables");
+}
+
 extern "C" {
 
 int slos_batch_plan(int count, const int32_t *ms, const int32_t *inputs, int flags, const slos_options_t *opts,
@@ -2288,6 +2579,8 @@ int slos_batch_plan(int count, const int32_t *ms, const int32_t *inputs, int fla
         return fail(SLOS_ERR_DTYPE, "flags must hold exactly one of SLOS_C64, SLOS_C128");
     slos_options_t o{};
     if (opts) o = *opts;
+    // an option that shapes the tiling asks for the tiled batch kernel
+    const bool tiled = o.leaf_max || o.block_threads || o.grid_blocks || o.outputs_per_lane || o.low_block_max;
     if (o.leaf_max == 0) o.leaf_max = 1024;
     if (o.block_threads == 0) o.block_threads = 256;
     if (o.grid_blocks == 0) o.grid_blocks = 1024;
@@ -2323,11 +2616,20 @@ int slos_batch_plan(int count, const int32_t *ms, const int32_t *inputs, int fla
     b->c64 = dt == SLOS_C64;
     b->opts = o;
     const size_t es = b->c64 ? 8 : 16;
+    std::vector<FlatTables> flat_tables;
+    uint64_t flat_entries = 0, flat_scales = 0;
     try {
         slos_plan_s &P = b->builder;
         P.opts = o;
         if (o.low_block_max > 0) P.low_cap = (uint64_t)o.low_block_max;  // default: no cap
         P.B.build(maxm + maxn, maxn);
+        b->flat = !tiled && plan_flat_batch(*b, ms, inputs, flat_tables, flat_entries, flat_scales);
+    } catch (std::bad_alloc &) {
+        delete b;
+        return fail(SLOS_ERR_OOM, "host allocation failed while building the batch");
+    }
+    if (!b->flat) try {
+        slos_plan_s &P = b->builder;
         b->inst.resize(count);
         b->out_off.assign(count + 1, 0);
         b->u_off.assign(count + 1, 0);
@@ -2399,53 +2701,21 @@ int slos_batch_plan(int count, const int32_t *ms, const int32_t *inputs, int fla
             pos += m;
         }
         // Instances whose last layer has at least four tiles per wave run
-        // cooperatively on a workgroup; the rest run on single waves.  Both
-        // lists are filled largest first, each instance to the least loaded
-        // workgroup (load in wave time: cost / W) or wave slot (whose load
-        // starts at its workgroup's cooperative load).
+        // cooperatively on a workgroup; the rest run on single waves.
         const int G = std::min(o.grid_blocks, count);
         const int W = o.block_threads / 64;
         const uint64_t coop_min = 4ull * (uint64_t)W * 64u * (uint64_t)o.outputs_per_lane;
-        std::vector<int> order(count);
-        for (int i = 0; i < count; ++i) order[i] = i;
-        std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return cost[x] > cost[y]; });
-        std::vector<double> load(G, 0.0);
-        std::vector<std::vector<uint32_t>> lists(G), wlists((size_t)G * W);
+        std::vector<double> wg_cost(count, -1.0);
         uint64_t coop_inter = 0, small_inter = 0;
-        typedef std::pair<double, uint32_t> Slot;
-        std::vector<int> small;
-        for (int i : order) {
+        for (int i = 0; i < count; ++i) {
             if (W > 1 && last[i] >= coop_min) {
-                int g = (int)(std::min_element(load.begin(), load.end()) - load.begin());
-                load[g] += cost[i] / W;
-                lists[g].push_back((uint32_t)i);
+                wg_cost[i] = cost[i] / W;
                 coop_inter = std::max(coop_inter, inter[i]);
             } else {
-                small.push_back(i);
                 small_inter = std::max(small_inter, inter[i]);
             }
         }
-        std::priority_queue<Slot, std::vector<Slot>, std::greater<Slot>> heap;
-        for (int g = 0; g < G; ++g)
-            for (int w = 0; w < W; ++w) heap.push(Slot(load[g], (uint32_t)(g * W + w)));
-        for (int i : small) {
-            Slot sl = heap.top();
-            heap.pop();
-            wlists[sl.second].push_back((uint32_t)i);
-            sl.first += cost[i];
-            heap.push(sl);
-        }
-        b->grid = G;
-        b->wg_start.assign(G + 1, 0);
-        for (int g = 0; g < G; ++g) {
-            b->wg_start[g + 1] = b->wg_start[g] + (uint32_t)lists[g].size();
-            b->wg_list.insert(b->wg_list.end(), lists[g].begin(), lists[g].end());
-        }
-        b->wv_start.assign((size_t)G * W + 1, 0);
-        for (size_t sl = 0; sl < (size_t)G * W; ++sl) {
-            b->wv_start[sl + 1] = b->wv_start[sl] + (uint32_t)wlists[sl].size();
-            b->wv_list.insert(b->wv_list.end(), wlists[sl].begin(), wlists[sl].end());
-        }
+        deal_instances(*b, G, W, wg_cost, cost);
         // scratch: a cooperative pair for each workgroup that has cooperative
         // instances, then a small pair for every wave slot
         const uint64_t slack = (SLOS_BUFFER_SLACK + es - 1) / es;
@@ -2454,7 +2724,7 @@ int slos_batch_plan(int count, const int32_t *ms, const int32_t *inputs, int fla
         b->wg_scr.assign(G, 0);
         uint64_t pos_scr = 0;
         for (int g = 0; g < G; ++g)
-            if (!lists[g].empty()) {
+            if (b->wg_start[g + 1] > b->wg_start[g]) {
                 b->wg_scr[g] = pos_scr;
                 pos_scr += 2 * b->scratch_stride;
             }
@@ -2480,6 +2750,15 @@ int slos_batch_plan(int count, const int32_t *ms, const int32_t *inputs, int fla
         return fail(SLOS_ERR_NO_DEVICE, "no HIP device (%s)", hipGetErrorString(e));
     }
     int rc;
+    if (b->flat) {
+        if ((rc = upload_flat_batch(b, flat_tables, flat_entries, flat_scales))) {
+            b->free_device();
+            delete b;
+            return rc;
+        }
+        *out = b;
+        return SLOS_OK;
+    }
     double one_d[2] = {1.0, 0.0};
     float one_f[2] = {1.0f, 0.0f};
     if ((rc = dev_upload(&b->d_inst, b->inst.data(), b->inst.size(), "batch instances")) ||
@@ -2527,12 +2806,23 @@ int slos_batch_offsets(slos_batch_t b, int64_t *u_offsets, int64_t *out_offsets)
     return SLOS_OK;
 }
 
+static int launch_batch(slos_batch_t b, const void *U, void *out, double *sum_p, void *stream)
+{
+    if (b->flat) {
+        const FlatBatchParams fp = b->flat_params(U, out, sum_p);
+        BatchParams bp{};
+        bp.flat = &fp;
+        return slos_launch_batch(bp, b->c64, 0, 0, b->grid, stream);
+    }
+    const BatchParams bp = b->params(U, out, sum_p);
+    return slos_launch_batch(bp, b->c64, b->opts.outputs_per_lane, b->opts.block_threads, b->grid, stream);
+}
+
 int slos_batch_amplitudes(slos_batch_t b, const void *U, void *out, double *sum_p, void *stream)
 {
     if (!b) return fail(SLOS_ERR_INVALID_ARG, "batch is NULL");
     if (!U || !out) return fail(SLOS_ERR_INVALID_ARG, "U and out must be device pointers");
-    const BatchParams bp = b->params(U, out, sum_p);
-    int e = slos_launch_batch(bp, b->c64, b->opts.outputs_per_lane, b->opts.block_threads, b->grid, stream);
+    int e = launch_batch(b, U, out, sum_p, stream);
     if (e) return hip_fail((hipError_t)e, "batch kernel");
     return SLOS_OK;
 }
@@ -2551,8 +2841,7 @@ int slos_batch_capture(slos_batch_t b, const void *U, void *out, double *sum_p)
     hipGraph_t g = nullptr;
     e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
-        const BatchParams bp = b->params(U, out, sum_p);
-        int le = slos_launch_batch(bp, b->c64, b->opts.outputs_per_lane, b->opts.block_threads, b->grid, s);
+        int le = launch_batch(b, U, out, sum_p, s);
         hipError_t ee = hipStreamEndCapture(s, &g);
         e = le ? (hipError_t)le : ee;
     }

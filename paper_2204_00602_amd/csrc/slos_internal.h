@@ -274,7 +274,10 @@ struct BatchInst {
 // waves run cooperatively (all waves, a barrier between layers), first; then
 // each wave runs its own list of small instances alone (wave-level ordering
 // between layers), so no wave idles at a barrier on a one-leaf layer.
+struct FlatBatchParams;  // flat.h
+
 struct BatchParams {
+    const FlatBatchParams *flat;  // host only: the table-driven batch kernel instead (the rest is unused)
     const void *U;              // packed U matrices
     void *out;                  // packed amplitudes
     double *sum_p;              // per instance, or NULL
