@@ -9,18 +9,14 @@
 // form a colex prefix).
 //
 // Layout: P is cut into blocks of SLOS_CDF_BLOCK states.  cdf_block_kernel sums
-// each block in FP64 (one wave per block, fixed order); runs of SLOS_CDF_BLOCK
-// block sums are summed again, those few run sums are scanned in one
-// workgroup, and cdf_fix_kernel turns the block sums into the exclusive prefix
-// bp[0..nb] (bp[nb] = sum P), every step in a fixed order, so the table is
-// reproducible; the run prefixes stay after the table (sp = bp + nb + 1), and
-// the block kernel also keeps the sums of each block's 16 chunks of 64 states
-// (cs = sp + nsup + 1), and a last pass copies every 16^l-th prefix into a
-// 16-ary search tree (after cs).  A sample takes 16 lanes, so a wave serves
-// four at once: it descends the tree, each level one 16-way step over 16
-// consecutive prefixes (one cache line), to its block, finds its chunk from the
-// block's 16 chunk sums (one line), and then its state with a 16-lane scan of
-// that chunk's 64 probabilities (four per lane): about 1 KB per sample.
+// each block in FP64 (one wave per block, fixed order) and keeps the sums of its
+// 16 chunks of 64 states (cs = sp + nsup + 1); runs of SLOS_CDF_BLOCK block sums
+// are summed again (sp = bp + nb + 1), and cdf_scan_kernel turns the block sums
+// into the exclusive prefix bp[0..nb] (bp[nb] = sum P), every step in a fixed
+// order, so the table is reproducible, and copies every 16^l-th prefix into a
+// 16-ary search tree (after cs).  A sample finds its block in the tree, its chunk
+// from the block's 16 chunk sums (one line), and then its state with a scan of
+// that chunk's 64 probabilities: about 1 KB per sample.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -116,91 +112,95 @@ __global__ __launch_bounds__(256) void cdf_block_kernel(const T *__restrict__ P,
     }
 }
 
-// Sum of each run of SLOS_CDF_BLOCK consecutive entries of v[0..nv): one wave per run.
-__global__ __launch_bounds__(256) void cdf_super_kernel(const double *__restrict__ v, int64_t nv, int64_t nsup,
-                                                        double *__restrict__ out)
+// Sum of each run of SLOS_CDF_BLOCK consecutive entries of v[0..nv): one wave per
+// run, its sixteen loads in flight together.
+__global__ __launch_bounds__(64) void cdf_super_kernel(const double *__restrict__ v, int64_t nv, int64_t nsup,
+                                                       double *__restrict__ out)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t gw = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
-    for (int64_t b = gw; b < nsup; b += nw) {
+    const int lane = threadIdx.x;
+    for (int64_t b = blockIdx.x; b < nsup; b += gridDim.x) {
+        double x[kChunks];
+#pragma unroll
+        for (int i = 0; i < kChunks; ++i) x[i] = v[min(b * SLOS_CDF_BLOCK + i * 64 + lane, nv - 1)];
         double s = 0.0;
-        for (int i = 0; i < kChunks; ++i) {
-            const int64_t x = b * SLOS_CDF_BLOCK + i * 64 + lane;
-            if (x < nv) s += v[x];
-        }
+#pragma unroll
+        for (int i = 0; i < kChunks; ++i) s += b * SLOS_CDF_BLOCK + i * 64 + lane < nv ? x[i] : 0.0;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
         if (lane == 0) out[b] = s;
     }
 }
 
-// In place, one workgroup: v[0..nv) -> exclusive prefix, v[nv] = total.
-__global__ __launch_bounds__(1024) void cdf_scan_kernel(double *__restrict__ v, int64_t nv)
+// Block sums -> exclusive prefix, its total bp[nb] and the search tree over it.
+// A workgroup takes one run of SLOS_CDF_BLOCK block sums: it adds up the sums sp
+// of the runs before it (1024 parts, then their serial prefix, the same order in
+// every workgroup), and each of its waves scans a chunk of 64 block sums (wave
+// scan in a fixed order) and adds the prefix of the run's chunks, serially, to
+// it.  Every 16^l-th prefix goes to level l of the tree.  What bounds it is the
+// serial prefix and the latency of a few loads: for 126,000 blocks (123 runs) this
+// and the launch above take 9.4 us; as four launches (run sums, their scan on
+// one workgroup, prefix, tree) 33.
+__global__ __launch_bounds__(1024) void cdf_scan_kernel(double *__restrict__ bp, int64_t nb,
+                                                        const double *__restrict__ sp, int64_t nsup,
+                                                        double *__restrict__ tree, CdfTree t)
 {
     __shared__ double part[1024];
-    const int t = threadIdx.x;
-    const int64_t per = (nv + 1023) / 1024;
-    const int64_t lo = min((int64_t)t * per, nv), hi = min(lo + per, nv);
-    double s = 0.0;
-    for (int64_t i = lo; i < hi; ++i) s += v[i];
-    part[t] = s;
-    __syncthreads();
-    if (t == 0) {
-        double run = 0.0;
-        for (int i = 0; i < 1024; ++i) {
-            const double x = part[i];
-            part[i] = run;
-            run += x;
-        }
-        v[nv] = run;
-    }
-    __syncthreads();
-    double run = part[t];
-    for (int64_t i = lo; i < hi; ++i) {
-        const double x = v[i];
-        v[i] = run;
-        run += x;
-    }
-}
-
-// Block sums -> exclusive prefix: each wave takes one run of SLOS_CDF_BLOCK
-// block sums, starts from that run's prefix sp[run] and scans it in chunks of
-// 64 (wave scans in a fixed order).  bp[nb] = total.
-__global__ __launch_bounds__(256) void cdf_fix_kernel(double *__restrict__ bp, int64_t nb,
-                                                      const double *__restrict__ sp, int64_t nsup)
-{
-    const int lane = threadIdx.x & 63;
-    const int64_t gw = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
-    for (int64_t b = gw; b < nsup; b += nw) {
-        double run = sp[b];
-        for (int i = 0; i < kChunks; ++i) {
-            const int64_t x = b * SLOS_CDF_BLOCK + i * 64 + lane;
-            const double v = x < nb ? bp[x] : 0.0;
-            double c = v;
+    __shared__ double chunk[kChunks];
+    __shared__ double start;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int64_t per = (nsup + 1023) / 1024;
+    const int nparts = (int)((nsup + per - 1) / per);
+    for (int64_t b = blockIdx.x; b < nsup; b += gridDim.x) {
+        const int64_t x = b * SLOS_CDF_BLOCK + tid;
+        const double v = x < nb ? bp[x] : 0.0;
+        double s = 0.0;
+        for (int64_t i = min(tid * per, nsup); i < min((tid + 1) * per, nsup); ++i) s += sp[i];
+        part[tid] = s;
+        double c = v;
 #pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const double u = __shfl_up(c, o, 64);
-                if (lane >= o) c += u;
-            }
-            if (x < nb) bp[x] = run + (c - v);
-            run += __shfl(c, 63, 64);
+        for (int o = 1; o < 64; o <<= 1) {
+            const double u = __shfl_up(c, o, 64);
+            if (lane >= o) c += u;
         }
-    }
-    if (gw == 0 && lane == 0) bp[nb] = sp[nsup];
-}
-
-// Levels 1.. of the search tree: level l entry i = bp[i * 16^l].
-__global__ __launch_bounds__(256) void cdf_tree_kernel(const double *__restrict__ bp, double *__restrict__ tree,
-                                                       CdfTree t)
-{
-    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t ni = (int64_t)gridDim.x * blockDim.x;
-    for (int l = 1; l < t.nlev; ++l) {
-        int64_t stride = 1;
-        for (int q = 0; q < l; ++q) stride *= 16;
-        for (int64_t i = i0; i < t.n[l]; i += ni) tree[t.off[l] + i] = bp[i * stride];
+        if (lane == 63) chunk[wv] = c;
+        __syncthreads();
+        if (tid == 0) {
+            // prefix of the part that run b is in, then of the runs in it; the
+            // last run goes on to the total
+            const int pb = (int)(b / per);
+            double run = 0.0;
+            auto add_parts = [&](int i, int end) {
+                for (; i + 16 <= end; i += 16) {  // sixteen reads in flight before their chain of additions
+                    double y[16];
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) y[e] = part[i + e];
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) run += y[e];
+                }
+                for (; i < end; ++i) run += part[i];
+            };
+            add_parts(0, pb);
+            double r = run;
+            for (int64_t i = pb * per; i < b; ++i) r += sp[i];
+            start = r;
+            if (b == nsup - 1) {
+                add_parts(pb, nparts);
+                bp[nb] = run;
+            }
+        }
+        __syncthreads();
+        double run = start;
+        for (int i = 0; i < wv; ++i) run += chunk[i];
+        if (x < nb) {
+            const double y = run + (c - v);
+            bp[x] = y;
+            int64_t i = x;
+            for (int l = 1; l < t.nlev && (i & 15) == 0; ++l) {
+                i >>= 4;
+                tree[t.off[l] + i] = y;
+            }
+        }
+        __syncthreads();  // part, chunk and start are free
     }
 }
 
@@ -215,109 +215,191 @@ __global__ __launch_bounds__(256) void marginal_kernel(const T *__restrict__ P, 
     if (K >= m) return;
     const int64_t e = ends[K];
     const int64_t b = e / SLOS_CDF_BLOCK;
+    T v[kChunks];  // the block's states below e: sixteen loads in flight
+#pragma unroll
+    for (int i = 0; i < kChunks; ++i) {
+        const int64_t x = b * SLOS_CDF_BLOCK + i * 64 + lane;
+        v[i] = x < e ? P[x] : (T)0;
+    }
     double s = 0.0;
-    for (int64_t x = b * SLOS_CDF_BLOCK + lane; x < e; x += 64) s += (double)P[x];
+#pragma unroll
+    for (int i = 0; i < kChunks; ++i) s += (double)v[i];
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
     if (lane == 0) pk[K] = bp[b] + s;
 }
 
-// Four samples per wave, 16 lanes each: ranks[s] = first state whose
-// cumulative P exceeds r[s] * total.  A group's lanes hold the same search state;
-// each step is one load instruction for all four groups.
+// States x .. x + 3, zeros from M on.  P needs no more than its elements'
+// alignment.
+typedef float cdf_f4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef double cdf_d2u __attribute__((ext_vector_type(2), aligned(8)));
+template <typename T> __device__ __forceinline__ void load_states(T *v, const T *__restrict__ P, int64_t x, int64_t M)
+{
+    if (x + 4 <= M) {
+        if constexpr (sizeof(T) == 4) {
+            const cdf_f4u y = *(const cdf_f4u *)(P + x);
+            v[0] = y.x, v[1] = y.y, v[2] = y.z, v[3] = y.w;
+        } else {
+            const cdf_d2u y = *(const cdf_d2u *)(P + x);
+            const cdf_d2u z = *((const cdf_d2u *)(P + x) + 1);
+            v[0] = y.x, v[1] = y.y, v[2] = z.x, v[3] = z.y;
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = x + e < M ? P[x + e] : (T)0;
+    }
+}
+
+// The group's sixteen lanes: inclusive prefix of c, each partial sum from the
+// lane o below (o = 1, 2, 4, 8); the lanes without one add nothing.
+template <int CTRL> __device__ __forceinline__ double row_shr(double x)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ double group_prefix(double c)
+{
+    c += row_shr<0x111>(c);
+    c += row_shr<0x112>(c);
+    c += row_shr<0x114>(c);
+    c += row_shr<0x118>(c);
+    return c;
+}
+
+// ranks[s] = first state whose cumulative P exceeds r[s] * total.  The finest
+// level of the tree that fits the LDS is searched there by one lane per sample;
+// from it down, sixteen lanes serve a sample, four samples to an instruction and
+// kFlight of these in flight: what bounds a sample is its chain of dependent loads
+// (tree lines, chunk sums, states), and what bounds many of them is their random
+// lines (two of states, two of sums: 131 us for 1,048,576 samples of 129 M
+// states, 4 TB/s; with sixteen lanes on every level and one sample each 222).
+// States are read through the caches: 93 us at 490,314 states in c128, 122 past
+// them, and the same at 129 M.
+constexpr int kFlight = 4;
+
 template <typename T>
 __global__ __launch_bounds__(256) void sample_kernel(const T *__restrict__ P, int64_t M, const double *__restrict__ bp,
-                                                     int64_t nb, const double *__restrict__ r, int64_t count,
-                                                     int64_t *__restrict__ ranks, CdfTree tr)
+                                                      int64_t nb, const double *__restrict__ r, int64_t count,
+                                                      int64_t *__restrict__ ranks, CdfTree tr, int top, int per_wave)
 {
+    extern __shared__ double tab[];  // level `top`
     const int64_t nsup = (nb + SLOS_CDF_BLOCK - 1) / SLOS_CDF_BLOCK;
-    const double *__restrict__ sp = bp + nb + 1;  // run prefixes, nsup + 1 entries
+    const double *__restrict__ sp = bp + nb + 1;  // run sums, nsup + 1 places
     const double *__restrict__ cs = sp + nsup + 1;  // chunk sums, kChunks per block
     const double *__restrict__ tree = cs + kChunks * nb;
     const int lane = threadIdx.x & 63, g = lane >> 4, l16 = lane & 15;
     const int64_t gw = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
     const double total = bp[nb];
+    const uint32_t ntop = (uint32_t)tr.n[top];
+    {
+        const double *src = top == 0 ? bp : tree + tr.off[top];
+        for (uint32_t i = threadIdx.x; i < ntop; i += blockDim.x) tab[i] = src[i];
+    }
+    __syncthreads();
+    uint32_t half = 1;
+    while (half * 2 < ntop) half *= 2;
     // the group's 16 bits of a wave ballot
     auto gbits = [&](bool pred) -> uint32_t { return (uint32_t)((__ballot(pred) >> (16 * g)) & 0xFFFFu); };
-    for (int64_t s0 = gw * 4; s0 < count; s0 += nw * 4) {
-        const int64_t sidx = s0 + g;
-        const bool live = sidx < count;
-        const double t = r[live ? sidx : s0] * total;
-        // down the tree: at each level the largest entry <= t among the 16
-        // children of the choice above (the tables are non-decreasing and
-        // start at 0 <= t, so the predicate holds on a prefix)
-        int64_t lo = 0;
-        for (int l = tr.nlev - 1; l >= 0; --l) {
-            const double *tab = l == 0 ? bp : tree + tr.off[l];
-            const int64_t first = lo * 16;  // < n[l]: entry lo above is bp[lo * 16^(l+1)]
-            const int64_t end = min(first + 16, tr.n[l]);
-            const uint32_t bal = gbits(first + l16 < end && tab[first + l16] <= t);
-            lo = first + (bal ? 31 - __builtin_clz(bal) : 0);  // lane 0 of the group holds: tab[first] <= t
-        }
-        // the block's chunk sums (one line): the first chunk whose running sum
-        // exceeds t, else the last chunk of non-zero probability
-        const int64_t base = lo * SLOS_CDF_BLOCK;
-        const double c_own = cs[lo * kChunks + l16];
-        double c_inc = c_own;
+    for (int64_t w0 = gw * per_wave; w0 < count; w0 += nw * per_wave) {
+        // lane: one sample.  The largest entry <= t: the tables are non-decreasing
+        // and start at 0 <= t.
+        const int64_t own = w0 + (lane & (per_wave - 1));
+        const double t_own = r[min(own, count - 1)] * total;
+        uint32_t at = 0;
+        for (uint32_t h = half; h > 0; h >>= 1)
+            if (at + h < ntop && tab[at + h] <= t_own) at += h;
+        for (int q = 0; q < per_wave && w0 + q < count; q += 4 * kFlight) {
+            // group: kFlight samples.  Down the tree: at each level the largest
+            // entry <= t among the 16 children of the choice above
+            double t[kFlight], b0[kFlight], c_own[kFlight];
+            uint32_t lo[kFlight];
 #pragma unroll
-        for (int o = 1; o < kChunks; o <<= 1) {
-            const double u = __shfl_up(c_inc, o, 16);
-            if (l16 >= o) c_inc += u;
-        }
-        const double b0 = bp[lo];
-        const uint32_t c_cross = gbits(b0 + c_inc > t && c_own > 0.0);
-        const uint32_t c_pos = gbits(c_own > 0.0);
-        const int i0 = c_cross ? __builtin_ctz(c_cross) : (c_pos ? 31 - __builtin_clz(c_pos) : 0);
-        double run = b0 + __shfl(c_inc - c_own, i0, 16);
-        // then the states of the chunks from i0 on, four per lane (rounding
-        // between the chunk sums and this scan can move the crossing on to a
-        // later chunk)
-        int64_t found = -1, last_pos = -1;
-        int ci = i0;
-        for (int it = 0; it < kChunks; ++it) {
-            const bool open = found < 0 && ci < kChunks;
-            if (!__ballot(open)) break;
-            double v[4];
-            const int64_t x0 = base + (int64_t)ci * 64 + 4 * l16;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = (open && x0 + e < M) ? (double)P[x0 + e] : 0.0;
-            double in[4];
-            in[0] = v[0];
-#pragma unroll
-            for (int e = 1; e < 4; ++e) in[e] = in[e - 1] + v[e];
-            double lsum = in[3];  // exclusive prefix of the lanes' sums over the group
-#pragma unroll
-            for (int o = 1; o < 16; o <<= 1) {
-                const double u = __shfl_up(lsum, o, 16);
-                if (l16 >= o) lsum += u;
+            for (int u = 0; u < kFlight; ++u) {
+                t[u] = __shfl(t_own, q + 4 * u + g, 64);
+                lo[u] = (uint32_t)__shfl((int)at, q + 4 * u + g, 64);
+                if (top == 0) b0[u] = tab[lo[u]];
             }
-            const double excl = lsum - in[3];
-            int first_e = -1, last_e = -1;
+            for (int l = top - 1; l >= 0; --l) {
+                const double *lev = l == 0 ? bp : tree + tr.off[l];
+                const int64_t n = tr.n[l];
+                double y[kFlight];
 #pragma unroll
-            for (int e = 3; e >= 0; --e) {
-                if (v[e] > 0.0 && run + excl + in[e] > t) first_e = e;
-                if (last_e < 0 && v[e] > 0.0) last_e = e;
-            }
-            const uint32_t cross = gbits(open && first_e >= 0);
-            const uint32_t pos = gbits(open && last_e >= 0);
-            if (open) {
-                if (cross) {
-                    const int src = __builtin_ctz(cross);
-                    found = base + (int64_t)ci * 64 + 4 * src + __shfl(first_e, src, 16);
+                for (int u = 0; u < kFlight; ++u) y[u] = lev[min((int64_t)lo[u] * 16 + l16, n - 1)];
+#pragma unroll
+                for (int u = 0; u < kFlight; ++u) {
+                    const uint32_t bal = gbits((int64_t)lo[u] * 16 + l16 < n && y[u] <= t[u]);
+                    const int i = bal ? 31 - __builtin_clz(bal) : 0;
+                    lo[u] = lo[u] * 16 + (uint32_t)i;
+                    if (l == 0) b0[u] = __shfl(y[u], i, 16);
                 }
-                if (pos) {
-                    const int src = 31 - __builtin_clz(pos);
-                    last_pos = base + (int64_t)ci * 64 + 4 * src + __shfl(last_e, src, 16);
+            }
+            // the block's chunk sums (one line): the first chunk whose running sum
+            // exceeds t, else the last chunk of non-zero probability
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) c_own[u] = cs[(int64_t)lo[u] * kChunks + l16];
+            double run[kFlight];
+            int ci[kFlight];
+            T p[kFlight][4];  // the chunk's states, four per lane
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) {
+                const double c_inc = group_prefix(c_own[u]);
+                const uint32_t c_cross = gbits(b0[u] + c_inc > t[u] && c_own[u] > 0.0);
+                const uint32_t c_pos = gbits(c_own[u] > 0.0);
+                ci[u] = c_cross ? __builtin_ctz(c_cross) : (c_pos ? 31 - __builtin_clz(c_pos) : 0);
+                run[u] = b0[u] + __shfl(c_inc - c_own[u], ci[u], 16);
+                const int64_t x0 = (int64_t)lo[u] * SLOS_CDF_BLOCK + (int64_t)ci[u] * 64 + 4 * l16;
+                load_states(p[u], P, x0, M);
+            }
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) {
+                // the states of the chunks from ci on (rounding between the chunk
+                // sums and this scan can move the crossing on to a later chunk)
+                const int64_t base = (int64_t)lo[u] * SLOS_CDF_BLOCK;
+                int64_t found = -1, last_pos = -1;
+                int c = ci[u];
+                for (int it = 0; it < kChunks; ++it) {
+                    const bool open = found < 0 && c < kChunks;
+                    if (!__ballot(open)) break;
+                    if (it > 0) load_states(p[u], P, open ? base + (int64_t)c * 64 + 4 * l16 : M, M);
+                    double v[4], in[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = (double)p[u][e];
+                    in[0] = v[0];
+#pragma unroll
+                    for (int e = 1; e < 4; ++e) in[e] = in[e - 1] + v[e];
+                    const double lsum = group_prefix(in[3]);  // of the lanes' sums
+                    const double excl = lsum - in[3];
+                    int first_e = -1, last_e = -1;
+#pragma unroll
+                    for (int e = 3; e >= 0; --e) {
+                        if (v[e] > 0.0 && run[u] + excl + in[e] > t[u]) first_e = e;
+                        if (last_e < 0 && v[e] > 0.0) last_e = e;
+                    }
+                    const uint32_t cross = gbits(open && first_e >= 0);
+                    const uint32_t pos = gbits(open && last_e >= 0);
+                    if (open) {
+                        if (cross) {
+                            const int src = __builtin_ctz(cross);
+                            found = base + (int64_t)c * 64 + 4 * src + __shfl(first_e, src, 16);
+                        }
+                        if (pos) {
+                            const int src = 31 - __builtin_clz(pos);
+                            last_pos = base + (int64_t)c * 64 + 4 * src + __shfl(last_e, src, 16);
+                        }
+                        run[u] += __shfl(lsum, 15, 16);  // shuffles stay within the group, all of whose lanes are here
+                        ++c;
+                    }
                 }
-                run += __shfl(lsum, 15, 16);  // shuffles stay within the group, all of whose lanes are here
-                ++ci;
+                // rounding can leave the crossing past the block's recomputed sum:
+                // take the block's last state of non-zero probability
+                if (found < 0) found = last_pos >= 0 ? last_pos : min(base, M - 1);
+                const int64_t sidx = w0 + q + 4 * u + g;
+                if (l16 == 0 && sidx < count) ranks[sidx] = found;
             }
         }
-        // rounding can leave the crossing past the block's recomputed sum:
-        // take the block's last state of non-zero probability
-        if (found < 0) found = last_pos >= 0 ? last_pos : min(base, M - 1);
-        if (l16 == 0 && live) ranks[sidx] = found;
     }
 }
 
@@ -330,20 +412,15 @@ int slos_launch_cdf(const void *P, int c64, int64_t M, double *bp, void *stream)
     double *sp = bp + nb + 1;    // nsup + 1 run prefixes after the table
     double *cs = sp + nsup + 1;  // then 16 chunk sums per block
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((nb + 3) / 4, 8192));
-    const int gsup = (int)std::max<int64_t>(1, std::min<int64_t>((nsup + 3) / 4, 8192));
+    const int gsup = (int)std::max<int64_t>(1, std::min<int64_t>(nsup, 8192));
     hipStream_t s = (hipStream_t)stream;
     if (c64)
         hipLaunchKernelGGL(cdf_block_kernel<float>, dim3(grid), dim3(256), 0, s, (const float *)P, M, nb, bp, cs);
     else
         hipLaunchKernelGGL(cdf_block_kernel<double>, dim3(grid), dim3(256), 0, s, (const double *)P, M, nb, bp, cs);
-    hipLaunchKernelGGL(cdf_super_kernel, dim3(gsup), dim3(256), 0, s, (const double *)bp, nb, nsup, sp);
-    hipLaunchKernelGGL(cdf_scan_kernel, dim3(1), dim3(1024), 0, s, sp, nsup);
-    hipLaunchKernelGGL(cdf_fix_kernel, dim3(gsup), dim3(256), 0, s, bp, nb, (const double *)sp, nsup);
-    const CdfTree tr = cdf_tree_layout(nb);
-    if (tr.nlev > 1) {
-        const int gt = (int)std::max<int64_t>(1, std::min<int64_t>((tr.n[1] + 255) / 256, 1024));
-        hipLaunchKernelGGL(cdf_tree_kernel, dim3(gt), dim3(256), 0, s, (const double *)bp, cs + kChunks * nb, tr);
-    }
+    hipLaunchKernelGGL(cdf_super_kernel, dim3(gsup), dim3(64), 0, s, (const double *)bp, nb, nsup, sp);
+    hipLaunchKernelGGL(cdf_scan_kernel, dim3(gsup), dim3(1024), 0, s, bp, nb, (const double *)sp, nsup, cs + kChunks * nb,
+                       cdf_tree_layout(nb));
     return (int)hipGetLastError();
 }
 
@@ -363,14 +440,25 @@ int slos_launch_sample(const void *P, int c64, int64_t M, const double *bp, cons
                        int64_t *ranks, void *stream)
 {
     const int64_t nb = (M + SLOS_CDF_BLOCK - 1) / SLOS_CDF_BLOCK;
-    const int64_t waves = (count + 3) / 4;  // four samples per wave
-    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((waves + 3) / 4, 8192));
+    const CdfTree tr = cdf_tree_layout(nb);
+    // A lane for every sample's search where there are enough of them for the
+    // chip's 8192 waves, else sixteen samples to a wave, which spreads their chains
+    // of loads over the chip (65,536 samples of 20 modes, 10 photons in c128 with
+    // the table: 53 us, 72 at 64 to a wave; 1,048,576 of 22 and 11: 241 and 228).
+    // A level of at most 1024 entries (8 KB) in the LDS: one of 8192 for large
+    // workgroups is no faster (225 us against 228, 123 against 122 at 16 and 8).
+    const int threads = 256, group = threads / 64, per_wave = count >= 64 * 8192 ? 64 : 16;
+    int top = 0;
+    while (tr.n[top] > 1024) ++top;  // the last level has at most 16 entries
+    const size_t lds = (size_t)tr.n[top] * sizeof(double);
+    const int64_t waves = (count + per_wave - 1) / per_wave;
+    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((waves + group - 1) / group, 2048));
     hipStream_t s = (hipStream_t)stream;
     if (c64)
-        hipLaunchKernelGGL(sample_kernel<float>, dim3(grid), dim3(256), 0, s, (const float *)P, M, bp, nb, r, count,
-                           ranks, cdf_tree_layout(nb));
+        hipLaunchKernelGGL(sample_kernel<float>, dim3(grid), dim3(threads), lds, s, (const float *)P, M, bp, nb, r, count,
+                           ranks, tr, top, per_wave);
     else
-        hipLaunchKernelGGL(sample_kernel<double>, dim3(grid), dim3(256), 0, s, (const double *)P, M, bp, nb, r,
-                           count, ranks, cdf_tree_layout(nb));
+        hipLaunchKernelGGL(sample_kernel<double>, dim3(grid), dim3(threads), lds, s, (const double *)P, M, bp, nb, r,
+                           count, ranks, tr, top, per_wave);
     return (int)hipGetLastError();
 }
