@@ -7,7 +7,10 @@
 // amplitude each output must equal).
 #include <hip/hip_runtime_api.h>
 
+#include <emmintrin.h>
+
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -166,6 +169,15 @@ struct ByteVecHash {
     }
 };
 
+// One target of slos_select on the host: its occupied modes (occupation
+// descending, then mode ascending) and the multiset of its occupations as a 64-bit
+// key (the occupations in descending order, each written as that many one bits
+// and a zero: at most n + 32 bits).
+struct SelectParsed {
+    uint64_t key, R;
+    int nocc;
+};
+
 struct slos_plan_s {
     int m = 0, n = 0, flags = 0;
     bool c64 = true, comp = false, keep = false, host_only = false;
@@ -215,9 +227,23 @@ struct slos_plan_s {
     double *d_cdf = nullptr;          // block prefix of the last slos_cdf input (nb + 1), run prefixes, chunk sums, search tree
     int64_t *d_pk_ends = nullptr;     // C(K+n-1, n) for K = 1..m
     double *d_ps_partials = nullptr;  // post-selection partial sums + reduction stage
-    SelectTarget *d_sel = nullptr;    // target descriptors of the last slos_select call
-    SelectTarget *h_sel = nullptr;    // their pinned host staging (sel_cap entries)
-    std::vector<SelectTarget> sel_build;  // built here, then copied to the staging
+    char *d_sel = nullptr;            // targets of the last slos_select call: their order, then their rows
+    char *h_sel = nullptr;            // pinned host staging (both of sel_cap targets)
+    struct SelectMissing {            // a target whose pattern no earlier call met
+        int64_t i;
+        SelectParsed t;
+    };
+    struct SelectWorker {             // a host thread that parses targets
+        std::vector<SelectMissing> missing;
+        std::vector<int64_t> uses;    // targets of each known pattern
+        int64_t bad = -1;
+        int kind = 0;
+        bool oom = false;
+    };
+    std::vector<SelectWorker> sel_work;
+    std::vector<uint32_t> sel_ids;    // each target's pattern
+    std::vector<int64_t> sel_uses, sel_at;  // each pattern's targets, and its place in the order
+    std::vector<uint8_t> sel_cls;     // each pattern's class
     // sub-lattice tables of every occupation multiset seen by slos_select so
     // far (kept across calls; re-uploaded when a call adds one)
     std::unordered_map<std::vector<uint8_t>, uint32_t, ByteVecHash> sel_pat_of;
@@ -1942,6 +1968,93 @@ int slos_postselect(slos_plan_t p, const void *probs, const int32_t *group_of_mo
     return SLOS_OK;
 }
 
+// Any target; returns 0, or 1: a negative occupation, 2: R > r_cap, 3: not n photons.
+static int select_parse(const int32_t *s, int m, int n, uint64_t r_cap, uint8_t *mode, SelectParsed &o)
+{
+    int occ_n[SLOS_SELECT_MAX_OCC], occ_j[SLOS_SELECT_MAX_OCC];
+    int tot = 0, nocc = 0;
+    uint64_t R = 1;
+    for (int j = 0; j < m; ++j) {
+        const int v = s[j];
+        if (v == 0) continue;
+        if (v < 0 || tot + v > n) {
+            tot = v < 0 ? -1 : n + 1;
+            break;
+        }
+        tot += v;
+        int q = nocc++;  // insert: occupation descending, then mode ascending
+        while (q > 0 && occ_n[q - 1] < v) {
+            occ_n[q] = occ_n[q - 1];
+            occ_j[q] = occ_j[q - 1];
+            --q;
+        }
+        occ_n[q] = v;
+        occ_j[q] = j;
+        R *= (uint64_t)v + 1;
+        if (R > r_cap) break;
+    }
+    if (tot != n || R > r_cap) return tot < 0 ? 1 : (R > r_cap ? 2 : 3);
+    o.key = 0;
+    for (int q = 0; q < nocc; ++q) {
+        o.key = (o.key << (occ_n[q] + 1)) | (((1ull << occ_n[q]) - 1) << 1);
+        mode[q] = (uint8_t)occ_j[q];
+    }
+    o.R = R;
+    o.nocc = nocc;
+    return 0;
+}
+
+// The same for m <= 64 without a branch per mode: occupations as bytes, sixteen to
+// a vector, and a bit mask of the modes that hold v for each v.  False for what
+// it does not decide: an error, or more than twelve photons in a mode.
+// `room`: int32 values that may be read from s on.
+#define SLOS_SELECT_FAST_OCC 12
+static bool select_parse_fast(const int32_t *s, int m, int n, int64_t room, uint64_t r_cap, uint8_t *mode, SelectParsed &o)
+{
+    const int groups = (m + 15) / 16;
+    __m128i b[4];
+    __m128i sum = _mm_setzero_si128();
+    int neg = 0;
+    for (int g = 0; g < groups; ++g) {
+        alignas(16) int32_t tail[16];
+        const int32_t *from = s + 16 * g;
+        if (16 * (g + 1) > room) {  // the last rows
+            for (int e = 0; e < 16; ++e) tail[e] = 16 * g + e < m ? from[e] : 0;
+            from = tail;
+        }
+        const __m128i *v = (const __m128i *)from;
+        b[g] = _mm_packs_epi16(_mm_packs_epi32(_mm_loadu_si128(v), _mm_loadu_si128(v + 1)),
+                               _mm_packs_epi32(_mm_loadu_si128(v + 2), _mm_loadu_si128(v + 3)));
+        if (16 * (g + 1) > m)  // past the row
+            b[g] = _mm_and_si128(b[g], _mm_cmplt_epi8(_mm_set_epi8(15, 14, 13, 12, 11, 10, 9, 8, 7, 6, 5, 4, 3, 2, 1, 0),
+                                                      _mm_set1_epi8((char)(m - 16 * g))));
+        neg |= _mm_movemask_epi8(b[g]);
+        sum = _mm_add_epi64(sum, _mm_sad_epu8(b[g], _mm_setzero_si128()));
+    }
+    const int tot = _mm_cvtsi128_si32(sum) + _mm_cvtsi128_si32(_mm_unpackhi_epi64(sum, sum));
+    if (neg || tot != n) return false;
+    uint64_t at[SLOS_SELECT_FAST_OCC + 1];
+    int left = n, top = 0;
+    while (left > 0) {
+        if (++top > SLOS_SELECT_FAST_OCC) return false;
+        uint64_t w = 0;
+        for (int g = 0; g < groups; ++g)
+            w |= (uint64_t)(uint32_t)_mm_movemask_epi8(_mm_cmpeq_epi8(b[g], _mm_set1_epi8((char)top))) << (16 * g);
+        at[top] = w;
+        left -= top * __builtin_popcountll(w);
+    }
+    o.key = 0;
+    o.R = 1;
+    o.nocc = 0;
+    for (int v = top; v > 0; --v)
+        for (uint64_t w = at[v]; w; w &= w - 1) {
+            mode[o.nocc++] = (uint8_t)__builtin_ctzll(w);
+            o.key = (o.key << (v + 1)) | (((1ull << v) - 1) << 1);
+            o.R *= (uint64_t)v + 1;
+        }
+    return o.R <= r_cap;
+}
+
 // The sub-lattice of one occupation multiset (occupations descending): its
 // states in mixed radix, listed layer by layer, each with the mask of its
 // non-zero digits; appended to the plan's pools.
@@ -1952,6 +2065,10 @@ static uint32_t select_pattern(slos_plan_s *p, const std::vector<uint8_t> &key, 
     const int n = p->n;
     SelectPattern pt{};
     pt.R = R;
+    double f = 1.0;
+    for (uint8_t v : key)
+        for (int w = 2; w <= v; ++w) f *= w;
+    pt.fac = std::sqrt(f) * p->norm_t;
     pt.nocc = (uint32_t)key.size();
     pt.off = (uint32_t)p->sel_state.size();
     uint32_t st = 1;
@@ -1959,8 +2076,11 @@ static uint32_t select_pattern(slos_plan_s *p, const std::vector<uint8_t> &key, 
         pt.stride[q] = st;
         st *= (uint32_t)key[q] + 1u;
     }
-    std::vector<uint8_t> layer(R);
-    std::vector<uint32_t> msk(R), cnt(n + 2, 0);
+    // by layer, and in a layer by the number of non-zero digits: lanes of a wave
+    // then have equally many terms
+    const int W = SLOS_SELECT_MAX_OCC + 1;
+    std::vector<uint16_t> layer(R);  // layer * W + digits
+    std::vector<uint32_t> msk(R), cnt((size_t)(n + 1) * W, 0);
     std::vector<uint32_t> digit(key.size(), 0);  // digits of x, counted up in mixed radix
     for (uint32_t x = 0; x < R; ++x) {
         uint32_t k = 0, mk = 0;
@@ -1968,9 +2088,9 @@ static uint32_t select_pattern(slos_plan_s *p, const std::vector<uint8_t> &key, 
             k += digit[q];
             if (digit[q]) mk |= 1u << q;
         }
-        layer[x] = (uint8_t)k;
+        layer[x] = (uint16_t)(k * W + __builtin_popcount(mk));
         msk[x] = mk;
-        ++cnt[k];
+        ++cnt[layer[x]];
         for (size_t q = 0; q < key.size(); ++q) {  // x + 1
             if (++digit[q] <= key[q]) break;
             digit[q] = 0;
@@ -1979,8 +2099,11 @@ static uint32_t select_pattern(slos_plan_s *p, const std::vector<uint8_t> &key, 
     uint32_t run = 0;
     for (int k = 0; k <= n; ++k) {
         pt.lstart[k] = run;
-        run += cnt[k];
-        cnt[k] = pt.lstart[k];
+        for (int d = 0; d < W; ++d) {
+            const uint32_t c = cnt[(size_t)k * W + d];
+            cnt[(size_t)k * W + d] = run;
+            run += c;
+        }
     }
     pt.lstart[n + 1] = run;
     p->sel_state.resize(p->sel_state.size() + R);
@@ -2004,7 +2127,7 @@ int slos_select(slos_plan_t p, const void *U, const int32_t *targets, int64_t co
     if (count == 0) return SLOS_OK;
     if (!U || !targets || !out) return fail(SLOS_ERR_INVALID_ARG, "U, targets and out must not be NULL");
     const int m = p->m, n = p->n;
-    const size_t es = p->elem();
+    const size_t es = p->elem(), tg_bytes = n + sizeof(uint64_t);
     // largest sub-lattice whose amplitudes fit a workgroup's LDS
     const uint64_t r_cap = SLOS_LDS_DYNAMIC_MAX / es;
     if ((size_t)count > p->sel_cap) {
@@ -2013,118 +2136,162 @@ int slos_select(slos_plan_t p, const void *U, const int32_t *targets, int64_t co
         p->d_sel = nullptr;
         p->h_sel = nullptr;
         p->sel_cap = 0;
-        if ((rc = alloc_dev((void **)&p->d_sel, (size_t)count * sizeof(SelectTarget), "target descriptors")))
-            return rc;
-        hipError_t he = hipHostMalloc((void **)&p->h_sel, (size_t)count * sizeof(SelectTarget), hipHostMallocDefault);
+        if ((rc = alloc_dev((void **)&p->d_sel, (size_t)count * tg_bytes, "target descriptors"))) return rc;
+        hipError_t he = hipHostMalloc((void **)&p->h_sel, (size_t)count * tg_bytes, hipHostMallocDefault);
         if (he != hipSuccess) {
             p->h_sel = nullptr;
             return hip_fail(he, "pinned staging of the target descriptors");
         }
         p->sel_cap = (size_t)count;
     }
-    // Targets are prepared in parallel (host threads over contiguous ranges):
-    // occupied modes in canonical order, the normalisation, and the multiset of
-    // occupations as a 64-bit key (the occupations in descending order, each
-    // written as that many one bits and a zero: at most n + 32 bits).  Patterns
-    // are then assigned in one serial pass over the keys.
-    std::vector<uint64_t> keys;
-    std::vector<uint32_t> rs;
-    try {
-        p->sel_build.resize((size_t)count);
-        keys.resize((size_t)count);
-        rs.resize((size_t)count);
-    } catch (std::bad_alloc &) {
-        return fail(SLOS_ERR_OOM, "host allocation of %lld target descriptors failed", (long long)count);
+    uint64_t *order = (uint64_t *)p->h_sel;
+    uint8_t *rows = (uint8_t *)(order + count);
+    // Targets are parsed in parallel straight into the staging: ranges of 512 from
+    // a common counter, taken by this thread and, from 4096 targets on, by one
+    // helper per 2048 (at most seven), which are joined before the call goes on.
+    // Patterns known from earlier calls are looked up there, the others are listed.
+    typedef slos_plan_s::SelectWorker Worker;
+    const int64_t kRange = 512;
+    int helpers = 0;
+    if (count >= 4096) {  // asking for the number of processors takes about 2 us
+        const int cpus = (int)std::max(1u, std::thread::hardware_concurrency());
+        helpers = (int)std::min<int64_t>(std::min(7, cpus - 1), count / 2048);
     }
-    std::vector<int64_t> bad_at(1, -1);
-    std::vector<int> bad_kind(1, 0);
-    auto prepare = [&](int64_t lo, int64_t hi, int64_t &bad, int &kind) {
-        int occ_n[SLOS_SELECT_MAX_OCC], occ_j[SLOS_SELECT_MAX_OCC];
-        for (int64_t i = lo; i < hi; ++i) {
-            const int32_t *s = targets + (size_t)i * m;
-            int tot = 0, nocc = 0;
-            double f = 1.0;
-            uint64_t R = 1;
-            for (int j = 0; j < m; ++j) {
-                const int v = s[j];
-                if (v == 0) continue;
-                if (v < 0 || tot + v > n) {
-                    tot = v < 0 ? -1 : n + 1;
-                    break;
+    std::vector<Worker> &work = p->sel_work;
+    std::vector<uint32_t> &pattern = p->sel_ids;
+    std::atomic<int64_t> next{0};
+    auto parse = [&](Worker &w) {
+        try {
+            w.uses.assign(p->sel_pats.size(), 0);
+            w.missing.clear();
+            w.bad = -1;
+            w.kind = 0;
+            w.oom = false;
+            // the patterns met last, by a hash of their keys (0 is no key: n > 0)
+            struct { uint64_t key; uint32_t pattern; } recent[64] = {};
+            for (int64_t lo; (lo = next.fetch_add(kRange, std::memory_order_relaxed)) < count;) {
+                const int64_t hi = std::min(lo + kRange, count);
+                for (int64_t i = lo; i < hi; ++i) {
+                    const int32_t *s = targets + (size_t)i * m;
+                    uint8_t *row = rows + (size_t)i * n;
+                    SelectParsed t;
+                    if (m > 64 || !select_parse_fast(s, m, n, (count - i) * m, r_cap, row, t)) {
+                        w.kind = select_parse(s, m, n, r_cap, row, t);
+                        if (w.kind) {
+                            w.bad = i;
+                            return;
+                        }
+                    }
+                    auto &r = recent[t.key * 0x9E3779B97F4A7C15ull >> 58];
+                    if (r.key != t.key || t.key == 0) {
+                        auto it = p->sel_key.find(t.key);
+                        if (it == p->sel_key.end()) {
+                            w.missing.push_back({i, t});
+                            continue;
+                        }
+                        r.key = t.key;
+                        r.pattern = it->second;
+                    }
+                    pattern[(size_t)i] = r.pattern;
+                    ++w.uses[r.pattern];
                 }
-                tot += v;
-                int q = nocc++;  // insert: occupation descending, then mode ascending
-                while (q > 0 && occ_n[q - 1] < v) {
-                    occ_n[q] = occ_n[q - 1];
-                    occ_j[q] = occ_j[q - 1];
-                    --q;
-                }
-                occ_n[q] = v;
-                occ_j[q] = j;
-                R *= (uint64_t)v + 1;
-                for (int w = 2; w <= v; ++w) f *= w;
-                if (R > r_cap) break;
             }
-            if (tot != n || R > r_cap) {
-                bad = i;
-                kind = tot < 0 ? 1 : (R > r_cap ? 2 : 3);
-                return;
-            }
-            uint64_t key = 0;
-            for (int q = 0; q < nocc; ++q) key = (key << (occ_n[q] + 1)) | (((1ull << occ_n[q]) - 1) << 1);
-            keys[(size_t)i] = key;
-            rs[(size_t)i] = (uint32_t)R;
-            SelectTarget &t = p->sel_build[(size_t)i];
-            t = SelectTarget{};
-            t.nocc = (uint32_t)nocc;
-            for (int q = 0; q < nocc; ++q) t.mode[q] = (uint8_t)occ_j[q];
-            t.fac = std::sqrt(f) * p->norm_t;
+        } catch (std::bad_alloc &) {
+            w.oom = true;
         }
     };
-    const int nth = count >= 4096 ? (int)std::min<unsigned>(8u, std::max(1u, std::thread::hardware_concurrency())) : 1;
-    bad_at.assign(nth, -1);
-    bad_kind.assign(nth, 0);
-    if (nth == 1) {
-        prepare(0, count, bad_at[0], bad_kind[0]);
-    } else {
-        std::vector<std::thread> pool;
-        try {
-            for (int w = 0; w < nth; ++w)
-                pool.emplace_back(prepare, count * w / nth, count * (w + 1) / nth, std::ref(bad_at[w]),
-                                  std::ref(bad_kind[w]));
-        } catch (...) {
-            for (auto &th : pool) th.join();
-            return fail(SLOS_ERR_OOM, "could not start the host threads that prepare the targets");
-        }
-        for (auto &th : pool) th.join();
-    }
-    for (int w = 0; w < nth; ++w) {
-        if (bad_at[w] < 0) continue;
-        const long long i = (long long)bad_at[w];
-        if (bad_kind[w] == 1) return fail(SLOS_ERR_INVALID_ARG, "target %lld has a negative occupation", i);
-        if (bad_kind[w] == 2)
-            return fail(SLOS_ERR_INVALID_ARG, "target %lld: prod(s_j + 1) exceeds %llu states (one workgroup's LDS)",
-                        i, (unsigned long long)r_cap);
-        return fail(SLOS_ERR_INVALID_ARG, "target %lld does not hold n = %d photons", i, n);
-    }
-    uint32_t r_max = 1;
     try {
+        work.resize(helpers + 1);
+        pattern.resize((size_t)count);
+        std::vector<std::thread> pool;
+        pool.reserve(helpers);
+        try {
+            for (int w = 1; w <= helpers; ++w) pool.emplace_back(parse, std::ref(work[w]));
+        } catch (...) {
+            // no more threads: those there are parse all targets
+        }
+        parse(work[0]);
+        for (auto &th : pool) th.join();
+    } catch (std::bad_alloc &) {
+        return fail(SLOS_ERR_OOM, "host allocation of the target descriptors failed");
+    }
+    int64_t bad = -1;
+    int kind = 0;
+    for (Worker &w : work) {
+        if (w.oom) return fail(SLOS_ERR_OOM, "host allocation of the target descriptors failed");
+        if (w.bad >= 0 && (bad < 0 || w.bad < bad)) {
+            bad = w.bad;
+            kind = w.kind;
+        }
+    }
+    if (kind == 1) return fail(SLOS_ERR_INVALID_ARG, "target %lld has a negative occupation", (long long)bad);
+    if (kind == 2)
+        return fail(SLOS_ERR_INVALID_ARG, "target %lld: prod(s_j + 1) exceeds %llu states (one workgroup's LDS)",
+                    (long long)bad, (unsigned long long)r_cap);
+    if (kind == 3) return fail(SLOS_ERR_INVALID_ARG, "target %lld does not hold n = %d photons", (long long)bad, n);
+
+    // New patterns, then each target to the smallest part of a workgroup that holds
+    // it (10,000 of 24 modes and 12 photons: 80 us, on whole workgroups 116; of 12
+    // and 6 in c128: 17, 74; 1,000 of 24 and 12 in c128: 20, 28).  No more targets
+    // than compute units get the waves that a large layer, a quarter of the states,
+    // fills (one of 24 and 12: 10.2 us, 11.3 on two waves).
+    SelectParams sp{};
+    try {
+        std::vector<int64_t> &uses = p->sel_uses, &at = p->sel_at;
+        uses.assign(p->sel_pats.size(), 0);
+        for (Worker &w : work)
+            for (size_t q = 0; q < w.uses.size(); ++q) uses[q] += w.uses[q];
         std::vector<uint8_t> mult;
-        for (int64_t i = 0; i < count; ++i) {
-            auto it = p->sel_key.find(keys[(size_t)i]);
-            uint32_t pi;
-            if (it != p->sel_key.end()) {
-                pi = it->second;
-            } else {
-                mult.clear();  // decode the key: runs of ones, most significant first
-                const SelectTarget &t = p->sel_build[(size_t)i];
-                const int32_t *s = targets + (size_t)i * m;
-                for (uint32_t q = 0; q < t.nocc; ++q) mult.push_back((uint8_t)s[t.mode[q]]);
-                pi = select_pattern(p, mult, rs[(size_t)i]);
-                p->sel_key.emplace(keys[(size_t)i], pi);
+        for (Worker &w : work)
+            for (const slos_plan_s::SelectMissing &t : w.missing) {
+                const uint8_t *row = rows + (size_t)t.i * n;
+                uint32_t pi;
+                auto it = p->sel_key.find(t.t.key);
+                if (it != p->sel_key.end()) {
+                    pi = it->second;
+                } else {
+                    mult.clear();
+                    const int32_t *s = targets + (size_t)t.i * m;
+                    for (int q = 0; q < t.t.nocc; ++q) mult.push_back((uint8_t)s[row[q]]);
+                    pi = select_pattern(p, mult, (uint32_t)t.t.R);
+                    p->sel_key.emplace(t.t.key, pi);
+                }
+                pattern[(size_t)t.i] = pi;
+                uses.resize(p->sel_pats.size(), 0);
+                ++uses[pi];
             }
-            p->sel_build[(size_t)i].pattern = pi;
-            r_max = std::max(r_max, rs[(size_t)i]);
+        // bytes of LDS: the sub-lattice and U's columns
+        auto need = [&](size_t q) {
+            return (uint64_t)p->sel_pats[q].R * es + (uint64_t)n * p->sel_pats[q].nocc * SLOS_SELECT_ENTRY(p->c64);
+        };
+        uint64_t lds = SLOS_SELECT_LDS;
+        for (size_t q = 0; q < uses.size(); ++q)
+            if (uses[q]) lds = std::max(lds, need(q));
+        sp.lds = (uint32_t)std::min<uint64_t>(lds, SLOS_LDS_DYNAMIC_MAX);
+        std::vector<uint8_t> &cls = p->sel_cls;
+        cls.assign(uses.size(), 0);
+        at.assign(uses.size(), 0);
+        for (size_t q = 0; q < uses.size(); ++q) {
+            int c = 0;
+            while (c < SLOS_SELECT_CLASSES - 1 && (need(q) > sp.lds >> (SLOS_SELECT_CLASSES - 1 - c) ||
+                                                   (count <= 256 && 64u << c < p->sel_pats[q].R / 4)))
+                ++c;
+            cls[q] = (uint8_t)c;
+        }
+        int64_t pos = 0;
+        for (int j = 0; j < SLOS_SELECT_CLASSES; ++j) {  // the largest first
+            const int c = SLOS_SELECT_CLASSES - 1 - j, per = SLOS_SELECT_THREADS / 64 >> c;
+            for (size_t q = 0; q < uses.size(); ++q)
+                if (cls[q] == c) {
+                    at[q] = pos;
+                    pos += uses[q];
+                }
+            sp.start[j + 1] = pos;
+            sp.blocks[j + 1] = sp.blocks[j] + (pos - sp.start[j] + per - 1) / per;
+        }
+        for (int64_t i = 0; i < count; ++i) {
+            const uint32_t pi = pattern[(size_t)i];
+            order[at[pi]++] = (uint64_t)i << SLOS_SELECT_PATTERN_BITS | pi;
         }
     } catch (std::bad_alloc &) {
         return fail(SLOS_ERR_OOM, "host allocation of the sub-lattice tables failed");
@@ -2154,19 +2321,16 @@ int slos_select(slos_plan_t p, const void *U, const int32_t *targets, int64_t co
         p->sel_uploaded = npat;
         p->sel_st_bytes = st_bytes;
     }
-    std::memcpy(p->h_sel, p->sel_build.data(), (size_t)count * sizeof(SelectTarget));
-    hipError_t e = hipMemcpyAsync(p->d_sel, p->h_sel, (size_t)count * sizeof(SelectTarget), hipMemcpyHostToDevice,
+    hipError_t e = hipMemcpyAsync(p->d_sel, p->h_sel, (size_t)count * tg_bytes, hipMemcpyHostToDevice,
                                   (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "target upload");
-    SelectParams sp{};
     sp.U = U;
-    sp.targets = p->d_sel;
+    sp.order = (const uint64_t *)p->d_sel;
+    sp.rows = (const uint8_t *)(p->d_sel + (size_t)count * sizeof(uint64_t));
     sp.patterns = (const SelectPattern *)p->d_sel_tab;
     sp.state = (const uint16_t *)(p->d_sel_tab + pat_bytes);
     sp.mask = (const uint32_t *)(p->d_sel_tab + pat_bytes + p->sel_st_bytes);
-    sp.count = count;
     sp.out = out;
-    sp.r_max = r_max;
     sp.m = m;
     sp.n = n;
     for (int k = 0; k < n; ++k) sp.cols[k] = (uint8_t)p->photons[k];

@@ -89,25 +89,32 @@ int slos_launch_postselect_table(const PostselectParams &p, int c64, const int64
 struct SelectPattern {
     uint32_t R;                          // prod over digits of (s_q + 1)
     uint32_t nocc;                       // digits
+    double fac;                          // sqrt(prod s_j!) / sqrt(prod t_i!)
     uint32_t off;                        // its states in the state and mask pools
     uint32_t lstart[SLOS_MAX_PHOTONS + 2];  // layer k: pool positions [off + lstart[k], off + lstart[k+1])
     uint32_t stride[SLOS_SELECT_MAX_OCC];   // t - e_q = index - stride[q]
 };
-struct SelectTarget {
-    uint32_t pattern;                    // its sub-lattice table
-    uint32_t nocc;                       // occupied modes of the target
-    double fac;                          // sqrt(prod s_j!) / sqrt(prod t_i!)
-    uint8_t mode[SLOS_SELECT_MAX_OCC];   // occupied modes in the pattern's digit order
-};
+// A target is a row of n bytes: its occupied modes in the pattern's digit order.
+// 32 photons have 8349 multisets of occupations.
+#define SLOS_SELECT_PATTERN_BITS 16
+// Targets by the part of a workgroup that runs one: class c has 2^c of a
+// workgroup's eight waves and of its LDS to a target.
+#define SLOS_SELECT_CLASSES 4
+#define SLOS_SELECT_THREADS 512
+#define SLOS_SELECT_LDS 32768     // bytes of a workgroup where that holds its targets: four on a CU
+#define SLOS_SELECT_ENTRY(c64) ((c64) ? 16u : 32u)  // bytes of one entry of U's columns (see select.hip)
 struct SelectParams {
     const void *U;                // m x m, plan dtype
-    const SelectTarget *targets;  // device
+    const uint8_t *rows;          // device, one per target
+    const uint64_t *order;        // the targets by class, the largest first: each its row (also its place
+                                  // in the output) * 2^SLOS_SELECT_PATTERN_BITS + its pattern
     const SelectPattern *patterns;  // device
     const uint16_t *state;        // per pattern, its states by layer (mixed-radix index)
     const uint32_t *mask;         // the non-zero digits of each listed state
-    int64_t count;
-    void *out;                    // count amplitudes, plan dtype
-    uint32_t r_max;               // largest R of the call (LDS sizing)
+    int64_t start[SLOS_SELECT_CLASSES + 1];   // class SLOS_SELECT_CLASSES - 1 - i: targets [start[i], start[i + 1])
+    int64_t blocks[SLOS_SELECT_CLASSES + 1];  // and turns of a workgroup [blocks[i], blocks[i + 1])
+    void *out;                    // plan dtype
+    uint32_t lds;                 // bytes of a workgroup
     int m, n;
     uint8_t cols[SLOS_MAX_PHOTONS];  // i_k, k = 1..n
 };
