@@ -455,9 +455,11 @@ typedef struct slos_source_s *slos_source_t;
  * Output layout ("graded"): photon number k occupies elements
  * [offsets[k], offsets[k+1]) in colex order, offsets from slos_source_info;
  * fewer than 2^32 states in all.  opts: leaf_max (default 256) only.  The
- * plan allocates 1.5 x 2^n graded FP64 vectors of device scratch, the leaf
- * tables of photon numbers 1..nmax and a batch of the 2^n common-wavepacket
- * groups; it owns them until slos_source_destroy.
+ * plan allocates 1.5 x 2^n graded FP64 vectors of device scratch, predecessor
+ * tables of photon numbers 1..nmax (4 bytes per state and occupied mode it can
+ * have; with an explicit leaf_max, more than 3,200,000 states of nmax photons or
+ * more than 512 MiB of them: leaf tables) and a batch of the 2^n
+ * common-wavepacket groups; it owns them until slos_source_destroy.
  * Errors: INVALID_ARG (bad sizes or source parameters), SIZE_OVERFLOW, OOM,
  * NO_DEVICE.
  */

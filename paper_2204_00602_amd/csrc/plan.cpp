@@ -3055,6 +3055,8 @@ struct slos_source_s {
     double *d_inv_tfac = nullptr;
     double *d_lowfac = nullptr;
     uint64_t *d_binom = nullptr;
+    uint32_t *d_table = nullptr;    // predecessor tables of photon numbers 1..nmax, or NULL
+    std::vector<uint64_t> toff;     // each photon number's, in entries
     void *d_amp = nullptr;
     double *d_slots = nullptr;      // 2^n graded vectors
     double *d_temp = nullptr;       // 2^(n-1) graded vectors (at least one)
@@ -3074,6 +3076,7 @@ struct slos_source_s {
         f(d_inv_tfac);
         f(d_lowfac);
         f(d_binom);
+        f(d_table);
         f(d_amp);
         f(d_slots);
         f(d_temp);
@@ -3087,6 +3090,7 @@ struct slos_source_s {
         d_inv_tfac = nullptr;
         d_lowfac = nullptr;
         d_binom = nullptr;
+        d_table = nullptr;
         d_amp = nullptr;
         d_slots = d_temp = d_part = d_res = nullptr;
     }
@@ -3138,6 +3142,8 @@ int slos_source_plan(int m, const int32_t *input_state, const slos_source_params
     s->x = std::sqrt(V);
     std::vector<LeafDescNarrow> desc;
     std::vector<int32_t> ms, inputs;
+    FlatTables tables{};   // kf > 0: the plan runs from tables
+    uint64_t entries = 0;
     int rc = SLOS_OK;
     try {
         for (int j = 0; j < m; ++j)
@@ -3157,10 +3163,30 @@ int slos_source_plan(int m, const int32_t *input_state, const slos_source_params
         if (s->G >= (uint64_t(1) << 32))
             throw std::pair<int, std::string>(SLOS_ERR_SIZE_OVERFLOW, "more than 2^32 states up to nmax photons");
         const uint64_t cap = (opts && opts->leaf_max > 0) ? (uint64_t)opts->leaf_max : 256u;
+        // The groups and the passes run from predecessor tables up to the states and
+        // the table sizes that the other table-driven paths take; an explicit leaf
+        // size asks for leaves.  With tables, leaves serve the groups' normalisation
+        // alone, which has at most n photons.
+        if (n > 0 && nmax > 0 && !(opts && opts->leaf_max > 0) && s->off[nmax + 1] - s->off[nmax] <= SLOS_FLAT_MAX_STATES) {
+            tables.m = m;
+            tables.bstride = P.B.stride;
+            tables.norm_t = 1.0;
+            s->toff.assign(nmax + 1, 0);
+            for (int k = 0; k <= nmax; ++k) {
+                tables.N[k] = (uint32_t)(s->off[k + 1] - s->off[k]);
+                tables.off[k] = s->toff[k] = entries;
+                tables.leaf_cap[k] = (uint32_t)cap;
+                if (k > 0) entries += (uint64_t)tables.N[k] * std::min(m, k);
+            }
+            if (entries <= SLOS_FB_MAX_ENTRIES) tables.kf = nmax;
+        }
+        const int kleaf = tables.kf > 0 ? std::min((int)n, nmax) : nmax;
         std::vector<uint64_t> deltas;
         std::vector<uint8_t> md;
         s->leaves_upto.assign(nmax + 1, 0);
         for (int k = 1; k <= nmax; ++k) {
+            s->leaves_upto[k] = desc.size();
+            if (k > kleaf) continue;
             std::vector<LeafRec> lv;
             std::vector<uint8_t> hm;
             P.gen_leaves(k, m - 1, k, cap, hm, lv);
@@ -3240,6 +3266,23 @@ int slos_source_plan(int m, const int32_t *input_state, const slos_source_params
         delete s;
         return rc;
     }
+    if (tables.kf > 0) {
+        FlatLaunch l{};
+        l.tables = &tables;
+        rc = alloc_dev((void **)&s->d_table, (size_t)entries * sizeof(uint32_t), "source tables");
+        if (rc == SLOS_OK) {
+            tables.binom = s->d_binom;
+            tables.pred = s->d_table;
+            hipError_t te = (hipError_t)launch_flat(l, nullptr);
+            if (te == hipSuccess) te = hipStreamSynchronize(nullptr);  // the plan may be used from any stream
+            if (te != hipSuccess) rc = hip_fail(te, "source tables");
+        }
+        if (rc) {
+            s->free_device();
+            delete s;
+            return rc;
+        }
+    }
     const double one[2] = {1.0, 0.0};  // the empty group: the vacuum's coefficient
     hipError_t he = hipMemcpy(s->d_amp, one, sizeof one, hipMemcpyHostToDevice);
     if (he != hipSuccess) {
@@ -3294,6 +3337,12 @@ int slos_source_probs(slos_source_t s, const void *U, double *probs, void *strea
         gp.leaf_hi = s->leaves_upto[a];
         gp.off_out = s->off[a];
         gp.off_in = s->off[a - 1];
+        if (s->d_table) {
+            gp.table = s->d_table + s->toff[a];
+            gp.N = (uint32_t)(s->off[a + 1] - s->off[a]);
+            gp.Nprev = (uint32_t)(s->off[a] - s->off[a - 1]);
+            gp.cmax = (uint32_t)std::min(s->m, a);
+        }
         if ((e = slos_launch_src_group(gp, (int)(s->sub_off[a + 1] - s->sub_off[a]), stream)))
             return hip_fail((hipError_t)e, "source group kernel");
     }
@@ -3316,6 +3365,15 @@ int slos_source_probs(slos_source_t s, const void *U, double *probs, void *strea
     pp.U = U;
     pp.m = s->m;
     pp.nmax = s->nmax;
+    if (s->d_table) {
+        pp.table = s->d_table;
+        for (int k = 0; k <= s->nmax; ++k) {
+            pp.off[k] = s->off[k];
+            pp.off[k + 1] = s->off[k + 1];
+            pp.toff[k] = s->toff[k];
+            pp.blk[k + 1] = pp.blk[k] + (uint32_t)((s->off[k + 1] - s->off[k] + 255) / 256);
+        }
+    }
     for (int b = 0; b < s->n; ++b) {
         // pairs r: P0 = slot (2r) << b (source b not common), P1 = slot (2r+1) << b.
         // With c = popcount(r): P0 holds photon numbers [c, c + 2b], P1 [c + 1, c + 1 + 2b].
@@ -3358,7 +3416,7 @@ int slos_source_probs(slos_source_t s, const void *U, double *probs, void *strea
         pp.s_b = st;
         pp.b_lo = 1;
         pp.b_len = 2 * b;
-        pp.y = P0;
+        pp.y = b == s->n - 1 ? probs : P0;  // the last one is the mixture
         pp.s_y = st;
         pp.y_len = 2 * b + 2;
         pp.gamma = 1.0;
@@ -3367,6 +3425,7 @@ int slos_source_probs(slos_source_t s, const void *U, double *probs, void *strea
         pp.nleaves = s->leaves_upto[std::min(s->nmax, cmax + pp.y_len)];
         if ((e = slos_launch_src_pass(pp, npairs, stream))) return hip_fail((hipError_t)e, "source pass kernel");
     }
+    if (s->n > 0) return SLOS_OK;
     hipError_t he = hipMemcpyAsync(probs, s->d_slots, G * 8, hipMemcpyDeviceToDevice, (hipStream_t)stream);
     if (he != hipSuccess) return hip_fail(he, "source result copy");
     return SLOS_OK;

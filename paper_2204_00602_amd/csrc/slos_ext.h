@@ -141,6 +141,8 @@ struct SrcGroupParams {
     const void *U;                  // complex128 m x m
     int m;
     uint8_t modes[SLOS_SRC_MAX_SOURCES];  // input mode of each source
+    const uint32_t *table;          // predecessor table of photon number a, or NULL: from leaves
+    uint32_t N, Nprev, cmax;
 };
 // Common-group probabilities into the slots: slot s (bit b = source b in the
 // common wavepacket) receives P = |A_s|^2 prod_j s_j! / prod_i t_i! on the
@@ -180,6 +182,11 @@ struct SrcPassParams {
     const void *U;                  // complex128 m x m
     int m, col, nmax;
     int in_lo, in_len, a_lo, a_len, b_lo, b_len, y_len;
+    // from predecessor tables (flat.hip's) instead of leaves
+    const uint32_t *table;          // or NULL
+    uint64_t off[SLOS_SRC_MAX_NMAX + 2];      // first state of each photon number
+    uint64_t toff[SLOS_SRC_MAX_NMAX + 1];     // its table, in entries
+    uint32_t blk[SLOS_SRC_MAX_NMAX + 2];      // first workgroup of each photon number
 };
 struct SrcStatsParams {
     const double *P;

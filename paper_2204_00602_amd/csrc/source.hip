@@ -27,13 +27,17 @@
 // launch per subset size), then squared and normalised into the slots.
 //
 // Vectors are graded: photon numbers 0..nmax, each in colex order, one after
-// the other.  The L pass walks the leaves of photon numbers 1..nmax (the leaf
-// descriptors of the layer kernel, ranks shifted to the graded layout): one
-// wave per leaf, lane x takes output x, predecessors through the leaf's fixed
-// high modes are whole blocks at the same inner position (coalesced), those
-// through its low modes come from the inner table.  FP64 throughout.
+// the other.  L and the groups' recurrence run one state per thread from
+// predecessor tables (flat.hip builds them at plan time).  A plan with an explicit
+// leaf size, or with too many states for the tables, walks the leaves of photon
+// numbers 1..nmax instead (the leaf descriptors of the layer kernel, ranks shifted
+// to the graded layout): one wave per leaf, lane x takes output x, predecessors
+// through the leaf's fixed high modes are whole blocks at the same inner position
+// (coalesced), those through its low modes come from the inner table.  FP64
+// throughout.
 #include <hip/hip_runtime.h>
 
+#include "flat_dev.h"
 #include "slos_ext.h"
 
 namespace {
@@ -200,6 +204,128 @@ __global__ __launch_bounds__(256) void src_pass_kernel(SrcPassParams p)
     }
 }
 
+// The same advance from a predecessor table, one state per thread (as in
+// src_flat_kernel): the chain of descriptor, inner table and gather of the leaves
+// gives way to one of entry and gather.  Six sources in 12 modes, all sizes: 27 us,
+// from the leaves 47.
+template <int CM>
+__device__ __forceinline__ void src_group_terms(const Entries &en, const double2 *__restrict__ X, uint32_t Nprev,
+                                                const double2 *uc, double &re, double &im)
+{
+    double2 v[CM], u[CM];
+#pragma unroll
+    for (int i = 0; i < CM; ++i) {
+        v[i] = X[min(en.e[i] & SLOS_PRED_MASK, Nprev - 1u)];
+        u[i] = uc[en.e[i] >> 24];
+    }
+#pragma unroll
+    for (int i = 0; i < CM; ++i)
+        if ((en.e[i] & SLOS_PRED_MASK) < Nprev) {  // not a padded entry
+            re = fma(u[i].x, v[i].x, fma(-u[i].y, v[i].y, re));
+            im = fma(u[i].x, v[i].y, fma(u[i].y, v[i].x, im));
+        }
+}
+
+__global__ __launch_bounds__(256) void src_flat_group_kernel(SrcGroupParams p)
+{
+    __shared__ double2 uc[256];
+    const uint32_t A = p.subsets[blockIdx.y], s = blockIdx.x * 256u + threadIdx.x;
+    const int top = 31 - __clz(A), j = threadIdx.x;
+    uc[j] = j < p.m ? ((const double2 *)p.U)[(size_t)j * p.m + p.modes[top]] : double2{0.0, 0.0};
+    __syncthreads();
+    if (s >= p.N) return;
+    const double2 *__restrict__ X = p.amp + p.amp_off[A & ~(1u << top)];
+    double re = 0.0, im = 0.0;
+    with_terms(p.cmax, [&](auto t) {
+        constexpr int CM = decltype(t)::value;
+        Entries en;
+        load_entries<CM>(en, p.table, p.N, s);
+        src_group_terms<CM>(en, X, p.Nprev, uc, re, im);
+        if constexpr (CM == kChunk)
+            for (uint32_t c0 = kChunk; c0 < p.cmax; c0 += kChunk) {
+                load_chunk(en, p.table, p.N, p.cmax, c0, s, SLOS_FLAT_PAD(p.m, p.Nprev));
+                src_group_terms<kChunk>(en, X, p.Nprev, uc, re, im);
+            }
+    });
+    p.amp[p.amp_off[A] + s] = double2{re, im};
+}
+
+// y = gamma L(in) + alpha a + beta b from predecessor tables: one state per thread,
+// a workgroup in one photon number, entries coalesced and all gathers of a chunk
+// of eight in flight.  The terms are summed in the leaves' order, so the bits are
+// theirs.  What bounds it is the tables (4 bytes per term; 2.7 M states of 12
+// modes and up to 12 photons: 37 us, from the leaves 81, whose waves wait for
+// a descriptor and an inner table every hundred states; all twelve passes of six
+// sources 169 and 381).
+template <int CM>
+__device__ __forceinline__ double src_terms(const Entries &en, const double *__restrict__ in, uint32_t Nprev,
+                                            const double *W, double acc)
+{
+    double v[CM], w[CM];
+#pragma unroll
+    for (int i = 0; i < CM; ++i) {
+        v[i] = in[min(en.e[i] & SLOS_PRED_MASK, Nprev - 1u)];
+        w[i] = W[en.e[i] >> 24];
+    }
+#pragma unroll
+    for (int i = 0; i < CM; ++i)  // a padded entry adds nothing, whatever the state it is clamped to holds
+        acc = (en.e[i] & SLOS_PRED_MASK) < Nprev ? fma(w[i], v[i], acc) : acc;
+    return acc;
+}
+
+__global__ __launch_bounds__(256) void src_flat_kernel(SrcPassParams p)
+{
+    __shared__ double W[256];
+    const uint32_t r = blockIdx.y;
+    const int c = __popc(r), kmax = min(p.nmax, c + p.y_len);
+    const uint32_t b = p.blk[c] + blockIdx.x;
+    if (c > p.nmax || b >= p.blk[kmax + 1]) return;
+    const double2 *U = (const double2 *)p.U;
+    {
+        const int j = threadIdx.x;
+        double w = 0.0;
+        if (j < p.m) {
+            const double2 u = U[(size_t)j * p.m + p.col];
+            w = u.x * u.x + u.y * u.y;
+        }
+        W[j] = w;
+    }
+    int k = c;
+    while (b >= p.blk[k + 1]) ++k;
+    const uint32_t N = (uint32_t)(p.off[k + 1] - p.off[k]), s = (b - p.blk[k]) * 256u + threadIdx.x;
+    const uint32_t cmax = (uint32_t)min(p.m, k);
+    const bool useL = in_support(k - 1, c, p.in_lo, p.in_len, p.nmax);
+    const double ca = in_support(k, c, p.a_lo, p.a_len, p.nmax) ? p.alpha : 0.0;
+    const double cb = in_support(k, c, p.b_lo, p.b_len, p.nmax) ? p.beta : 0.0;
+    const uint64_t at = p.off[k] + s;
+    __syncthreads();
+    if (s >= N) return;
+    double va = 0.0, vb = 0.0;
+    if (ca != 0.0) va = p.a[(size_t)r * p.s_a + at];
+    if (cb != 0.0) vb = p.b[(size_t)r * p.s_b + at];
+    double acc = 0.0;
+    if (useL) {
+        const uint32_t Nprev = (uint32_t)(p.off[k] - p.off[k - 1]);
+        const double *in = p.in + (size_t)r * p.s_in + p.off[k - 1];
+        const uint32_t *table = p.table + p.toff[k];
+        with_terms(cmax, [&](auto t) {
+            constexpr int CM = decltype(t)::value;
+            Entries en;
+            load_entries<CM>(en, table, N, s);
+            acc = src_terms<CM>(en, in, Nprev, W, acc);
+            if constexpr (CM == kChunk)
+                for (uint32_t c0 = kChunk; c0 < cmax; c0 += kChunk) {
+                    load_chunk(en, table, N, cmax, c0, s, SLOS_FLAT_PAD(p.m, Nprev));
+                    acc = src_terms<kChunk>(en, in, Nprev, W, acc);
+                }
+        });
+    }
+    double v = p.gamma * acc;
+    if (ca != 0.0) v += ca * va;
+    if (cb != 0.0) v += cb * vb;
+    p.y[(size_t)r * p.s_y + at] = v;
+}
+
 // Block i sums the states [i * chunk, (i + 1) * chunk) of its photon number k
 // (blocks blk_off[k] .. blk_off[k+1] - 1 cover photon number k) in a fixed order
 // into (mass, physical, kept); src_stats_final adds each number's blocks in order.
@@ -283,6 +409,10 @@ __global__ __launch_bounds__(256) void src_stats_final(SrcStatsParams p)
 
 int slos_launch_src_group(const SrcGroupParams &p, int nsub, void *stream)
 {
+    if (p.table) {
+        hipLaunchKernelGGL(src_flat_group_kernel, dim3((p.N + 255) / 256, nsub), dim3(256), 0, (hipStream_t)stream, p);
+        return (int)hipGetLastError();
+    }
     const uint64_t blocks = std::min<uint64_t>((p.leaf_hi - p.leaf_lo + 3) / 4, 1024);
     hipLaunchKernelGGL(src_group_kernel, dim3((unsigned)std::max<uint64_t>(blocks, 1), nsub), dim3(256), 0,
                        (hipStream_t)stream, p);
@@ -291,8 +421,8 @@ int slos_launch_src_group(const SrcGroupParams &p, int nsub, void *stream)
 
 int slos_launch_src_fill(const SrcFillParams &p, int nslots, void *stream)
 {
-    uint64_t most = 1;
-    for (int k = 1; k <= p.nmax; ++k) most = std::max<uint64_t>(most, p.leaves_upto[k] - p.leaves_upto[k - 1]);
+    uint64_t most = 1;  // of the photon numbers that a subset's group has
+    for (int k = 1; k <= p.nmax && 1 << k <= nslots; ++k) most = std::max<uint64_t>(most, p.leaves_upto[k] - p.leaves_upto[k - 1]);
     const uint64_t blocks = std::min<uint64_t>((most + 3) / 4, 1024);
     hipLaunchKernelGGL(src_fill_kernel, dim3((unsigned)blocks, nslots), dim3(256), 0, (hipStream_t)stream, p);
     return (int)hipGetLastError();
@@ -300,6 +430,13 @@ int slos_launch_src_fill(const SrcFillParams &p, int nslots, void *stream)
 
 int slos_launch_src_pass(const SrcPassParams &p, int npairs, void *stream)
 {
+    if (p.table) {
+        uint32_t grid = 1;
+        for (int c = 0; c <= p.nmax && 1 << c <= npairs; ++c)
+            grid = std::max(grid, p.blk[std::min(p.nmax, c + p.y_len) + 1] - p.blk[c]);
+        hipLaunchKernelGGL(src_flat_kernel, dim3(grid, npairs), dim3(256), 0, (hipStream_t)stream, p);
+        return (int)hipGetLastError();
+    }
     const uint64_t blocks = std::min<uint64_t>((p.nleaves + 3) / 4, 4096);
     hipLaunchKernelGGL(src_pass_kernel, dim3((unsigned)std::max<uint64_t>(blocks, 1), npairs), dim3(256), 0,
                        (hipStream_t)stream, p);
