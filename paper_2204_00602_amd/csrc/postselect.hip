@@ -44,13 +44,6 @@ __device__ void unrank(const PostselectParams &p, uint64_t rank, uint8_t *t)
     }
 }
 
-__device__ __forceinline__ bool kept(const PostselectParams &p, const uint8_t *cnt)
-{
-    bool ok = true;
-    for (int g = 0; g < p.ngroups; ++g) ok = ok && cnt[g] >= p.cmin[g] && cnt[g] <= p.cmax[g];
-    return ok;
-}
-
 __device__ __forceinline__ void count_groups(const PostselectParams &p, const uint8_t *t, uint8_t *cnt)
 {
     for (int g = 0; g < p.ngroups; ++g) cnt[g] = 0;
@@ -131,24 +124,60 @@ __global__ __launch_bounds__(256) void postselect_kernel(PostselectParams p)
 // call for the inner types the last layer uses, and ps_leaf_kernel reads P and
 // the table with the leaf's outputs (contiguous, so all accesses coalesce).
 
-// Occupations of colex rank `rank` of F(q, K) (the same decoding as unrank).
-__device__ void unrank_q(const PostselectParams &p, int q, int K, uint64_t rank, uint8_t *t)
+// The group counts of one state, without its occupations: bytes 0-7 and 8-15.
+struct GroupCounts {
+    uint64_t lo = 0, hi = 0;
+};
+
+// Those of colex rank `rank` of F(q, K) (the same decoding as unrank).  bin: the
+// binomials, grp: the group table; both in LDS, since every step of the walk waits
+// for them (the two kernels below with binomials, groups and occupations in memory:
+// 35 and 21 us at 20 modes, 10 photons and 1000 ranks; so 14 and 15).
+__device__ __forceinline__ GroupCounts unrank_counts(const uint64_t *bin, int bstride, const int8_t *grp, int q, int K,
+                                                     uint64_t rank)
 {
-    for (int j = 0; j < q; ++j) t[j] = 0;
+    GroupCounts n;
     int c = q + K - 2;
     for (int r = K; r >= 1; --r) {
-        while (c >= r && binom_at(p, c, r) > rank) --c;
-        if (c < r - 1) c = r - 1;
-        rank -= (c >= r) ? binom_at(p, c, r) : 0;
-        t[c - (r - 1)] += 1;
+        // four binomials of the walk at a time: the first of them not above rank
+        uint64_t b = 0;
+        bool found = false;
+        while (c >= r && !found) {
+            uint64_t x[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i] = bin[max(c - i, 0) * bstride + r];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (!found && c >= r) {
+                    found = x[i] <= rank;
+                    if (found) b = x[i];
+                    else --c;
+                }
+        }
+        if (found) rank -= b;
+        else c = r - 1;
+        const int g = grp[c - (r - 1)];
+        if (g >= 0) (g < 8 ? n.lo : n.hi) += uint64_t(1) << (8 * (g & 7));
         --c;
     }
+    return n;
+}
+
+// C(a, b) for a < m + n - 1 into LDS (a plan whose distribution fits the memory has
+// at most some 2,000), and the group table
+__device__ __forceinline__ void stage_unrank(const PostselectParams &p, uint64_t *bin, int8_t *grp)
+{
+    for (int j = threadIdx.x; j < 256; j += blockDim.x) grp[j] = p.group[j];
+    const int total = (p.m + p.n - 1) * p.bstride;
+    for (int i = threadIdx.x; i < total; i += blockDim.x) bin[i] = p.binom[i];
+    __syncthreads();
 }
 
 __global__ __launch_bounds__(256) void ps_low_kernel(PostselectParams p)
 {
-    extern __shared__ __align__(16) unsigned char lds[];
-    uint8_t *t = lds + (size_t)threadIdx.x * 256;  // occupations of up to 255 low modes
+    extern __shared__ __align__(16) uint64_t lds_bin[];
+    __shared__ int8_t grp[256];
+    stage_unrank(p, lds_bin, grp);
     const uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= p.entries) return;
     // inner type of entry e: last type with off <= e
@@ -159,17 +188,9 @@ __global__ __launch_bounds__(256) void ps_low_kernel(PostselectParams p)
         else hi = mid;
     }
     const PsType ty = p.types[lo];
-    unrank_q(p, ty.q, ty.K, e - ty.off, t);
-    uint8_t c[SLOS_PS_MAX_GROUPS] = {};
-    for (int j = 0; j < ty.q; ++j)
-        if (p.group[j] >= 0) c[p.group[j]] += t[j];
-    uint4 w;
-    w.x = c[0] | c[1] << 8 | c[2] << 16 | (uint32_t)c[3] << 24;
-    w.y = c[4] | c[5] << 8 | c[6] << 16 | (uint32_t)c[7] << 24;
-    w.z = c[8] | c[9] << 8 | c[10] << 16 | (uint32_t)c[11] << 24;
-    w.w = c[12] | c[13] << 8 | c[14] << 16 | (uint32_t)c[15] << 24;
-    if (p.ngroups <= 4) ((uint32_t *)p.low)[e] = w.x;  // narrow table: 4 bytes per state
-    else ((uint4 *)p.low)[e] = w;
+    const GroupCounts n = unrank_counts(lds_bin, p.bstride, grp, ty.q, ty.K, e - ty.off);
+    if (p.ngroups <= 4) ((uint32_t *)p.low)[e] = (uint32_t)n.lo;  // narrow table: 4 bytes per state
+    else ((uint4 *)p.low)[e] = uint4{(uint32_t)n.lo, (uint32_t)(n.lo >> 32), (uint32_t)n.hi, (uint32_t)(n.hi >> 32)};
 }
 
 __device__ __forceinline__ uint32_t byte_of(const uint4 &w, int g)
@@ -289,9 +310,9 @@ template <typename T>
 __global__ __launch_bounds__(64) void postselect_table_kernel(PostselectParams p, const int64_t *ranks,
                                                               int64_t nranks, const double *sum, double *table)
 {
-    extern __shared__ __align__(16) unsigned char lds[];
-    uint8_t *t = lds + (size_t)threadIdx.x * (p.m + SLOS_PS_MAX_GROUPS);
-    uint8_t *cnt = t + p.m;
+    extern __shared__ __align__(16) uint64_t lds_bin[];
+    __shared__ int8_t grp[256];
+    stage_unrank(p, lds_bin, grp);
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nranks) return;
     const int64_t r = ranks[i];
@@ -299,10 +320,14 @@ __global__ __launch_bounds__(64) void postselect_table_kernel(PostselectParams p
         table[i] = 0.0;
         return;
     }
-    unrank(p, (uint64_t)r, t);
-    count_groups(p, t, cnt);
     const double v = (double)((const T *)p.P)[r];
-    table[i] = kept(p, cnt) ? v / *sum : 0.0;
+    const GroupCounts n = unrank_counts(lds_bin, p.bstride, grp, p.m, p.n, (uint64_t)r);
+    bool ok = true;
+    for (int g = 0; g < p.ngroups; ++g) {
+        const uint32_t c = (uint32_t)((g < 8 ? n.lo : n.hi) >> (8 * (g & 7))) & 0xFFu;
+        ok = ok && c >= p.cmin[g] && c <= p.cmax[g];
+    }
+    table[i] = ok ? v / *sum : 0.0;
 }
 
 template <typename K>
@@ -315,6 +340,8 @@ hipError_t allow_lds(K kernel, size_t bytes)
     return e;
 }
 
+size_t binom_lds(const PostselectParams &p) { return (size_t)(p.m + p.n - 1) * p.bstride * sizeof(uint64_t); }
+
 } // namespace
 
 int slos_launch_postselect(const PostselectParams &p, int c64, void *stream)
@@ -323,10 +350,9 @@ int slos_launch_postselect(const PostselectParams &p, int c64, void *stream)
     if (p.nleaves > 0) {
         // leaf path: tabulate the low parts, then one wave per leaf
         const int gl = (int)((p.entries + 255) / 256);
-        hipError_t e = allow_lds(ps_low_kernel, 256 * 256);
+        hipLaunchKernelGGL(ps_low_kernel, dim3(gl > 0 ? gl : 1), dim3(256), binom_lds(p), s, p);
+        hipError_t e = hipGetLastError();
         if (e != hipSuccess) return (int)e;
-        hipLaunchKernelGGL(ps_low_kernel, dim3(gl > 0 ? gl : 1), dim3(256), 256 * 256, s, p);
-        if ((e = hipGetLastError()) != hipSuccess) return (int)e;
         const int grid = SLOS_PS_MAX_WAVES / 4;
         const bool narrow = p.ngroups <= 4;
         if (c64 && narrow)
@@ -357,7 +383,7 @@ int slos_launch_postselect_table(const PostselectParams &p, int c64, const int64
 {
     hipStream_t s = (hipStream_t)stream;
     const int grid = (int)((nranks + 63) / 64);
-    const size_t lds = 64 * (size_t)(p.m + SLOS_PS_MAX_GROUPS);
+    const size_t lds = binom_lds(p);
     if (c64)
         hipLaunchKernelGGL(postselect_table_kernel<float>, dim3(grid), dim3(64), lds, s, p, ranks, nranks, sum,
                            table);
