@@ -3076,7 +3076,6 @@ struct slos_source_s {
         f(d_inv_tfac);
         f(d_lowfac);
         f(d_binom);
-        f(d_table);
         f(d_amp);
         f(d_slots);
         f(d_temp);
@@ -3258,7 +3257,8 @@ int slos_source_plan(int m, const int32_t *input_state, const slos_source_params
         (rc = dev_upload(&s->d_binom, s->builder.B.t.data(), s->builder.B.t.size(), "binomial table")) ||
         (rc = alloc_dev(&s->d_amp, (size_t)s->namp * 16, "common-group amplitudes")) ||
         (rc = alloc_dev((void **)&s->d_slots, nslots * G * 8, "source subset vectors")) ||
-        (rc = alloc_dev((void **)&s->d_temp, ntemp * G * 8, "source butterfly scratch")) ||
+        (rc = alloc_dev((void **)&s->d_temp, ntemp * G * 8 + (tables.kf > 0 ? entries : 0) * sizeof(uint32_t),
+                        "source butterfly scratch and tables")) ||
         (rc = alloc_dev((void **)&s->d_part, (size_t)(SLOS_SRC_STATS_MAX_BLOCKS + nmax + 1) * 3 * 8,
                         "source statistics partials")) ||
         (rc = alloc_dev((void **)&s->d_res, (size_t)(nmax + 1) * 3 * 8, "source statistics"))) {
@@ -3269,15 +3269,14 @@ int slos_source_plan(int m, const int32_t *input_state, const slos_source_params
     if (tables.kf > 0) {
         FlatLaunch l{};
         l.tables = &tables;
-        rc = alloc_dev((void **)&s->d_table, (size_t)entries * sizeof(uint32_t), "source tables");
-        if (rc == SLOS_OK) {
-            tables.binom = s->d_binom;
-            tables.pred = s->d_table;
-            hipError_t te = (hipError_t)launch_flat(l, nullptr);
-            if (te == hipSuccess) te = hipStreamSynchronize(nullptr);  // the plan may be used from any stream
-            if (te != hipSuccess) rc = hip_fail(te, "source tables");
-        }
-        if (rc) {
+        s->d_table = (uint32_t *)(s->d_temp + ntemp * G);  // behind the scratch
+        tables.binom = s->d_binom;
+        tables.pred = s->d_table;
+        // complete when the copy below returns, which follows it on the null
+        // stream: the plan may be used from any stream
+        hipError_t te = (hipError_t)launch_flat(l, nullptr);
+        if (te != hipSuccess) {
+            rc = hip_fail(te, "source tables");
             s->free_device();
             delete s;
             return rc;
