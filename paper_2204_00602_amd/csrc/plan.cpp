@@ -722,6 +722,18 @@ int build_flat(slos_plan_t p)
 
 } // namespace
 
+// States per leaf of post-selection.  Leaves are dealt to 8192 waves, so few large
+// ones leave most waves idle, while many small ones share less of a table that is
+// made in every call: near the square root of the states both are small.  Whole
+// calls, with leaves of 32768 and by this rule: 20 modes, 10 photons, c128, masked
+// 184 and 112 us; 22 and 11, c64 387 and 323; 18 and 9, c128, six groups 291 and
+// 58; 15 and 7, c64 86 and 35; 24 and 12, c64 1764 with 32768 in both.  Below 1024
+// states a leaf takes no longer than its launch (8 and 4: 30 us, split 34).
+static uint64_t ps_leaf_cap(uint64_t states)
+{
+    return (uint64_t)std::min((double)SLOS_PS_LEAF_MAX, std::max(1024.0, 1.2 * std::sqrt((double)states)));
+}
+
 extern "C" {
 
 const char *slos_last_error(void) { return g_last_error.c_str(); }
@@ -887,7 +899,7 @@ int slos_plan_ex(int m, int n, const int32_t *input_state, int flags, const slos
             p->low_cap = ~uint64_t(0);
             p->ps_pass = true;
             std::vector<uint8_t> hm;
-            p->gen_leaves(n, m - 1, n, SLOS_PS_LEAF_MAX, hm, p->ps_leaves);
+            p->gen_leaves(n, m - 1, n, ps_leaf_cap(p->B(m + n - 1, n)), hm, p->ps_leaves);
             order_leaves(p->ps_leaves, 1);  // the grouped order (measured faster than colex here too)
             p->ps_pass = false;
             p->low_cap = saved;

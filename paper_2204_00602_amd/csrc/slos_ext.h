@@ -44,7 +44,7 @@ int slos_launch_sample(const void *P, int c64, int64_t M, const double *bp, cons
 // post-selection (postselect.hip)
 #define SLOS_PS_MAX_GROUPS 16
 #define SLOS_PS_MAX_WAVES 8192  // partial sums per post-selection launch
-#define SLOS_PS_LEAF_MAX 32768   // states per post-selection leaf
+#define SLOS_PS_LEAF_MAX 32768   // most states of a post-selection leaf
 // an inner shape (q low modes, K low photons) of the post-selection leaves:
 // its low states occupy table entries [off, off + size)
 struct PsType {
