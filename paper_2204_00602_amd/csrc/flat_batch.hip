@@ -18,7 +18,7 @@
 // tiled kernel takes 480 and 677, the outputs alone 43 and 86 at the rate of a
 // copy.  16 of m 6..14: c128 58 us against 376, 64 in c64 42 against 282.  What
 // bounds it is instruction issue (65 M wave instructions, 106 us on 1024 SIMDs)
-// and, in c128, 60 KB layers that no longer fit twice.
+// and, in c128, the blocks of layers that no longer fit the LDS.
 // Sixteen waves hide the gathers' latency; eight with twice the registers: 195 us
 // instead of 152 for 256 of (14, 7).
 #include <algorithm>
