@@ -2175,10 +2175,6 @@ int slos_select(slos_plan_t p, const void *U, const int32_t *targets, int64_t co
     auto parse = [&](Worker &w) {
         try {
             w.uses.assign(p->sel_pats.size(), 0);
-            w.missing.clear();
-            w.bad = -1;
-            w.kind = 0;
-            w.oom = false;
             // the patterns met last, by a hash of their keys (0 is no key: n > 0)
             struct { uint64_t key; uint32_t pattern; } recent[64] = {};
             for (int64_t lo; (lo = next.fetch_add(kRange, std::memory_order_relaxed)) < count;) {
@@ -2214,6 +2210,13 @@ int slos_select(slos_plan_t p, const void *U, const int32_t *targets, int64_t co
     };
     try {
         work.resize(helpers + 1);
+        for (Worker &w : work) {  // here: a helper that cannot be started keeps nothing of an earlier call
+            w.uses.clear();
+            w.missing.clear();
+            w.bad = -1;
+            w.kind = 0;
+            w.oom = false;
+        }
         pattern.resize((size_t)count);
         std::vector<std::thread> pool;
         pool.reserve(helpers);
