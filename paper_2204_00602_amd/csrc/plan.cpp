@@ -2282,7 +2282,10 @@ int slos_select(slos_plan_t p, const void *U, const int32_t *targets, int64_t co
         uint64_t lds = SLOS_SELECT_LDS;
         for (size_t q = 0; q < uses.size(); ++q)
             if (uses[q]) lds = std::max(lds, need(q));
-        sp.lds = (uint32_t)std::min<uint64_t>(lds, SLOS_LDS_DYNAMIC_MAX);
+        // the parts of a workgroup start where the kernel's 16-byte entries may
+        const uint64_t unit = 16u << (SLOS_SELECT_CLASSES - 1);
+        static_assert(SLOS_LDS_DYNAMIC_MAX % (16u << (SLOS_SELECT_CLASSES - 1)) == 0, "the whole LDS divides too");
+        sp.lds = (uint32_t)std::min<uint64_t>((lds + unit - 1) / unit * unit, SLOS_LDS_DYNAMIC_MAX);
         std::vector<uint8_t> &cls = p->sel_cls;
         cls.assign(uses.size(), 0);
         at.assign(uses.size(), 0);

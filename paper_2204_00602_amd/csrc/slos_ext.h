@@ -114,7 +114,7 @@ struct SelectParams {
     int64_t start[SLOS_SELECT_CLASSES + 1];   // class SLOS_SELECT_CLASSES - 1 - i: targets [start[i], start[i + 1])
     int64_t blocks[SLOS_SELECT_CLASSES + 1];  // and turns of a workgroup [blocks[i], blocks[i + 1])
     void *out;                    // plan dtype
-    uint32_t lds;                 // bytes of a workgroup
+    uint32_t lds;                 // bytes of a workgroup, a multiple of 16 in each of its parts
     int m, n;
     uint8_t cols[SLOS_MAX_PHOTONS];  // i_k, k = 1..n
 };

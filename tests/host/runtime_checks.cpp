@@ -1,6 +1,7 @@
 // Checks of plan.cpp over a stand-in runtime (runtime.cpp): what a call hands to its
 // kernel and what a plan takes of the device's memory.  The check is named by the
 // argument; prints one line per failure and exits non-zero if there was one.
+#include <algorithm>
 #include <cstdio>
 #include <cstring>
 #include <vector>
@@ -82,10 +83,67 @@ static void select_without_threads()
     slos_plan_destroy(p);
 }
 
+// every multiset of `left` photons, each occupation at most the one before, in at most `room` modes
+template <typename F> static void multisets(std::vector<int32_t> &q, int left, size_t room, F &&f)
+{
+    if (left == 0) {
+        f();
+        return;
+    }
+    if (q.size() == room) return;
+    for (int v = q.empty() ? left : std::min(left, (int)q.back()); v > 0; --v) {
+        q.push_back(v);
+        multisets(q, left - v, room, f);
+        q.pop_back();
+    }
+}
+
+// The parts of a workgroup's LDS that targets run in, for every multiset of
+// occupations beside a small one: each starts at a multiple of 16 bytes and holds
+// its target.
+static void select_parts()
+{
+    const struct { int m, n; } sizes[] = {{11, 11}, {13, 13}, {8, 16}, {8, 21}, {4, 30}};
+    for (int flags : {SLOS_C64, SLOS_C128})
+        for (const auto &z : sizes) {
+            const uint64_t es = flags == SLOS_C64 ? 8 : 16;
+            std::vector<int32_t> T(z.m, 0);
+            for (int i = 0; i < z.n; ++i) ++T[i % z.m];
+            slos_plan_t p = nullptr;
+            CHECK(slos_plan(z.m, z.n, T.data(), flags, &p) == SLOS_OK, "plan m=%d n=%d", z.m, z.n);
+            if (!p) continue;
+            std::vector<int32_t> q;
+            multisets(q, z.n, (size_t)z.m, [&] {
+                uint64_t R = 1;
+                for (int v : q) R *= (uint64_t)v + 1;
+                if (R * es > SLOS_LDS_DYNAMIC_MAX) return;
+                std::vector<int32_t> t(2 * (size_t)z.m, 0);
+                std::copy(q.begin(), q.end(), t.begin());
+                t[z.m] = z.n;
+                float u[2], out[4];
+                CHECK(slos_select(p, u, t.data(), 2, out, nullptr) == SLOS_OK, "m=%d n=%d", z.m, z.n);
+                const SelectParams &sp = fake.select;
+                CHECK(sp.lds <= SLOS_LDS_DYNAMIC_MAX && R * es <= sp.lds, "m=%d n=%d: %u bytes", z.m, z.n, sp.lds);
+                for (int j = 0; j < SLOS_SELECT_CLASSES; ++j) {
+                    if (sp.start[j + 1] == sp.start[j]) continue;
+                    const uint32_t part = sp.lds / (SLOS_SELECT_THREADS / 64 >> (SLOS_SELECT_CLASSES - 1 - j));
+                    CHECK(part % 16 == 0, "m=%d n=%d, %llu states: parts of %u bytes", z.m, z.n, (unsigned long long)R, part);
+                    for (int64_t i = sp.start[j]; i < sp.start[j + 1]; ++i) {
+                        const SelectPattern &pt = sp.patterns[sp.order[i] & ((1u << SLOS_SELECT_PATTERN_BITS) - 1)];
+                        CHECK(j == 0 || pt.R * es + (uint64_t)z.n * pt.nocc * SLOS_SELECT_ENTRY(flags == SLOS_C64) <= part,
+                              "m=%d n=%d: %u states in %u bytes", z.m, z.n, pt.R, part);
+                    }
+                }
+            });
+            slos_plan_destroy(p);
+        }
+}
+
 int main(int argc, char **argv)
 {
     const char *what = argc > 1 ? argv[1] : "";
     if (!std::strcmp(what, "select-threads")) select_without_threads();
+    else if (!std::strcmp(what, "select-parts")) select_parts();
     else {
         std::printf("no check named '%s'\n", what);
         return 2;
