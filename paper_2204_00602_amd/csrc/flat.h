@@ -91,10 +91,16 @@ struct FlatTables {
     uint64_t scale_off[SLOS_MAX_PHOTONS + 1];
     uint64_t scale_on;
     double norm_t;
-    uint32_t *succ;              // mode-major: succ[succ_off[k] + j * N[k - 1] + y] = rank of y + e_j
-    int kb;                      // layers with a successor table: 1..kb
+    uint32_t *succ;              // mode-major: succ[succ_off[k] + j * slos_succ_row + y] = rank of y + e_j
+    int kb, kt;                  // layers with a successor table: 1..kb; 1..kt are the tail launch's
     uint64_t succ_off[SLOS_MAX_PHOTONS + 1];
 };
+
+// Successor tables: N entries to a mode, N the states of layer k - 1.  In the tail
+// launch's layers a column for the states past the end and a row for the modes past
+// the last, which hold N_k, the index of the zero behind g_k.
+SLOS_HD static inline uint32_t slos_succ_row(uint32_t N, bool tail) { return N + (tail ? 1u : 0u); }
+static inline uint64_t slos_succ_entries(uint64_t N, int m, bool tail) { return tail ? (N + 1) * (m + 1) : N * m; }
 
 struct FlatLaunch {
     const HeadParams *head;      // exactly one of the three is set
@@ -215,7 +221,7 @@ struct TailParams {
     uint64_t part_off[SLOS_MAX_PHOTONS + 1];   // double2
     uint32_t rows[SLOS_MAX_PHOTONS + 1];
     uint32_t N[SLOS_MAX_PHOTONS + 1];
-    uint32_t cap[2];             // elements of the even and the odd LDS buffer
+    uint32_t cap[2];             // elements of the even and the odd LDS buffer (a zero follows each layer)
     int m, n, t;
     int wave_rows;               // sum of slos_tail_waves over its layers
     uint8_t col[SLOS_MAX_PHOTONS + 1];

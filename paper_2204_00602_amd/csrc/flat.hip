@@ -371,20 +371,25 @@ __global__ __launch_bounds__(256) void table_kernel(FlatTables p)
         }
         return;
     }
-    const uint32_t N = p.N[k - 1];
-    if (s >= N) return;
+    const uint32_t N = p.N[k - 1], row = slos_succ_row(N, k <= p.kt);
+    if (s >= row) return;
+    uint32_t *out = p.succ + p.succ_off[k] + s;
+    if (k <= p.kt) out[(size_t)p.m * row] = p.N[k];
+    if (s == N) {
+        for (int j = 0; j < p.m; ++j) out[(size_t)j * row] = p.N[k];
+        return;
+    }
     unrank_photons(p, k - 1, s, d);
     uint64_t here = 0, up = 0;  // photons above the new one: one position up
     for (int r = 1; r < k; ++r) up += B(d[r - 1] + r, r + 1);
     int q = 0;                  // photons in modes <= j
-    uint32_t *out = p.succ + p.succ_off[k] + s;
     for (int j = 0; j < p.m; ++j) {
         while (q < k - 1 && d[q] <= j) {
             here += B(d[q] + q, q + 1);
             up -= B(d[q] + q + 1, q + 2);
             ++q;
         }
-        out[(size_t)j * N] = (uint32_t)(here + B(j + q, q + 1) + up);
+        out[(size_t)j * row] = (uint32_t)(here + B(j + q, q + 1) + up);
     }
 }
 
@@ -446,8 +451,8 @@ int slos_launch_flat(const FlatLaunch &l, void *stream)
     hipStream_t s = (hipStream_t)stream;
     if (l.tables) {
         const FlatTables &t = *l.tables;
-        uint32_t most = 1;
-        for (int k = 1; k <= t.kf; ++k) most = std::max(most, t.N[k]);
+        uint32_t most = 1;  // N_k, and one more in a tail layer's successor table
+        for (int k = 1; k <= t.kf; ++k) most = std::max(most, t.N[k] + 1u);
         hipLaunchKernelGGL(table_kernel, dim3((most + 255) / 256, t.kf + t.kb), dim3(256), 0, s, t);
         return (int)hipGetLastError();
     }

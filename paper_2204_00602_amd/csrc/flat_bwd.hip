@@ -134,6 +134,7 @@ __global__ __launch_bounds__(SLOS_BWD_THREADS) void bwd_flat_kernel(FlatBwdParam
     uint32_t y[PT];
     double2 a[PT], g[PT];
     const uint32_t N = p.N, y0 = blockIdx.x * (uint32_t)(PT * SLOS_BWD_THREADS) + tid;
+    const bool whole = (blockIdx.x + 1u) * (uint64_t)(PT * SLOS_BWD_THREADS) <= N;  // no state past the end here
 #pragma unroll
     for (int r = 0; r < PT; ++r) {
         const uint32_t yr = y0 + (uint32_t)r * SLOS_BWD_THREADS;
@@ -164,6 +165,15 @@ __global__ __launch_bounds__(SLOS_BWD_THREADS) void bwd_flat_kernel(FlatBwdParam
                 }
             }
         if (j0 + 4 < m) fetch(j0 + 4);
+        // no term of a state past the end or of a mode past the last: an infinite g
+        // would not vanish against their zeros
+        if (!whole || j0 + 4 > m) {
+#pragma unroll
+            for (int r = 0; r < PT; ++r)
+#pragma unroll
+                for (int d = 0; d < 4; ++d)
+                    if (y0 + (uint32_t)r * SLOS_BWD_THREADS >= N || j0 + d >= m) s[r][d] = double2{0.0, 0.0};
+        }
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
             pj[d] = double2{0.0, 0.0};
@@ -222,8 +232,10 @@ __global__ __launch_bounds__(SLOS_BWD_TAIL_THREADS) void tail_kernel(TailParams 
     const uint64_t b = blockIdx.x;
     const C *__restrict__ Um = (const C *)((const char *)p.U + b * p.u_stride);
 
-    // A and the successor ranks of state y, clamped to the layer: NM modes jb,
-    // jb + step, ..
+    // A and the successor ranks of state y: NM modes jb, jb + step, ..  The rank of
+    // a mode past the last or of a state past the end is that of the zero behind
+    // g_k, whatever the layer's values are (the tables have a row and a column for
+    // them: forming that index here cost 43 spilled registers and 16 us).
     struct First {
         double2 a;
         uint32_t e[GM];
@@ -231,12 +243,12 @@ __global__ __launch_bounds__(SLOS_BWD_TAIL_THREADS) void tail_kernel(TailParams 
     auto load = [&](First &f, int k, int jb, uint32_t y, auto modes, int step) {
         const uint32_t N = p.N[k - 1];
         const uint32_t *__restrict__ succ = p.succ + p.succ_off[k];
-        y = min(y, N - 1u);
-        f.a = wide(((const C *)((const char *)p.keep + b * p.keep_stride + p.keep_off[k - 1]))[y]);
+        y = min(y, N);
+        f.a = wide(((const C *)((const char *)p.keep + b * p.keep_stride + p.keep_off[k - 1]))[min(y, N - 1u)]);
 #pragma unroll
         for (int d = 0; d < decltype(modes)::value; ++d) {
             f.e[d] = 0;
-            if (jb / 4 * 4 + step * (step == 1 ? d & ~3 : d) < m) f.e[d] = (succ + (size_t)min(jb + d * step, m - 1) * N)[y];
+            if (jb / 4 * 4 + step * (step == 1 ? d & ~3 : d) < m) f.e[d] = (succ + (size_t)min(jb + d * step, m) * (N + 1u))[y];
         }
     };
     auto small = [&](int k) { return p.N[k - 1] <= (uint32_t)TH; };  // four lanes a state
@@ -265,7 +277,7 @@ __global__ __launch_bounds__(SLOS_BWD_TAIL_THREADS) void tail_kernel(TailParams 
         // kernels form it one after the other, and the loss in the same order
         const C *a = (const C *)p.a + b * p.a_stride;
         const double *pt = p.p_target + b * (uint64_t)p.count;
-        for (uint32_t s = tid; s < Nt; s += TH) top[s] = C{0, 0};
+        for (uint32_t s = tid; s <= Nt; s += TH) top[s] = C{0, 0};
         __syncthreads();
         double s = 0.0;
         if (tid < 256) {
@@ -299,6 +311,7 @@ __global__ __launch_bounds__(SLOS_BWD_TAIL_THREADS) void tail_kernel(TailParams 
             }
             top[s] = v;
         }
+        if (tid == 0) top[Nt] = C{0, 0};
     }
     __syncthreads();
 
@@ -309,6 +322,7 @@ __global__ __launch_bounds__(SLOS_BWD_TAIL_THREADS) void tail_kernel(TailParams 
         const uint32_t N = p.N[k - 1];
         const double2 *uk = u + (k - 1) * ms;
         const int busy = slos_tail_waves(N);
+        if (tid == 0) gd[N] = C{0, 0};
         if (small(k)) {
             // Four lanes a state, lane q of them modes q, q + 4, ..: the chain of
             // a layer with few states is a quarter as long.
@@ -330,7 +344,7 @@ __global__ __launch_bounds__(SLOS_BWD_TAIL_THREADS) void tail_kernel(TailParams 
                         if (jb + 4 * d < m) grad_terms(g, acc[d], uk[jb + 4 * d + q], wide(gk[cur.e[d]]), a);
                     if (jb == 0) {
                         for (int j = 16 + q; j < m; j += 4)
-                            cmac(g, uk[j], wide(gk[(p.succ + p.succ_off[k] + (size_t)j * N)[min(y, N - 1u)]]));
+                            cmac(g, uk[j], wide(gk[(p.succ + p.succ_off[k] + (size_t)j * (N + 1u))[min(y, N)]]));
                         g.x = quad_sum(g.x);
                         g.y = quad_sum(g.y);
                         if (on && q == 0) gd[y] = C{(T)g.x, (T)g.y};
@@ -363,7 +377,7 @@ __global__ __launch_bounds__(SLOS_BWD_TAIL_THREADS) void tail_kernel(TailParams 
                     if (jb == 0) {
                         // modes beyond the first turn's, for g_{k-1} alone
                         for (int j = GM; j < m; ++j)
-                            cmac(g, uk[j], wide(gk[(p.succ + p.succ_off[k] + (size_t)j * N)[y]]));
+                            cmac(g, uk[j], wide(gk[(p.succ + p.succ_off[k] + (size_t)j * (N + 1u))[y]]));
                         gd[y] = C{(T)g.x, (T)g.y};
                     }
                 }

@@ -536,7 +536,7 @@ struct slos_plan_s {
         int rows = 0;
         while (bwd_t < bwd_kb) {
             const int k = bwd_t + 1;
-            const uint64_t cap[2] = {Nk[k & 1 ? k - 1 : k], Nk[k & 1 ? k : k - 1]};
+            const uint64_t cap[2] = {Nk[k & 1 ? k - 1 : k] + 1, Nk[k & 1 ? k : k - 1] + 1};
             rows += slos_tail_waves((uint32_t)Nk[k - 1]);
             if (slos_tail_lds(cap[0], cap[1], m, n, k, rows, elem()) > SLOS_BWD_LDS_MAX) break;
             if (k > 1 && Nk[k - 1] * (uint64_t)m > SLOS_BWD_TAIL_TERMS) break;
@@ -698,7 +698,7 @@ int build_flat(slos_plan_t p)
     p->bwd_succ_off.assign(p->n + 2, 0);
     for (int k = 1; k <= p->bwd_kb; ++k) {
         p->bwd_succ_off[k] = t.succ_off[k] = nsucc;
-        nsucc += p->Nk[k - 1] * (uint64_t)p->m;
+        nsucc += slos_succ_entries(p->Nk[k - 1], p->m, k <= p->bwd_t);
     }
     if ((rc = alloc_dev((void **)&p->d_scale, nscale * sizeof(double) + (entries + nsucc) * sizeof(uint32_t),
                         "predecessor tables")))
@@ -706,6 +706,7 @@ int build_flat(slos_plan_t p)
     p->d_flat = (uint32_t *)(p->d_scale + nscale);
     p->d_bwd_succ = p->d_flat + entries;
     t.kb = p->bwd_kb;
+    t.kt = p->bwd_t;
     t.succ = p->d_bwd_succ;
     t.pred = p->d_flat;
     t.scale = p->d_scale;
@@ -1576,7 +1577,7 @@ static int run_reverse_flat(slos_plan_t p, int batch, const void *U, void *grad_
     tp.cap[0] = tp.cap[1] = 1;
     for (int k = 0; k <= t; ++k) {
         tp.N[k] = (uint32_t)p->Nk[k];
-        tp.cap[k & 1] = std::max(tp.cap[k & 1], tp.N[k]);
+        tp.cap[k & 1] = std::max(tp.cap[k & 1], tp.N[k] + 1);
     }
     fl.layer = nullptr;
     fl.tail = &tp;
