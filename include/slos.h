@@ -82,7 +82,12 @@ typedef struct slos_plan_s *slos_plan_t;
  * (all but comp_from_layer and max_batch) at zero, a plan computes its layers
  * of up to a few million states from predecessor tables, the first of them in
  * one launch; a tiling option asks for the tiled kernels on every layer.  The
- * amplitudes are the same bit for bit. */
+ * amplitudes are the same bit for bit (SLOS_COMPENSATED above 64 modes: within
+ * that mode's rounding).  The tables take 4 bytes per state and mode it can
+ * occupy (at most 410 MiB), 8 per output where the last layer is among these
+ * layers, and with SLOS_KEEP_LAYERS 4 m bytes per state for the reverse layers, up
+ * to 512 MiB.  A plan, batch or source that finds no room for its tables on the
+ * device is made without them. */
 typedef struct slos_options {
     int32_t leaf_max;        /* max states per leaf tile, <= 65536 (default 16384 for
                                 c64, 8192 for c128, 4096 with SLOS_KEEP_LAYERS); a

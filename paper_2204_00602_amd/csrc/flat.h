@@ -21,6 +21,9 @@
 // 4,686,825 66 against 70 (c64; c128 99 against 84, but its table alone is
 // 170 MB), 6,906,900 83 against 100.  Also keeps every rank within 24 bits.
 #define SLOS_FLAT_MAX_STATES 3200000u
+// Entries of a plan's successor tables: 512 MiB, as the tables of a batch (by the
+// line above its predecessor tables have at most 410 MiB).
+#define SLOS_FLAT_MAX_SUCC (uint64_t(1) << 27)
 // Largest layer that every workgroup of the first launch computes for itself,
 // and the LDS its two layers may take.  One instance: m=13, n=6 (6,188 states
 // in layer 5) 12.1 us a pass with that layer in the first launch, 15.6 without;

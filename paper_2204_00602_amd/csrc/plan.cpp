@@ -529,10 +529,17 @@ struct slos_plan_s {
     }
 
     // Reverse layers from tables: those whose layer k - 1 has a table-driven
-    // size; of these the tail takes what fits one workgroup's LDS and time.
+    // size, up to the limit of all successor tables (4 m bytes a state: plans of 48
+    // modes and more meet it, at a layer below the last); of these the tail takes
+    // what fits one workgroup's LDS and time.
     void choose_flat_bwd()
     {
-        bwd_kb = std::min(n, flat_kf + 1);
+        uint64_t entries = 0;
+        while (bwd_kb < std::min(n, flat_kf + 1)) {
+            entries += Nk[bwd_kb] * (uint64_t)m;
+            if (entries > SLOS_FLAT_MAX_SUCC) break;
+            ++bwd_kb;
+        }
         int rows = 0;
         while (bwd_t < bwd_kb) {
             const int k = bwd_t + 1;
@@ -781,9 +788,12 @@ int slos_plan(int m, int n, const int32_t *input_state, int flags, slos_plan_t *
     return slos_plan_ex(m, n, input_state, flags, nullptr, out);
 }
 
-int slos_plan_ex(int m, int n, const int32_t *input_state, int flags, const slos_options_t *opts,
-                 slos_plan_t *out)
+// tables: in, whether layers may be table-driven; out, whether one is.
+static int make_plan(int m, int n, const int32_t *input_state, int flags, const slos_options_t *opts, bool &tables,
+                     slos_plan_t *out)
 {
+    const bool allowed = tables;
+    tables = false;
     if (!out) return fail(SLOS_ERR_INVALID_ARG, "out is NULL");
     *out = nullptr;
     if (m < 1 || m > SLOS_MAX_MODES)
@@ -905,7 +915,8 @@ int slos_plan_ex(int m, int n, const int32_t *input_state, int flags, const slos
             p->ps_pass = false;
             p->low_cap = saved;
         }
-        if (!tiled && n > 0 && !p->host_only) p->choose_flat();
+        if (allowed && !tiled && n > 0 && !p->host_only) p->choose_flat();
+        tables = p->flat_kf > 0;
         if (p->keep && p->flat_kf) p->choose_flat_bwd();
         if (p->keep) {
             p->units.resize(n + 1);
@@ -952,7 +963,8 @@ int slos_plan_ex(int m, int n, const int32_t *input_state, int flags, const slos
         std::vector<uint8_t> modes;
         for (int k = 1; k <= n; ++k) {
             p->desc_off[k] = descs.size();
-            if (k <= p->flat_kf) continue;  // table-driven: no descriptors
+            // table-driven: no descriptors, unless the adjoint's seed needs them
+            if (k <= p->flat_kf && !(p->keep && k == n && p->bwd_kb < n)) continue;
             // narrow unless a leaf has more than 16 groups or a 64-bit delta
             int wide = p->opts.wide_descriptors > 0 ? 1 : 0;
             for (const LeafRec &L : p->leaves[k]) {
@@ -1157,6 +1169,18 @@ int slos_plan_ex(int m, int n, const int32_t *input_state, int flags, const slos
     }
     *out = p;
     return SLOS_OK;
+}
+
+int slos_plan_ex(int m, int n, const int32_t *input_state, int flags, const slos_options_t *opts,
+                 slos_plan_t *out)
+{
+    bool tables = true;
+    const int rc = make_plan(m, n, input_state, flags, opts, tables, out);
+    if (rc != SLOS_ERR_OOM || !tables) return rc;
+    // no room for the tables beside the layers: the tiled kernels need none
+    (void)hipGetLastError();
+    tables = false;
+    return make_plan(m, n, input_state, flags, opts, tables, out);
 }
 
 void slos_plan_destroy(slos_plan_t p)
@@ -2749,9 +2773,11 @@ static int upload_flat_batch(slos_batch_t b, std::vector<FlatTables> &tables, ui
 
 extern "C" {
 
-int slos_batch_plan(int count, const int32_t *ms, const int32_t *inputs, int flags, const slos_options_t *opts,
-                    slos_batch_t *out)
+static int make_batch(int count, const int32_t *ms, const int32_t *inputs, int flags, const slos_options_t *opts,
+                      bool &tables, slos_batch_t *out)
 {
+    const bool allowed = tables;
+    tables = false;
     if (!out) return fail(SLOS_ERR_INVALID_ARG, "out is NULL");
     *out = nullptr;
     if (count < 1 || !ms || !inputs) return fail(SLOS_ERR_INVALID_ARG, "need count >= 1, ms and inputs");
@@ -2806,7 +2832,8 @@ int slos_batch_plan(int count, const int32_t *ms, const int32_t *inputs, int fla
         P.opts = o;
         if (o.low_block_max > 0) P.low_cap = (uint64_t)o.low_block_max;  // default: no cap
         P.B.build(maxm + maxn, maxn);
-        b->flat = !tiled && plan_flat_batch(*b, ms, inputs, flat_tables, flat_entries, flat_scales);
+        b->flat = allowed && !tiled && plan_flat_batch(*b, ms, inputs, flat_tables, flat_entries, flat_scales);
+        tables = b->flat;
     } catch (std::bad_alloc &) {
         delete b;
         return fail(SLOS_ERR_OOM, "host allocation failed while building the batch");
@@ -2971,6 +2998,17 @@ int slos_batch_plan(int count, const int32_t *ms, const int32_t *inputs, int fla
     return SLOS_OK;
 }
 
+int slos_batch_plan(int count, const int32_t *ms, const int32_t *inputs, int flags, const slos_options_t *opts,
+                    slos_batch_t *out)
+{
+    bool tables = true;
+    const int rc = make_batch(count, ms, inputs, flags, opts, tables, out);
+    if (rc != SLOS_ERR_OOM || !tables) return rc;
+    (void)hipGetLastError();  // no room for the tables: as in slos_plan_ex
+    tables = false;
+    return make_batch(count, ms, inputs, flags, opts, tables, out);
+}
+
 void slos_batch_destroy(slos_batch_t b)
 {
     if (!b) return;
@@ -3116,9 +3154,11 @@ struct slos_source_s {
 
 extern "C" {
 
-int slos_source_plan(int m, const int32_t *input_state, const slos_source_params_t *src, int nmax,
-                     const slos_options_t *opts, slos_source_t *out)
+static int make_source(int m, const int32_t *input_state, const slos_source_params_t *src, int nmax,
+                       const slos_options_t *opts, bool &with_tables, slos_source_t *out)
 {
+    const bool allowed = with_tables;
+    with_tables = false;
     if (!out) return fail(SLOS_ERR_INVALID_ARG, "out is NULL");
     *out = nullptr;
     if (m < 1 || m > SLOS_MAX_MODES) return fail(SLOS_ERR_INVALID_ARG, "m = %d outside [1, %d]", m, SLOS_MAX_MODES);
@@ -3185,7 +3225,7 @@ int slos_source_plan(int m, const int32_t *input_state, const slos_source_params
         // the table sizes that the other table-driven paths take; an explicit leaf
         // size asks for leaves.  With tables, leaves serve the groups' normalisation
         // alone, which has at most n photons.
-        if (n > 0 && nmax > 0 && !(opts && opts->leaf_max > 0) && s->off[nmax + 1] - s->off[nmax] <= SLOS_FLAT_MAX_STATES) {
+        if (allowed && n > 0 && nmax > 0 && !(opts && opts->leaf_max > 0) && s->off[nmax + 1] - s->off[nmax] <= SLOS_FLAT_MAX_STATES) {
             tables.m = m;
             tables.bstride = P.B.stride;
             tables.norm_t = 1.0;
@@ -3197,6 +3237,7 @@ int slos_source_plan(int m, const int32_t *input_state, const slos_source_params
                 if (k > 0) entries += (uint64_t)tables.N[k] * std::min(m, k);
             }
             if (entries <= SLOS_FB_MAX_ENTRIES) tables.kf = nmax;
+            with_tables = tables.kf > 0;
         }
         const int kleaf = tables.kf > 0 ? std::min((int)n, nmax) : nmax;
         std::vector<uint64_t> deltas;
@@ -3311,6 +3352,17 @@ int slos_source_plan(int m, const int32_t *input_state, const slos_source_params
     }
     *out = s;
     return SLOS_OK;
+}
+
+int slos_source_plan(int m, const int32_t *input_state, const slos_source_params_t *src, int nmax,
+                     const slos_options_t *opts, slos_source_t *out)
+{
+    bool tables = true;
+    const int rc = make_source(m, input_state, src, nmax, opts, tables, out);
+    if (rc != SLOS_ERR_OOM || !tables) return rc;
+    (void)hipGetLastError();  // no room for the tables: as in slos_plan_ex
+    tables = false;
+    return make_source(m, input_state, src, nmax, opts, tables, out);
 }
 
 void slos_source_destroy(slos_source_t s)

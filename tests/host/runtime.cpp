@@ -13,9 +13,11 @@
 // the launchers that these checks look at, in place of those that report a failure
 #define slos_launch_select no_launch_select
 #define slos_launch_layer no_launch_layer
+#define slos_prepare_batch_kernels no_prepare_batch_kernels
 #include "stubs.cpp"
 #undef slos_launch_select
 #undef slos_launch_layer
+#undef slos_prepare_batch_kernels
 
 FakeRuntime fake;
 static std::map<void *, size_t> blocks;
@@ -27,6 +29,7 @@ int slos_launch_select(const SelectParams &p, int, void *)
     return 0;
 }
 int slos_launch_layer(const LayerParams &, const LayerLaunch &, void *) { return 0; }
+int slos_prepare_batch_kernels() { return 0; }
 
 extern "C" {
 
@@ -82,6 +85,7 @@ hipError_t hipMemset(void *d, int v, size_t n)
     memset(d, v, n);
     return hipSuccess;
 }
+hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipGetDeviceCount(int *n)
 {
     *n = 1;

@@ -139,11 +139,87 @@ static void select_parts()
         }
 }
 
+// device memory that `make` takes, which returns what undoes it
+template <typename F> static size_t memory_of(F &&make)
+{
+    fake.used = fake.peak = 0;
+    auto undo = make();
+    const size_t used = fake.peak;
+    undo();
+    CHECK(fake.used == 0, "%zu bytes not given back", fake.used);
+    return used;
+}
+
+// Plans, batches and sources are made in the memory that they take without tables,
+// and a plan's tables stay within their limits.
+static void table_memory()
+{
+    slos_options_t tiled{};
+    auto plan = [&](int m, int n, int flags, bool tables) {
+        return [=] {
+            std::vector<int32_t> T(m, 0);
+            for (int i = 0; i < n; ++i) ++T[i % m];
+            slos_options_t o{};
+            // the default sizes, named: the same kernels and buffers without tables
+            o.leaf_max = flags & SLOS_KEEP_LAYERS ? 4096 : flags & SLOS_C64 ? 16384 : 8192;
+            slos_plan_t p = nullptr;
+            CHECK(slos_plan_ex(m, n, T.data(), flags, tables ? nullptr : &o, &p) == SLOS_OK, "plan m=%d n=%d flags=%x", m,
+                  n, flags);
+            return [p] { slos_plan_destroy(p); };
+        };
+    };
+    const struct { int m, n, flags; } plans[] = {{6, 3, SLOS_C128},
+                                                 {12, 6, SLOS_C64 | SLOS_KEEP_LAYERS},
+                                                 {17, 8, SLOS_C64 | SLOS_COMPENSATED},
+                                                 {16, 8, SLOS_C128 | SLOS_KEEP_LAYERS},
+                                                 {92, 5, SLOS_C64 | SLOS_KEEP_LAYERS}};
+    for (const auto &z : plans) {
+        const size_t without = memory_of(plan(z.m, z.n, z.flags, false)), with = memory_of(plan(z.m, z.n, z.flags, true));
+        CHECK(with <= without + (size_t(922) << 20) + 8 * (size_t)3200000, "m=%d n=%d flags=%x: %zu bytes beside %zu", z.m,
+              z.n, z.flags, with - without, without);
+        fake.budget = without;
+        memory_of(plan(z.m, z.n, z.flags, true));
+        fake.budget = ~size_t(0);
+    }
+    tiled.leaf_max = 1024;
+    auto batch = [&](bool tables) {
+        return [=] {
+            std::vector<int32_t> ms, in;
+            for (int m = 6; m < 15; ++m) {
+                ms.push_back(m);
+                for (int j = 0; j < m; ++j) in.push_back(j < 6);
+            }
+            slos_batch_t b = nullptr;
+            CHECK(slos_batch_plan((int)ms.size(), ms.data(), in.data(), SLOS_C64, tables ? nullptr : &tiled, &b) == SLOS_OK,
+                  "batch");
+            return [b] { slos_batch_destroy(b); };
+        };
+    };
+    fake.budget = memory_of(batch(false));
+    memory_of(batch(true));
+    fake.budget = ~size_t(0);
+    tiled.leaf_max = 256;
+    auto source = [&](bool tables) {
+        return [=] {
+            std::vector<int32_t> T(12, 0);
+            for (int j = 0; j < 6; ++j) T[j] = 1;
+            const slos_source_params_t sp{0.9, 0.05, 0.92};
+            slos_source_t s = nullptr;
+            CHECK(slos_source_plan(12, T.data(), &sp, -1, tables ? nullptr : &tiled, &s) == SLOS_OK, "source");
+            return [s] { slos_source_destroy(s); };
+        };
+    };
+    fake.budget = memory_of(source(false));
+    memory_of(source(true));
+    fake.budget = ~size_t(0);
+}
+
 int main(int argc, char **argv)
 {
     const char *what = argc > 1 ? argv[1] : "";
     if (!std::strcmp(what, "select-threads")) select_without_threads();
     else if (!std::strcmp(what, "select-parts")) select_parts();
+    else if (!std::strcmp(what, "table-memory")) table_memory();
     else {
         std::printf("no check named '%s'\n", what);
         return 2;
