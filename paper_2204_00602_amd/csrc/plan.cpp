@@ -213,7 +213,7 @@ struct slos_plan_s {
     uint64_t buf_stride[2] = {0, 0};  // elements per instance in d_buf[b]
     uint64_t g_stride = 0;            // elements per instance in d_g[b]
     uint64_t bpart_stride = 0;        // double2 per instance in d_bpart
-    uint32_t *d_tickets = nullptr;    // SLOS_XCDS ticket counters per layer, then the first launch's maxima
+    uint32_t *d_tickets = nullptr;    // SLOS_XCDS ticket counters per layer (run_forward: and the first launch's maxima)
     // table-driven layers (flat.hip): 1..flat_kf, of which 1..flat_h + 1 are the
     // first launch; 0 when a tiling option asks for the tiled kernels throughout
     int flat_kf = 0, flat_h = 0;
@@ -286,12 +286,8 @@ struct slos_plan_s {
     hipGraphExec_t graph = nullptr;   // slos_plan_capture
 
     size_t elem() const { return c64 ? 8 : 16; }
-    // words of the ticket area of one instance: a line per layer and XCD, the
-    // first launch's maxima, and its count of ended workgroups
-    uint64_t ticket_words() const
-    {
-        return (uint64_t)(n + 1) * SLOS_XCDS * SLOS_TICKET_STRIDE + SLOS_HEAD_MAX_GROUPS + SLOS_TICKET_STRIDE;
-    }
+    // words of the ticket area of one instance: a line per layer and XCD
+    uint64_t ticket_words() const { return (uint64_t)(n + 1) * SLOS_XCDS * SLOS_TICKET_STRIDE; }
     // states per leaf of layer k: small layers get smaller leaves so that they
     // still spread over about SLOS_TARGET_LEAVES workgroups
     uint64_t leaf_cap(int k) const
@@ -1077,9 +1073,12 @@ static int make_plan(int m, int n, const int32_t *input_state, int flags, const 
             }
     }
     p->n_partials = n > 0 ? (int64_t)p->leaves[n].size() * (p->opts.block_threads / 64) : 1;
-    if (p->last_flat())
-        p->n_partials = std::max<int64_t>(SLOS_HEAD_MAX_GROUPS,
-                                          (int64_t)((p->Nk[n] + SLOS_FLAT_THREADS - 1) / SLOS_FLAT_THREADS));
+    if (p->last_flat()) {
+        // one per workgroup of the last layer's launch (a call on fewer unitaries has the most)
+        int threads = 0, groups = 0;
+        p->head_shape(1, threads, groups);
+        p->n_partials = p->flat_h + 1 == n ? groups : (int64_t)((p->Nk[n] + SLOS_FLAT_THREADS - 1) / SLOS_FLAT_THREADS);
+    }
     if ((rc = alloc_dev((void **)&p->d_partials,
                         (size_t)(p->n_partials + SLOS_REDUCE_STAGE) * p->batch_cap * sizeof(double), "partial sums")) ||
         (rc = alloc_dev((void **)&p->d_tickets,
@@ -1307,10 +1306,13 @@ static int run_forward(slos_plan_t p, int batch, const void *U, void *out, doubl
         return sc.tickets + (uint64_t)k * tline + (k <= p->flat_kf ? 0 : SLOS_VMAX_SLOT);
     };
     auto needs_vmax = [&](int k) { return biased && k < n && k + 1 >= p->opts.comp_from_layer; };
-    uint32_t *head_vm = sc.tickets + (uint64_t)(n + 1) * tline;
-    // the first launch's count of ended workgroups is zero between passes (not
-    // in the static scratch, which other plans write over)
-    uint32_t *head_count = over ? nullptr : head_vm + SLOS_HEAD_MAX_GROUPS;
+    // The first launch's maxima and its count of ended workgroups are where layers 0
+    // and 1 would have their counters, which nothing else uses in a plan with that
+    // launch.  The count is zero between passes (not in the static scratch, which
+    // other plans write over).
+    static_assert(SLOS_HEAD_MAX_GROUPS <= SLOS_XCDS * SLOS_TICKET_STRIDE, "the maxima fit the counters of a layer");
+    uint32_t *head_vm = sc.tickets;
+    uint32_t *head_count = over ? nullptr : sc.tickets + tline;
     int64_t n_part = p->n_partials;  // partials of sum P per instance that this pass writes (0: the sum itself)
     int head_grid = 0;
     if (!p->flat_kf) {

@@ -214,12 +214,48 @@ static void table_memory()
     fake.budget = ~size_t(0);
 }
 
+// slos_amplitudes_noalloc takes every plan that its static area holds without tables
+// (the call then ends at the stand-in's missing area), and the tables' plan needs no more
+// partial sums per instance.
+static void noalloc_area()
+{
+    const struct { int m, n; } sizes[] = {{6, 3}, {12, 6}, {17, 8}, {20, 6}, {255, 3}, {40, 4}, {8, 20}, {3, 32}, {2, 1}};
+    int held = 0;
+    for (const auto &z : sizes)
+        for (int flags : {SLOS_C64, SLOS_C128})
+            for (int batch : {1, 64, 2048, 8192}) {
+                std::vector<int32_t> T(z.m, 0);
+                for (int i = 0; i < z.n; ++i) ++T[i % z.m];
+                int64_t M = 0;
+                slos_fock_count(z.m, z.n, &M);
+                if (M * batch > 40000000) continue;  // more layers than the stand-in's memory
+                int rc[2] = {};
+                for (int tables : {0, 1}) {
+                    slos_options_t o{};
+                    o.max_batch = batch;
+                    if (!tables) o.leaf_max = flags == SLOS_C64 ? 16384 : 8192;
+                    slos_plan_t p = nullptr;
+                    fake.used = fake.peak = 0;
+                    CHECK(slos_plan_ex(z.m, z.n, T.data(), flags, &o, &p) == SLOS_OK, "plan m=%d n=%d", z.m, z.n);
+                    if (!p) return;
+                    float u[2], out[2];
+                    rc[tables] = slos_amplitudes_noalloc(p, u, out, nullptr, nullptr);
+                    slos_plan_destroy(p);
+                }
+                held += rc[0] != SLOS_ERR_SIZE_OVERFLOW;
+                CHECK(rc[1] != SLOS_ERR_SIZE_OVERFLOW || rc[0] == SLOS_ERR_SIZE_OVERFLOW, "m=%d n=%d flags=%x max_batch=%d",
+                      z.m, z.n, flags, batch);
+            }
+    CHECK(held > 10, "only %d plans fit the area", held);
+}
+
 int main(int argc, char **argv)
 {
     const char *what = argc > 1 ? argv[1] : "";
     if (!std::strcmp(what, "select-threads")) select_without_threads();
     else if (!std::strcmp(what, "select-parts")) select_parts();
     else if (!std::strcmp(what, "table-memory")) table_memory();
+    else if (!std::strcmp(what, "noalloc-area")) noalloc_area();
     else {
         std::printf("no check named '%s'\n", what);
         return 2;

@@ -34,6 +34,7 @@ def checks(tmp_path_factory):
     "select-threads",  # a call whose helper threads cannot be started, after calls that had some
     "select-parts",    # every multiset of occupations beside a small one
     "table-memory",    # plans, batches and sources in the memory they take without tables
+    "noalloc-area",    # plans that slos_amplitudes_noalloc takes without tables
 ])
 def test_host_runtime(checks, name):
     res = subprocess.run([checks, name], capture_output=True, text=True, timeout=600)
