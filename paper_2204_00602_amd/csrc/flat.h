@@ -183,7 +183,19 @@ int slos_launch_flat_batch(const FlatBatchParams &p, int c64, int grid, void *st
 // us, and a launch of their own at least 5 with a seed or loss launch before it.
 #define SLOS_BWD_TAIL_TERMS 60000u
 #define SLOS_BWD_THREADS 512     // of a reverse layer
+// Threads of a tail workgroup.  With more instances than compute units
+// (SLOS_BWD_TAIL_MANY) small ones leave most of 1024 threads idle while no second
+// workgroup fits beside them (128 registers a thread), so those whose LDS lets four
+// workgroups share a unit get 256 threads, and those whose layers below the last
+// have at most 64 states 64.  Microseconds of slos_backward_many in c64 with 1024, 256 and
+// 64 threads, and of the unit kernels: m=6, n=3, 4096 instances 109, 34, 14 and
+// 66, 65,535 of them 1780, 487, 166 and 756; m=3, n=2, 65,535: 1264, 349, 108
+// and 311; m=10, n=5, 4096: 261, 102 and 332 (256 the most that fits).  One
+// instance: m=10, n=5 16.9 with 1024, 17.6 with 256; m=64, n=2 21.5 and 24.9.
 #define SLOS_BWD_TAIL_THREADS 1024
+#define SLOS_BWD_TAIL_MANY 256
+#define SLOS_BWD_TAIL_LDS_256 (40u * 1024u)
+#define SLOS_BWD_TAIL_LDS_64 (10u * 1024u)
 // Modes whose gradient sums a thread of the tail keeps in registers.
 #define SLOS_BWD_TAIL_MODES 12
 
@@ -226,6 +238,7 @@ struct TailParams {
     uint32_t N[SLOS_MAX_PHOTONS + 1];
     uint32_t cap[2];             // elements of the even and the odd LDS buffer (a zero follows each layer)
     int m, n, t;
+    int threads;                 // of a workgroup: SLOS_BWD_TAIL_THREADS, 256 or 64 (t = n)
     int wave_rows;               // sum of slos_tail_waves over its layers
     uint8_t col[SLOS_MAX_PHOTONS + 1];
 };
@@ -243,15 +256,15 @@ static inline uint32_t slos_bwd_rows(uint64_t N, int per_thread)
     return (uint32_t)((N + (uint64_t)per_thread * SLOS_BWD_THREADS - 1) / ((uint64_t)per_thread * SLOS_BWD_THREADS));
 }
 // the g buffers hold four layers' partial sums per thread at the end
-static inline uint64_t slos_tail_lds(uint64_t cap0, uint64_t cap1, int m, int n, int t, int wave_rows, uint64_t es)
+static inline uint64_t slos_tail_lds(uint64_t cap0, uint64_t cap1, int m, int n, int t, int wave_rows, int threads, uint64_t es)
 {
-    const uint64_t g = (cap0 + cap1) * es, red = t < n ? 4u * (uint64_t)SLOS_BWD_TAIL_THREADS * 16u : 0u;
+    const uint64_t g = (cap0 + cap1) * es, red = t < n ? 4u * (uint64_t)threads * 16u : 0u;
     return (g > red ? g : red) + 16u * ((uint64_t)t * (m + 16) + (uint64_t)(n + 1 + wave_rows) * m);
 }
-// waves of the tail that have a state of a layer of N states: four lanes a
-// state up to SLOS_BWD_TAIL_THREADS states, else one
-SLOS_HD static inline int slos_tail_waves(uint32_t N)
+// waves of the tail (of `threads` threads) that have a state of a layer of N states: four
+// lanes a state up to as many states as threads, else one
+SLOS_HD static inline int slos_tail_waves(uint32_t N, uint32_t threads)
 {
-    const uint32_t w = N <= SLOS_BWD_TAIL_THREADS ? (N + 15u) / 16u : SLOS_BWD_TAIL_THREADS / 64u;
-    return (int)(w < SLOS_BWD_TAIL_THREADS / 64u ? w : SLOS_BWD_TAIL_THREADS / 64u);
+    const uint32_t w = N <= threads ? (N + 15u) / 16u : threads / 64u;
+    return (int)(w < threads / 64u ? w : threads / 64u);
 }

@@ -215,12 +215,13 @@ template <int NM> struct Modes {
 // another turn over the states.  The wave reductions come once per layer (and
 // turn); the waves' sums stay apart in LDS and are added at the end, all layers
 // together.  A layer's first loads (A and successor ranks, which depend on
-// nothing computed here) are issued before the barrier that precedes it.
-template <typename T>
-__global__ __launch_bounds__(SLOS_BWD_TAIL_THREADS) void tail_kernel(TailParams p)
+// nothing computed here) are issued before the barrier that precedes it.  TH = 64
+// only for t = n: the partials of layers above t are added by groups of m threads.
+template <typename T, int TH>
+__global__ __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(4))) void tail_kernel(TailParams p)
 {
     using C = typename Cx<T>::type;
-    constexpr int TH = SLOS_BWD_TAIL_THREADS, GM = SLOS_BWD_TAIL_MODES;
+    constexpr int GM = SLOS_BWD_TAIL_MODES;
     extern __shared__ __align__(16) unsigned char dyn[];
     __shared__ double sh[256];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -279,9 +280,9 @@ __global__ __launch_bounds__(SLOS_BWD_TAIL_THREADS) void tail_kernel(TailParams 
         const double *pt = p.p_target + b * (uint64_t)p.count;
         for (uint32_t s = tid; s <= Nt; s += TH) top[s] = C{0, 0};
         __syncthreads();
-        double s = 0.0;
-        if (tid < 256) {
-            for (int64_t i = tid; i < p.count; i += 256) {
+        for (int q = tid; q < 256; q += TH) {
+            double s = 0.0;
+            for (int64_t i = q; i < p.count; i += 256) {
                 const int64_t r = p.ranks[i];
                 if (r < 0 || (uint64_t)r >= Nt) continue;  // outside the output set: ignored
                 const C v = a[r];
@@ -293,11 +294,11 @@ __global__ __launch_bounds__(SLOS_BWD_TAIL_THREADS) void tail_kernel(TailParams 
                 const double c = p.target_scale[i];
                 top[r] = C{(T)(c * (double)ga.x), (T)(c * (double)ga.y)};
             }
-            sh[tid] = s;
+            sh[q] = s;
         }
         __syncthreads();
         for (int w = 128; w > 0; w >>= 1) {
-            if (tid < w) sh[tid] += sh[tid + w];
+            for (int q = tid; q < w; q += TH) sh[q] += sh[q + w];
             __syncthreads();
         }
         if (tid == 0 && p.loss) p.loss[b] = sh[0];
@@ -321,7 +322,7 @@ __global__ __launch_bounds__(SLOS_BWD_TAIL_THREADS) void tail_kernel(TailParams 
         C *gd = k & 1 ? buf0 : buf1;
         const uint32_t N = p.N[k - 1];
         const double2 *uk = u + (k - 1) * ms;
-        const int busy = slos_tail_waves(N);
+        const int busy = slos_tail_waves(N, TH);
         if (tid == 0) gd[N] = C{0, 0};
         if (small(k)) {
             // Four lanes a state, lane q of them modes q, q + 4, ..: the chain of
@@ -399,8 +400,8 @@ __global__ __launch_bounds__(SLOS_BWD_TAIL_THREADS) void tail_kernel(TailParams 
     for (int i = tid; i < t * m; i += TH) {
         const int k = t - i / m, j = i % m;
         int row = 0;
-        for (int q = t; q > k; --q) row += slos_tail_waves(p.N[q - 1]);
-        const int end = row + slos_tail_waves(p.N[k - 1]);
+        for (int q = t; q > k; --q) row += slos_tail_waves(p.N[q - 1], TH);
+        const int end = row + slos_tail_waves(p.N[k - 1], TH);
         double2 v{0.0, 0.0};
         for (; row < end; ++row) {
             v.x += wpart[row * m + j].x;
@@ -473,21 +474,31 @@ void launch_layer(const FlatBwdParams &p, int batch, hipStream_t s)
     else hipLaunchKernelGGL((bwd_flat_kernel<T, PT, false>), g, dim3(SLOS_BWD_THREADS), lds, s, p);
 }
 
+template <typename T, int TH>
+hipError_t launch_tail(const TailParams &p, int batch, hipStream_t s)
+{
+    static bool attr_set = false;  // per instantiation; first call per process
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void *)tail_kernel<T, TH>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)SLOS_LDS_DYNAMIC_MAX);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    const size_t lds =
+        (size_t)slos_tail_lds(p.cap[0], p.cap[1], p.m, p.n, p.t, p.wave_rows, TH, sizeof(typename Cx<T>::type));
+    hipLaunchKernelGGL((tail_kernel<T, TH>), dim3(batch), dim3(TH), lds, s, p);
+    return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch(const FlatBwdLaunch &l, int batch, hipStream_t s)
 {
     if (l.tail) {
-        static bool attr_set = false;  // per instantiation; first call per process
-        if (!attr_set) {
-            hipError_t e = hipFuncSetAttribute((const void *)tail_kernel<T>,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)SLOS_LDS_DYNAMIC_MAX);
-            if (e != hipSuccess) return e;
-            attr_set = true;
+        switch (l.tail->threads) {
+        case 64: return launch_tail<T, 64>(*l.tail, batch, s);
+        case 256: return launch_tail<T, 256>(*l.tail, batch, s);
+        default: return launch_tail<T, SLOS_BWD_TAIL_THREADS>(*l.tail, batch, s);
         }
-        const TailParams &p = *l.tail;
-        const size_t lds = (size_t)slos_tail_lds(p.cap[0], p.cap[1], p.m, p.n, p.t, p.wave_rows, sizeof(typename Cx<T>::type));
-        hipLaunchKernelGGL(tail_kernel<T>, dim3(batch), dim3(SLOS_BWD_TAIL_THREADS), lds, s, p);
-        return hipGetLastError();
     }
     if (l.per_thread == 1) launch_layer<T, 1>(*l.layer, batch, s);
     else if (l.per_thread == 2) launch_layer<T, 2>(*l.layer, batch, s);

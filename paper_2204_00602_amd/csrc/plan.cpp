@@ -218,6 +218,7 @@ struct slos_plan_s {
     // first launch; 0 when a tiling option asks for the tiled kernels throughout
     int flat_kf = 0, flat_h = 0;
     int bwd_kb = 0, bwd_t = 0;        // table-driven reverse layers 1..bwd_kb, of which 1..bwd_t are the tail launch
+    int bwd_threads = 0;              // of a workgroup of the tail
     std::vector<uint64_t> bwd_succ_off;  // per layer: first entry of its successor table
     std::vector<int> bwd_pt;          // per layer: states per thread
     uint32_t *d_bwd_succ = nullptr;   // successor tables of the table-driven reverse layers
@@ -524,6 +525,19 @@ struct slos_plan_s {
             ++flat_h;
     }
 
+    // waves' sums and LDS bytes of a tail launch of layers t..1
+    int tail_rows(int t, int threads) const
+    {
+        int rows = 0;
+        for (int k = 1; k <= t; ++k) rows += slos_tail_waves((uint32_t)Nk[k - 1], (uint32_t)threads);
+        return rows;
+    }
+    uint64_t tail_lds(int t, int threads) const
+    {
+        return slos_tail_lds(Nk[t & 1 ? t - 1 : t] + 1, Nk[t & 1 ? t : t - 1] + 1, m, n, t, tail_rows(t, threads), threads,
+                             elem());
+    }
+
     // Reverse layers from tables: those whose layer k - 1 has a table-driven
     // size, up to the limit of all successor tables (4 m bytes a state: plans of 48
     // modes and more meet it, at a layer below the last); of these the tail takes
@@ -536,16 +550,19 @@ struct slos_plan_s {
             if (entries > SLOS_FLAT_MAX_SUCC) break;
             ++bwd_kb;
         }
-        int rows = 0;
         while (bwd_t < bwd_kb) {
             const int k = bwd_t + 1;
-            const uint64_t cap[2] = {Nk[k & 1 ? k - 1 : k] + 1, Nk[k & 1 ? k : k - 1] + 1};
-            rows += slos_tail_waves((uint32_t)Nk[k - 1]);
-            if (slos_tail_lds(cap[0], cap[1], m, n, k, rows, elem()) > SLOS_BWD_LDS_MAX) break;
+            const uint64_t need = tail_lds(k, SLOS_BWD_TAIL_THREADS);
+            if (need > SLOS_BWD_LDS_MAX) break;
             if (k > 1 && Nk[k - 1] * (uint64_t)m > SLOS_BWD_TAIL_TERMS) break;
             bwd_t = k;
         }
         if (bwd_t == 0) bwd_kb = 0;
+        bwd_threads = SLOS_BWD_TAIL_THREADS;
+        if (batch_cap > SLOS_BWD_TAIL_MANY && bwd_t > 0) {
+            if (tail_lds(bwd_t, 256) <= SLOS_BWD_TAIL_LDS_256) bwd_threads = 256;
+            if (bwd_t == n && Nk[n - 1] <= 64 && tail_lds(bwd_t, 64) <= SLOS_BWD_TAIL_LDS_64) bwd_threads = 64;
+        }
         bwd_pt.assign(n + 1, 1);
         for (int k = bwd_t + 1; k <= bwd_kb; ++k) {
             const uint64_t groups = (Nk[k - 1] * (uint64_t)batch_cap + 255) / 256;
@@ -1592,7 +1609,8 @@ static int run_reverse_flat(slos_plan_t p, int batch, const void *U, void *grad_
     tp.m = m;
     tp.n = n;
     tp.t = t;
-    for (int k = 1; k <= t; ++k) tp.wave_rows += slos_tail_waves((uint32_t)p->Nk[k - 1]);
+    tp.threads = p->bwd_threads;
+    tp.wave_rows = p->tail_rows(t, tp.threads);
     for (int k = 1; k <= n; ++k) {
         tp.col[k] = (uint8_t)p->photons[k - 1];
         tp.keep_off[k - 1] = p->keep_off[k - 1] * es;
