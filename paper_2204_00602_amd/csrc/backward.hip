@@ -15,6 +15,8 @@
 // order.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "flat.h"
 #include "slos_internal.h"
 
@@ -327,24 +329,23 @@ __device__ __forceinline__ Cd cexp_i(double a)
 // far as LDS reaches: whole blocks, else the phase factors e^{i phi}, else
 // nothing (sincos on the sweep's chain).
 enum MeshStage { kMeshNone = 0, kMeshFactors = 1, kMeshBlocks = 2 };
-struct MeshBlocks {
+template <int STAGE> struct MeshBlocks {
     const double *ph;
     Cd *lds;
-    int stage;
     __device__ void prepare(int nmzi, int tid, int nt)
     {
-        if (stage == kMeshBlocks) {
+        if constexpr (STAGE == kMeshBlocks) {
             for (int k = tid; k < nmzi; k += nt)
                 ((MziBlock *)lds)[k] = mzi_block(cexp_i(ph[2 * k]), cexp_i(ph[2 * k + 1]));
-        } else if (stage == kMeshFactors) {
+        } else if constexpr (STAGE == kMeshFactors) {
             for (int i = tid; i < 2 * nmzi; i += nt) lds[i] = cexp_i(ph[i]);
         }
     }
     __device__ __forceinline__ MziBlock block(int k) const
     {
-        if (stage == kMeshBlocks) return ((const MziBlock *)lds)[k];
-        if (stage == kMeshFactors) return mzi_block(lds[2 * k], lds[2 * k + 1]);
-        return mzi_block(cexp_i(ph[2 * k]), cexp_i(ph[2 * k + 1]));
+        if constexpr (STAGE == kMeshBlocks) return ((const MziBlock *)lds)[k];
+        else if constexpr (STAGE == kMeshFactors) return mzi_block(lds[2 * k], lds[2 * k + 1]);
+        else return mzi_block(cexp_i(ph[2 * k]), cexp_i(ph[2 * k + 1]));
     }
 };
 
@@ -388,32 +389,37 @@ __device__ __forceinline__ void mesh_apply(Cd *X, const MziBlock &B, int p0, int
     }
 }
 
-// The whole mesh on this wave's columns of X; each step's block is read while
-// the one before still computes.
-__device__ __forceinline__ void mesh_forward_sweep(Cd *X, const MeshBlocks &mb, int m, int nmzi, int i, int cw, int nc,
-                                                   int g, int gc)
+// The whole mesh on this wave's columns of X.  A prepared block is read while the
+// step before still computes; one that is formed here is formed in its own step.
+template <int STAGE>
+__device__ __forceinline__ void mesh_forward_sweep(Cd *X, const MeshBlocks<STAGE> &mb, int m, int nmzi, int i, int cw,
+                                                   int nc, int g, int gc)
 {
     int k0 = 0;
-    MziBlock B = mb.block(min(i, nmzi - 1));
+    MziBlock B;
+    if constexpr (STAGE == kMeshBlocks) B = mb.block(min(i, nmzi - 1));
     for (int col = 0; col < m; ++col) {
         const int cnt = (m - col % 2) / 2;
-        const MziBlock nb = mb.block(min(k0 + cnt + i, nmzi - 1));
-        if (i < cnt) mesh_apply(X, B, col % 2 + 2 * i, cw, nc, g, gc);
+        MziBlock nb;
+        if constexpr (STAGE == kMeshBlocks) nb = mb.block(min(k0 + cnt + i, nmzi - 1));
+        if (i < cnt) {
+            if constexpr (STAGE != kMeshBlocks) B = mb.block(k0 + i);
+            mesh_apply(X, B, col % 2 + 2 * i, cw, nc, g, gc);
+        }
         k0 += cnt;
-        B = nb;
+        if constexpr (STAGE == kMeshBlocks) B = nb;
         wave_step();
     }
 }
 
-template <typename T>
+template <typename T, int STAGE>
 __global__ __launch_bounds__(1024) void mesh_forward_kernel(int m, int nmzi, const double *__restrict__ phases,
-                                                            typename Cb<T>::type *__restrict__ Uout, int stage,
-                                                            MeshLanes ml)
+                                                            typename Cb<T>::type *__restrict__ Uout, MeshLanes ml)
 {
     using C = typename Cb<T>::type;
     extern __shared__ Cd Ush[];  // per wave m x cw, then the prepared blocks
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    MeshBlocks mb{phases + (size_t)b * 2 * nmzi, Ush + ml.waves * m * ml.cw, stage};
+    MeshBlocks<STAGE> mb{phases + (size_t)b * 2 * nmzi, Ush + ml.waves * m * ml.cw};
     mb.prepare(nmzi, tid, blockDim.x);
     const int gc = ml.gc, cw = ml.cw, i = lane / gc, g = lane % gc;
     const int c0 = wv * cw, nc = min(cw, m - c0);  // this wave's matrix columns (none if nc <= 0)
@@ -440,17 +446,17 @@ __global__ __launch_bounds__(1024) void mesh_forward_kernel(int m, int nmzi, con
 // m=12, 64 phase sets: bound by the chain of 2 m steps of LDS reads, complex
 // products and LDS writes; with one wave on all matrix columns, a barrier per
 // step, and the 2x2 derivative products formed in full it took 20 us.
-template <typename T>
+template <typename T, int STAGE>
 __global__ __launch_bounds__(1024) void mesh_backward_kernel(int m, int nmzi, const double *__restrict__ phases,
                                                              const typename Cb<T>::type *__restrict__ GU,
-                                                             double *__restrict__ gphases, int stage, MeshLanes ml, int lane_sums)
+                                                             double *__restrict__ gphases, MeshLanes ml, int lane_sums)
 {
     extern __shared__ Cd sh[];  // per wave P and Q (m x cw each), the prepared blocks, the waves' sums
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int gc = ml.gc, cw = ml.cw, W = ml.waves, i = lane / gc, g = lane % gc;
     Cd *blocks = sh + 2 * W * m * cw;
-    MeshBlocks mb{phases + (size_t)b * 2 * nmzi, blocks, stage};
-    double *part = (double *)(blocks + (stage == kMeshBlocks ? 5 * nmzi : stage == kMeshFactors ? 2 * nmzi : 0));
+    MeshBlocks<STAGE> mb{phases + (size_t)b * 2 * nmzi, blocks};
+    double *part = (double *)(blocks + (STAGE == kMeshBlocks ? 5 * nmzi : STAGE == kMeshFactors ? 2 * nmzi : 0));
     mb.prepare(nmzi, tid, blockDim.x);
     const int c0 = wv * cw, nc = min(cw, m - c0);
     Cd *P = sh + wv * 2 * m * cw, *Q = P + m * cw;
@@ -468,15 +474,18 @@ __global__ __launch_bounds__(1024) void mesh_backward_kernel(int m, int nmzi, co
     __syncthreads();
     mesh_forward_sweep(Q, mb, m, nmzi, i, cw, nc, g, gc);
     int k0 = nmzi;
-    MziBlock B = mb.block(min(nmzi - (m - (m - 1) % 2) / 2 + i, nmzi - 1));
+    MziBlock B;
+    if constexpr (STAGE == kMeshBlocks) B = mb.block(min(nmzi - (m - (m - 1) % 2) / 2 + i, nmzi - 1));
     double *out = gphases + (size_t)b * 2 * nmzi;
     // columns in reverse
     for (int col = m - 1; col >= 0; --col) {
         const int cnt = (m - col % 2) / 2;
         k0 -= cnt;
         double va = 0.0, vb = 0.0;
-        const MziBlock nb = mb.block(max(k0 - (m - (col + 1) % 2) / 2 + i, 0) % nmzi);
+        MziBlock nb;
+        if constexpr (STAGE == kMeshBlocks) nb = mb.block(max(k0 - (m - (col + 1) % 2) / 2 + i, 0) % nmzi);
         if (i < cnt) {
+            if constexpr (STAGE != kMeshBlocks) B = mb.block(k0 + i);
             const int p0 = col % 2 + 2 * i;
             const Cd eb = B.v[4], h0 = cconj(B.v[0]), h1 = cconj(B.v[1]), h2 = cconj(B.v[2]), h3 = cconj(B.v[3]);
             for (int c = g; c < nc; c += gc) {
@@ -509,7 +518,7 @@ __global__ __launch_bounds__(1024) void mesh_backward_kernel(int m, int nmzi, co
                 to[2 * (k0 + i) + 1] = vb;
             }
         }
-        B = nb;
+        if constexpr (STAGE == kMeshBlocks) B = nb;
         wave_step();
     }
     const int rows = lane_sums ? W * gc : W;
@@ -607,15 +616,25 @@ int slos_launch_sq_loss(const void *a, uint64_t M, const int64_t *ranks, int64_t
 // What the mesh kernels keep in LDS: the waves' matrices (mats of m x cw), the
 // blocks or factors prepared ahead, and the waves' sums; fewer waves, then less
 // prepared, where that does not fit.
+//
+// That is the shape for the shortest chain.  Many sets are bound by issue and by how
+// many of them LDS holds instead: they get factors alone, no term per lane, and few
+// waves (each with most of its lanes at work).  Forward from 1024 sets on (four to a
+// compute unit) and up to 40 modes (48: 445 us for 2048, 798 so); the adjoint where
+// the sets are more than LDS holds at a time and that is fewer than 16 to a unit.
+// 16,384 sets, us forward and adjoint in the shape for few and so: m=12 71 and 219, 52
+// and 162; m=16 100 and 426, 80 and 240; m=24 556 and 2032, 360 and 1177; m=32
+// 1128 and 3975, 951 and 2983.  m=8, whose adjoint LDS holds 20 times: 67, 76 so.
 struct MeshShape {
     MeshLanes ml;
     int stage;
     int lane_sums;
     size_t lds;
 };
-static MeshShape mesh_shape(int m, int nmzi, int mats, bool sums)
+static MeshShape mesh_shape(int m, int nmzi, int mats, bool sums, int batch)
 {
     MeshShape s{};
+    bool many = !sums && m <= 40 && batch >= 1024;
     if (sums) {
         // the mesh adjoint with a term per lane, all blocks prepared
         s.ml = mesh_lanes(m, 16);
@@ -624,14 +643,17 @@ static MeshShape mesh_shape(int m, int nmzi, int mats, bool sums)
         s.lane_sums = s.ml.waves * s.ml.gc > 1;
         s.lds = ((size_t)mats * s.ml.waves * m * s.ml.cw + 5 * (size_t)nmzi) * sizeof(Cd) +
                 (size_t)s.ml.waves * s.ml.gc * nmzi * 2 * sizeof(double);
-        if (s.lane_sums && s.lds <= SLOS_LDS_DYNAMIC_MAX) return s;
+        const size_t fit = SLOS_LDS_DYNAMIC_MAX / s.lds;
+        many = fit < 16 && (size_t)batch > 256 * fit;
+        if (s.lane_sums && fit > 0 && !many) return s;
         s.lane_sums = 0;
     }
-    for (int waves = 16; waves >= 1; waves /= 2) {
+    const int most = many ? m <= 18 ? 1 : m < 24 ? 2 : 4 : 16;
+    for (int waves = most; waves >= 1; waves /= 2) {
         s.ml = mesh_lanes(m, waves);
         const size_t mat = (size_t)mats * s.ml.waves * m * s.ml.cw * sizeof(Cd);
         const size_t part = sums && s.ml.waves > 1 ? (size_t)s.ml.waves * 2 * nmzi * sizeof(double) : 0;
-        for (s.stage = kMeshBlocks; s.stage >= kMeshNone; --s.stage) {
+        for (s.stage = many ? kMeshFactors : kMeshBlocks; s.stage >= kMeshNone; --s.stage) {
             const int per = s.stage == kMeshBlocks ? 5 : s.stage == kMeshFactors ? 2 : 0;
             s.lds = mat + part + (size_t)per * nmzi * sizeof(Cd);
             // sincos on the chain only where one wave's matrices leave no room
@@ -642,35 +664,54 @@ static MeshShape mesh_shape(int m, int nmzi, int mats, bool sums)
     return s;
 }
 
+template <typename T, int STAGE>
+static hipError_t mesh_forward(const MeshShape &sh, int m, int batch, const double *phases, void *U, hipStream_t s)
+{
+    static bool done = false;
+    hipError_t e = allow_lds(mesh_forward_kernel<T, STAGE>, done);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((mesh_forward_kernel<T, STAGE>), dim3(batch), dim3(64 * sh.ml.waves), sh.lds, s, m, m * (m - 1) / 2,
+                       phases, (typename Cb<T>::type *)U, sh.ml);
+    return hipGetLastError();
+}
+template <typename T, int STAGE>
+static hipError_t mesh_backward(const MeshShape &sh, int m, int batch, const double *phases, const void *GU, double *gphases,
+                                hipStream_t s)
+{
+    static bool done = false;
+    hipError_t e = allow_lds(mesh_backward_kernel<T, STAGE>, done);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((mesh_backward_kernel<T, STAGE>), dim3(batch), dim3(64 * sh.ml.waves), sh.lds, s, m, m * (m - 1) / 2,
+                       phases, (const typename Cb<T>::type *)GU, gphases, sh.ml, sh.lane_sums);
+    return hipGetLastError();
+}
+
+// f(STAGE as an integral constant)
+template <typename F> static hipError_t with_stage(int stage, F &&f)
+{
+    if (stage == kMeshBlocks) return f(std::integral_constant<int, kMeshBlocks>{});
+    if (stage == kMeshFactors) return f(std::integral_constant<int, kMeshFactors>{});
+    return f(std::integral_constant<int, kMeshNone>{});
+}
+
 int slos_launch_mesh_forward(int m, int batch, const double *phases, void *U, int c64, void *stream)
 {
-    const int nmzi = m * (m - 1) / 2;
-    const MeshShape sh = mesh_shape(m, nmzi, 1, false);
-    static bool a32 = false, a64 = false;
-    hipError_t e = c64 ? allow_lds(mesh_forward_kernel<float>, a32) : allow_lds(mesh_forward_kernel<double>, a64);
-    if (e != hipSuccess) return (int)e;
-    if (c64)
-        hipLaunchKernelGGL(mesh_forward_kernel<float>, dim3(batch), dim3(64 * sh.ml.waves), sh.lds, (hipStream_t)stream, m,
-                           nmzi, phases, (float2 *)U, sh.stage, sh.ml);
-    else
-        hipLaunchKernelGGL(mesh_forward_kernel<double>, dim3(batch), dim3(64 * sh.ml.waves), sh.lds, (hipStream_t)stream,
-                           m, nmzi, phases, (double2 *)U, sh.stage, sh.ml);
-    return (int)hipGetLastError();
+    const MeshShape sh = mesh_shape(m, m * (m - 1) / 2, 1, false, batch);
+    const hipStream_t s = (hipStream_t)stream;
+    return (int)with_stage(sh.stage, [&](auto st) {
+        constexpr int ST = decltype(st)::value;
+        return c64 ? mesh_forward<float, ST>(sh, m, batch, phases, U, s) : mesh_forward<double, ST>(sh, m, batch, phases, U, s);
+    });
 }
 
 int slos_launch_mesh_backward(int m, int batch, const double *phases, const void *GU, double *gphases, int c64,
                               void *stream)
 {
-    const int nmzi = m * (m - 1) / 2;
-    const MeshShape sh = mesh_shape(m, nmzi, 2, true);
-    static bool a32 = false, a64 = false;
-    hipError_t e = c64 ? allow_lds(mesh_backward_kernel<float>, a32) : allow_lds(mesh_backward_kernel<double>, a64);
-    if (e != hipSuccess) return (int)e;
-    if (c64)
-        hipLaunchKernelGGL(mesh_backward_kernel<float>, dim3(batch), dim3(64 * sh.ml.waves), sh.lds, (hipStream_t)stream,
-                           m, nmzi, phases, (const float2 *)GU, gphases, sh.stage, sh.ml, sh.lane_sums);
-    else
-        hipLaunchKernelGGL(mesh_backward_kernel<double>, dim3(batch), dim3(64 * sh.ml.waves), sh.lds, (hipStream_t)stream,
-                           m, nmzi, phases, (const double2 *)GU, gphases, sh.stage, sh.ml, sh.lane_sums);
-    return (int)hipGetLastError();
+    const MeshShape sh = mesh_shape(m, m * (m - 1) / 2, 2, true, batch);
+    const hipStream_t s = (hipStream_t)stream;
+    return (int)with_stage(sh.stage, [&](auto st) {
+        constexpr int ST = decltype(st)::value;
+        return c64 ? mesh_backward<float, ST>(sh, m, batch, phases, GU, gphases, s)
+                   : mesh_backward<double, ST>(sh, m, batch, phases, GU, gphases, s);
+    });
 }
