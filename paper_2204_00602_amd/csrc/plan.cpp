@@ -2185,6 +2185,8 @@ int slos_select(slos_plan_t p, const void *U, const int32_t *targets, int64_t co
     if (!U || !targets || !out) return fail(SLOS_ERR_INVALID_ARG, "U, targets and out must not be NULL");
     const int m = p->m, n = p->n;
     const size_t es = p->elem(), tg_bytes = n + sizeof(uint64_t);
+    // whole 16-byte units: a copy of any other size takes a microsecond longer
+    const size_t up_bytes = ((size_t)count * tg_bytes + 15) / 16 * 16;
     // largest sub-lattice whose amplitudes fit a workgroup's LDS
     const uint64_t r_cap = SLOS_LDS_DYNAMIC_MAX / es;
     if ((size_t)count > p->sel_cap) {
@@ -2193,8 +2195,8 @@ int slos_select(slos_plan_t p, const void *U, const int32_t *targets, int64_t co
         p->d_sel = nullptr;
         p->h_sel = nullptr;
         p->sel_cap = 0;
-        if ((rc = alloc_dev((void **)&p->d_sel, (size_t)count * tg_bytes, "target descriptors"))) return rc;
-        hipError_t he = hipHostMalloc((void **)&p->h_sel, (size_t)count * tg_bytes, hipHostMallocDefault);
+        if ((rc = alloc_dev((void **)&p->d_sel, up_bytes, "target descriptors"))) return rc;
+        hipError_t he = hipHostMalloc((void **)&p->h_sel, up_bytes, hipHostMallocDefault);
         if (he != hipSuccess) {
             p->h_sel = nullptr;
             return hip_fail(he, "pinned staging of the target descriptors");
@@ -2384,8 +2386,7 @@ int slos_select(slos_plan_t p, const void *U, const int32_t *targets, int64_t co
         p->sel_uploaded = npat;
         p->sel_st_bytes = st_bytes;
     }
-    hipError_t e = hipMemcpyAsync(p->d_sel, p->h_sel, (size_t)count * tg_bytes, hipMemcpyHostToDevice,
-                                  (hipStream_t)stream);
+    hipError_t e = hipMemcpyAsync(p->d_sel, p->h_sel, up_bytes, hipMemcpyHostToDevice, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "target upload");
     sp.U = U;
     sp.order = (const uint64_t *)p->d_sel;

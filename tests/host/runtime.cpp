@@ -77,6 +77,7 @@ hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind)
 }
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t)
 {
+    fake.copied = n;
     memcpy(d, s, n);
     return hipSuccess;
 }

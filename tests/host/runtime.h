@@ -17,5 +17,6 @@ struct FakeRuntime {
     bool no_threads = false;                         // pthread_create fails
     SelectParams select{};                           // of the last slos_launch_select
     int selects = 0;
+    size_t copied = 0;                               // bytes of the last asynchronous copy
 };
 extern FakeRuntime fake;

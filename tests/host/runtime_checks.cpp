@@ -100,7 +100,7 @@ template <typename F> static void multisets(std::vector<int32_t> &q, int left, s
 
 // The parts of a workgroup's LDS that targets run in, for every multiset of
 // occupations beside a small one: each starts at a multiple of 16 bytes and holds
-// its target.
+// its target; and the copy of a call's targets is of whole 16-byte units.
 static void select_parts()
 {
     const struct { int m, n; } sizes[] = {{11, 11}, {13, 13}, {8, 16}, {8, 21}, {4, 30}};
@@ -123,6 +123,7 @@ static void select_parts()
                 float u[2], out[4];
                 CHECK(slos_select(p, u, t.data(), 2, out, nullptr) == SLOS_OK, "m=%d n=%d", z.m, z.n);
                 const SelectParams &sp = fake.select;
+                CHECK(fake.copied % 16 == 0 && fake.copied >= 2 * (z.n + sizeof(uint64_t)), "%zu bytes copied", fake.copied);
                 CHECK(sp.lds <= SLOS_LDS_DYNAMIC_MAX && R * es <= sp.lds, "m=%d n=%d: %u bytes", z.m, z.n, sp.lds);
                 for (int j = 0; j < SLOS_SELECT_CLASSES; ++j) {
                     if (sp.start[j + 1] == sp.start[j]) continue;
