@@ -801,6 +801,241 @@ int slos_plan(int m, int n, const int32_t *input_state, int flags, slos_plan_t *
     return slos_plan_ex(m, n, input_state, flags, nullptr, out);
 }
 
+// Everything of a plan but what its arguments say directly: host tables, then the
+// device's.  tables: layers may be table-driven.
+static int fill_plan(slos_plan_s *p, const int32_t *input_state, bool tables)
+{
+    const int m = p->m, n = p->n;
+    const slos_options_t &o = p->opts;
+    int rc;
+    if (o.low_block_max > 0) p->low_cap = (uint64_t)o.low_block_max;
+    double tf = 1.0;
+    for (int i = 0; i < m; ++i) {
+        for (int c = 0; c < input_state[i]; ++c) p->photons.push_back(i);
+        for (int v = 2; v <= input_state[i]; ++v) tf *= v;
+    }
+    p->norm_t = 1.0 / std::sqrt(tf);
+    p->B.build(m + n, n);
+    p->Nk.resize(n + 1);
+    for (int k = 0; k <= n; ++k) p->Nk[k] = p->B(m + k - 1, k);
+
+    // size checks: every buffer in bytes must fit size_t with room to spare
+    uint64_t maxN = *std::max_element(p->Nk.begin(), p->Nk.end());
+    if (maxN > (uint64_t(1) << 58))
+        throw std::pair<int, std::string>(SLOS_ERR_SIZE_OVERFLOW, "layer too large for a device buffer");
+
+    p->leaves.resize(n + 1);
+    p->low_max.assign(n + 1, 0);
+    for (int k = 1; k <= n; ++k) {
+        std::vector<uint8_t> hm;
+        p->gen_leaves(k, m - 1, k, p->leaf_cap(k), hm, p->leaves[k]);
+        for (const LeafRec &L : p->leaves[k])
+            p->low_max[k] = std::max(p->low_max[k], p->types[L.tab].low_size);
+        // grouped order by default (depth 1: leaves that share the block
+        // reached by removing their top photon run together)
+        if (o.leaf_order >= 0) order_leaves(p->leaves[k], o.leaf_order > 0 ? o.leaf_order : 1);
+    }
+    if (n > 0) {
+        const uint64_t saved = p->low_cap;
+        p->low_cap = ~uint64_t(0);
+        p->ps_pass = true;
+        std::vector<uint8_t> hm;
+        p->gen_leaves(n, m - 1, n, ps_leaf_cap(p->B(m + n - 1, n)), hm, p->ps_leaves);
+        order_leaves(p->ps_leaves, 1);  // the grouped order (measured faster than colex here too)
+        p->ps_pass = false;
+        p->low_cap = saved;
+    }
+    if (tables && n > 0 && !p->host_only) p->choose_flat();
+    if (p->keep && p->flat_kf) p->choose_flat_bwd();
+    if (p->keep) {
+        p->units.resize(n + 1);
+        p->unit_chunk.assign(n + 1, 128u);
+        for (int k = p->bwd_kb + 1; k <= n; ++k) p->build_units(k);
+    }
+    // one wave must be able to hold its low block in LDS
+    const size_t es_ = p->elem();
+    for (int k = 1; k <= n; ++k)
+        if (slos_lds_wave_bytes(p->low_max[k], (uint32_t)es_) > SLOS_LDS_DYNAMIC_MAX)
+            throw std::pair<int, std::string>(SLOS_ERR_INVALID_ARG,
+                                              "leaf_max too large: a low block does not fit in LDS");
+
+    if (p->pred.size() >= (size_t(1) << 32) || p->lowfac.size() >= (size_t(1) << 32))
+        return fail(SLOS_ERR_SIZE_OVERFLOW, "inner tables exceed 2^32 entries; lower leaf_max");
+    if (p->host_only) return SLOS_OK;
+
+    int ndev = 0;
+    hipError_t e = hipGetDeviceCount(&ndev);
+    if (e != hipSuccess || ndev < 1) return fail(SLOS_ERR_NO_DEVICE, "no HIP device (%s)", hipGetErrorString(e));
+    (void)hipGetDevice(&p->device);
+
+    // upload tables
+    std::vector<unsigned char> descs;
+    p->desc_off.assign(n + 2, 0);
+    p->desc_wide.assign(n + 1, 0);
+    std::vector<uint64_t> deltas;
+    std::vector<uint8_t> modes;
+    for (int k = 1; k <= n; ++k) {
+        p->desc_off[k] = descs.size();
+        // table-driven: no descriptors, unless the adjoint's seed needs them
+        if (k <= p->flat_kf && !(p->keep && k == n && p->bwd_kb < n)) continue;
+        // narrow unless a leaf has more than 16 groups or a 64-bit delta
+        int wide = p->opts.wide_descriptors > 0 ? 1 : 0;
+        for (const LeafRec &L : p->leaves[k]) {
+            LeafDescHead h;
+            p->describe(k, L, h, deltas, modes);
+            if (h.nh > SLOS_NARROW_GROUPS) wide = 1;
+            for (uint64_t d : deltas)
+                if (d > 0xFFFFFFFFull) wide = 1;
+            if (wide) break;
+        }
+        p->desc_wide[k] = wide;
+        const size_t rec = wide ? sizeof(LeafDescWide) : sizeof(LeafDescNarrow);
+        descs.resize(descs.size() + rec * p->leaves[k].size());
+        unsigned char *dst = descs.data() + p->desc_off[k];
+        for (const LeafRec &L : p->leaves[k]) {
+            LeafDescHead h;
+            p->describe(k, L, h, deltas, modes);
+            if (wide) {
+                LeafDescWide w{};
+                w.h = h;
+                for (size_t g = 0; g < deltas.size(); ++g) {
+                    w.delta[g] = deltas[g];
+                    w.mode[g] = modes[g];
+                }
+                std::memcpy(dst, &w, sizeof w);
+            } else {
+                LeafDescNarrow w{};
+                w.h = h;
+                for (size_t g = 0; g < deltas.size(); ++g) {
+                    w.delta[g] = (uint32_t)deltas[g];
+                    w.mode[g] = modes[g];
+                }
+                std::memcpy(dst, &w, sizeof w);
+            }
+            dst += rec;
+        }
+    }
+    p->desc_off[n + 1] = descs.size();
+    if ((rc = dev_upload(&p->d_binom, p->B.t.data(), p->B.t.size(), "binomial table")) ||
+        (rc = dev_upload(&p->d_leaves, p->ps_leaves.data(), p->ps_leaves.size(), "post-selection leaves")) ||
+        (!descs.empty() &&  // no tiled layers: nothing reads their tables
+         ((rc = dev_upload(&p->d_desc, descs.data(), descs.size(), "leaf descriptors")) ||
+          (rc = dev_upload(&p->d_pred, p->pred.data(), p->pred.size(), "inner predecessor table")) ||
+          (rc = dev_upload(&p->d_lowfac, p->lowfac.data(), p->lowfac.size(), "inner factorial table")))))
+        return rc;
+
+    // A_0 = [1]
+    const size_t es = p->elem();
+    {
+        double one_d[2] = {1.0, 0.0};
+        float one_f[2] = {1.0f, 0.0f};
+        if ((rc = alloc_dev(&p->d_vac, es + SLOS_BUFFER_SLACK, "vacuum layer"))) return rc;
+        e = hipMemcpy(p->d_vac, p->c64 ? (const void *)one_f : (const void *)one_d, es, hipMemcpyHostToDevice);
+        if (e != hipSuccess) return hip_fail(e, "vacuum upload");
+    }
+    // intermediate layers 1..n-1
+    if (p->keep) {
+        p->keep_off.assign(n + 1, 0);
+        uint64_t tot = 0;
+        for (int k = 0; k < n; ++k) {
+            p->keep_off[k] = tot;
+            tot += (p->Nk[k] + 15) / 16 * 16;  // 128-byte aligned layers
+        }
+        p->keep_off[n] = tot;
+        p->keep_stride = tot;
+        if ((rc = alloc_dev(&p->d_keep, tot * es * p->batch_cap + SLOS_BUFFER_SLACK, "kept layers"))) return rc;
+        for (int b = 0; b < p->batch_cap; ++b) {
+            e = hipMemcpy((char *)p->d_keep + (size_t)b * tot * es, p->d_vac, es, hipMemcpyDeviceToDevice);
+            if (e != hipSuccess) return hip_fail(e, "kept vacuum layer");
+        }
+    } else {
+        uint64_t need[2] = {0, 0};
+        for (int k = 1; k < n; ++k) need[k & 1] = std::max(need[k & 1], p->Nk[k]);
+        for (int b = 0; b < 2; ++b) {
+            need[b] = (need[b] + 31) / 32 * 32;  // 256-byte aligned instances
+            p->buf_stride[b] = need[b];
+        }
+        for (int b = 0; b < 2; ++b)
+            if (need[b] && (rc = alloc_dev(&p->d_buf[b], need[b] * es * p->batch_cap + SLOS_BUFFER_SLACK,
+                                           "layer buffer")))
+                return rc;
+    }
+    p->n_partials = n > 0 ? (int64_t)p->leaves[n].size() * (p->opts.block_threads / 64) : 1;
+    if (p->last_flat()) {
+        // one per workgroup of the last layer's launch (a call on fewer unitaries has the most)
+        int threads = 0, groups = 0;
+        p->head_shape(1, threads, groups);
+        p->n_partials = p->flat_h + 1 == n ? groups : (int64_t)((p->Nk[n] + SLOS_FLAT_THREADS - 1) / SLOS_FLAT_THREADS);
+    }
+    if ((rc = alloc_dev((void **)&p->d_partials,
+                        (size_t)(p->n_partials + SLOS_REDUCE_STAGE) * p->batch_cap * sizeof(double), "partial sums")) ||
+        (rc = alloc_dev((void **)&p->d_tickets,
+                        (size_t)p->ticket_words() * p->batch_cap * sizeof(uint32_t), "ticket counters")) ||
+        (rc = clear_dev(p->d_tickets, (size_t)p->ticket_words() * p->batch_cap * sizeof(uint32_t))))
+        return rc;
+    {
+        const uint64_t nb = (p->Nk[n] + SLOS_CDF_BLOCK - 1) / SLOS_CDF_BLOCK;
+        const uint64_t nsup = (nb + SLOS_CDF_BLOCK - 1) / SLOS_CDF_BLOCK;
+        std::vector<int64_t> ends(m);
+        for (int K = 1; K <= m; ++K) ends[K - 1] = (int64_t)p->B(K + n - 1, n);
+        if ((rc = alloc_dev((void **)&p->d_cdf,
+                            (nb + 1 + nsup + 1 + (uint64_t)(SLOS_CDF_BLOCK / 64) * nb +
+                             (uint64_t)cdf_tree_layout((int64_t)nb).total) * sizeof(double),
+                            "cumulative probability table")) ||
+            (rc = dev_upload(&p->d_pk_ends, ends.data(), ends.size(), "marginal bounds")) ||
+            (rc = alloc_dev((void **)&p->d_ps_partials, (SLOS_PS_MAX_WAVES + SLOS_REDUCE_STAGE) * sizeof(double),
+                            "post-selection partial sums")))
+            return rc;
+    }
+    if (n > 0) {
+        // post-selection tables: one run of low states per inner shape of
+        // its leaves, in the order the shapes were met (ascending off)
+        std::vector<uint32_t> off(p->ps_type_list.size(), 0);
+        std::vector<PsType> pt = p->ps_type_list;
+        uint64_t entries = 0;
+        for (size_t i = 0; i < pt.size(); ++i) {
+            off[i] = (uint32_t)entries;
+            pt[i].off = (uint32_t)entries;
+            entries += pt[i].size;
+        }
+        if (entries >= (1ull << 32)) return fail(SLOS_ERR_SIZE_OVERFLOW, "post-selection table exceeds 2^32 entries");
+        p->ps_ntypes = (uint32_t)pt.size();
+        p->ps_entries = (uint32_t)entries;
+        if ((rc = dev_upload(&p->d_ps_types, pt.data(), pt.size(), "post-selection types")) ||
+            (rc = dev_upload(&p->d_ps_type_off, off.data(), off.size(), "post-selection offsets")) ||
+            (rc = alloc_dev((void **)&p->d_ps_low, entries * SLOS_PS_MAX_GROUPS, "post-selection table")))
+            return rc;
+    }
+    if (p->keep && n > 0) {
+        std::vector<BwdUnit> allu;
+        p->unit_off.assign(n + 2, 0);
+        p->bpart_off.assign(n + 2, 0);
+        uint64_t bp = 0;
+        for (int k = 1; k <= n; ++k) {
+            p->unit_off[k] = allu.size();
+            p->bpart_off[k] = bp;
+            allu.insert(allu.end(), p->units[k].begin(), p->units[k].end());
+            // the tail keeps its layers' sums to itself
+            if (k > p->bwd_t) bp += p->bwd_rows(k) * (uint64_t)m;
+        }
+        p->bpart_off[n + 1] = bp;
+        uint64_t gmax = *std::max_element(p->Nk.begin(), p->Nk.end());
+        gmax = (gmax + 31) / 32 * 32;
+        p->g_stride = gmax;
+        p->bpart_stride = std::max<uint64_t>(bp, 1);
+        std::vector<int32_t> ph(p->photons.begin(), p->photons.end());
+        if ((rc = dev_upload(&p->d_units, allu.data(), allu.size(), "reverse units")) ||
+            (rc = dev_upload(&p->d_succ, p->succ.data(), p->succ.size(), "successor tables")) ||
+            (rc = dev_upload(&p->d_hbase, p->hbase.data(), p->hbase.size(), "successor bases")) ||
+            (rc = dev_upload(&p->d_photons, ph.data(), ph.size(), "photon list")) ||
+            (rc = alloc_dev(&p->d_g[0], gmax * es * p->batch_cap, "adjoint layer")) ||
+            (rc = alloc_dev(&p->d_g[1], gmax * es * p->batch_cap, "adjoint layer")) ||
+            (rc = alloc_dev(&p->d_bpart, p->bpart_stride * 16 * p->batch_cap, "gradient partials")))
+            return rc;
+    }
+    return p->flat_kf > 0 ? build_flat(p) : SLOS_OK;
+}
+
 // tables: in, whether layers may be table-driven; out, whether one is.
 static int make_plan(int m, int n, const int32_t *input_state, int flags, const slos_options_t *opts, bool &tables,
                      slos_plan_t *out)
@@ -889,296 +1124,16 @@ static int make_plan(int m, int n, const int32_t *input_state, int flags, const 
     p->host_only = (flags & SLOS_HOST_ONLY) != 0;
     p->opts = o;
     p->batch_cap = o.max_batch;
-
-    if (o.low_block_max > 0) p->low_cap = (uint64_t)o.low_block_max;
+    // no exception leaves the library, and a plan that fails on the way is freed whole
     try {
-        double tf = 1.0;
-        for (int i = 0; i < m; ++i) {
-            for (int c = 0; c < input_state[i]; ++c) p->photons.push_back(i);
-            for (int v = 2; v <= input_state[i]; ++v) tf *= v;
-        }
-        p->norm_t = 1.0 / std::sqrt(tf);
-        p->B.build(m + n, n);
-        p->Nk.resize(n + 1);
-        for (int k = 0; k <= n; ++k) p->Nk[k] = p->B(m + k - 1, k);
-
-        // size checks: every buffer in bytes must fit size_t with room to spare
-        uint64_t maxN = *std::max_element(p->Nk.begin(), p->Nk.end());
-        if (maxN > (uint64_t(1) << 58))
-            throw std::pair<int, std::string>(SLOS_ERR_SIZE_OVERFLOW, "layer too large for a device buffer");
-
-        p->leaves.resize(n + 1);
-        p->low_max.assign(n + 1, 0);
-        for (int k = 1; k <= n; ++k) {
-            std::vector<uint8_t> hm;
-            p->gen_leaves(k, m - 1, k, p->leaf_cap(k), hm, p->leaves[k]);
-            for (const LeafRec &L : p->leaves[k])
-                p->low_max[k] = std::max(p->low_max[k], p->types[L.tab].low_size);
-            // grouped order by default (depth 1: leaves that share the block
-            // reached by removing their top photon run together)
-            if (o.leaf_order >= 0) order_leaves(p->leaves[k], o.leaf_order > 0 ? o.leaf_order : 1);
-        }
-        if (n > 0) {
-            const uint64_t saved = p->low_cap;
-            p->low_cap = ~uint64_t(0);
-            p->ps_pass = true;
-            std::vector<uint8_t> hm;
-            p->gen_leaves(n, m - 1, n, ps_leaf_cap(p->B(m + n - 1, n)), hm, p->ps_leaves);
-            order_leaves(p->ps_leaves, 1);  // the grouped order (measured faster than colex here too)
-            p->ps_pass = false;
-            p->low_cap = saved;
-        }
-        if (allowed && !tiled && n > 0 && !p->host_only) p->choose_flat();
-        tables = p->flat_kf > 0;
-        if (p->keep && p->flat_kf) p->choose_flat_bwd();
-        if (p->keep) {
-            p->units.resize(n + 1);
-            p->unit_chunk.assign(n + 1, 128u);
-            for (int k = p->bwd_kb + 1; k <= n; ++k) p->build_units(k);
-        }
-        // one wave must be able to hold its low block in LDS
-        const size_t es_ = (dt == SLOS_C64) ? 8 : 16;
-        for (int k = 1; k <= n; ++k)
-            if (slos_lds_wave_bytes(p->low_max[k], (uint32_t)es_) > SLOS_LDS_DYNAMIC_MAX)
-                throw std::pair<int, std::string>(SLOS_ERR_INVALID_ARG,
-                                                  "leaf_max too large: a low block does not fit in LDS");
+        rc = fill_plan(p, input_state, allowed && !tiled);
     } catch (std::bad_alloc &) {
-        delete p;
-        return fail(SLOS_ERR_OOM, "host allocation failed while building tables");
+        rc = fail(SLOS_ERR_OOM, "host allocation failed while building the plan");
     } catch (std::pair<int, std::string> &e) {
-        delete p;
-        return fail(e.first, "%s", e.second.c_str());
+        rc = fail(e.first, "%s", e.second.c_str());
     }
-
-    if (p->pred.size() >= (size_t(1) << 32) || p->lowfac.size() >= (size_t(1) << 32)) {
-        delete p;
-        return fail(SLOS_ERR_SIZE_OVERFLOW, "inner tables exceed 2^32 entries; lower leaf_max");
-    }
-    if (p->host_only) {
-        *out = p;
-        return SLOS_OK;
-    }
-
-    int ndev = 0;
-    hipError_t e = hipGetDeviceCount(&ndev);
-    if (e != hipSuccess || ndev < 1) {
-        delete p;
-        return fail(SLOS_ERR_NO_DEVICE, "no HIP device (%s)", hipGetErrorString(e));
-    }
-    (void)hipGetDevice(&p->device);
-
-    // upload tables
-    std::vector<unsigned char> descs;
-    p->desc_off.assign(n + 2, 0);
-    p->desc_wide.assign(n + 1, 0);
-    try {
-        std::vector<uint64_t> deltas;
-        std::vector<uint8_t> modes;
-        for (int k = 1; k <= n; ++k) {
-            p->desc_off[k] = descs.size();
-            // table-driven: no descriptors, unless the adjoint's seed needs them
-            if (k <= p->flat_kf && !(p->keep && k == n && p->bwd_kb < n)) continue;
-            // narrow unless a leaf has more than 16 groups or a 64-bit delta
-            int wide = p->opts.wide_descriptors > 0 ? 1 : 0;
-            for (const LeafRec &L : p->leaves[k]) {
-                LeafDescHead h;
-                p->describe(k, L, h, deltas, modes);
-                if (h.nh > SLOS_NARROW_GROUPS) wide = 1;
-                for (uint64_t d : deltas)
-                    if (d > 0xFFFFFFFFull) wide = 1;
-                if (wide) break;
-            }
-            p->desc_wide[k] = wide;
-            const size_t rec = wide ? sizeof(LeafDescWide) : sizeof(LeafDescNarrow);
-            descs.resize(descs.size() + rec * p->leaves[k].size());
-            unsigned char *dst = descs.data() + p->desc_off[k];
-            for (const LeafRec &L : p->leaves[k]) {
-                LeafDescHead h;
-                p->describe(k, L, h, deltas, modes);
-                if (wide) {
-                    LeafDescWide w{};
-                    w.h = h;
-                    for (size_t g = 0; g < deltas.size(); ++g) {
-                        w.delta[g] = deltas[g];
-                        w.mode[g] = modes[g];
-                    }
-                    std::memcpy(dst, &w, sizeof w);
-                } else {
-                    LeafDescNarrow w{};
-                    w.h = h;
-                    for (size_t g = 0; g < deltas.size(); ++g) {
-                        w.delta[g] = (uint32_t)deltas[g];
-                        w.mode[g] = modes[g];
-                    }
-                    std::memcpy(dst, &w, sizeof w);
-                }
-                dst += rec;
-            }
-        }
-        p->desc_off[n + 1] = descs.size();
-    } catch (std::bad_alloc &) {
-        delete p;
-        return fail(SLOS_ERR_OOM, "host allocation failed while building leaf descriptors");
-    }
-    if ((rc = dev_upload(&p->d_binom, p->B.t.data(), p->B.t.size(), "binomial table")) ||
-        (rc = dev_upload(&p->d_leaves, p->ps_leaves.data(), p->ps_leaves.size(), "post-selection leaves")) ||
-        (!descs.empty() &&  // no tiled layers: nothing reads their tables
-         ((rc = dev_upload(&p->d_desc, descs.data(), descs.size(), "leaf descriptors")) ||
-          (rc = dev_upload(&p->d_pred, p->pred.data(), p->pred.size(), "inner predecessor table")) ||
-          (rc = dev_upload(&p->d_lowfac, p->lowfac.data(), p->lowfac.size(), "inner factorial table"))))) {
-        p->free_device();
-        delete p;
-        return rc;
-    }
-
-    // A_0 = [1]
-    const size_t es = p->elem();
-    {
-        double one_d[2] = {1.0, 0.0};
-        float one_f[2] = {1.0f, 0.0f};
-        if ((rc = alloc_dev(&p->d_vac, es + SLOS_BUFFER_SLACK, "vacuum layer"))) {
-            p->free_device();
-            delete p;
-            return rc;
-        }
-        e = hipMemcpy(p->d_vac, p->c64 ? (const void *)one_f : (const void *)one_d, es,
-                      hipMemcpyHostToDevice);
-        if (e != hipSuccess) {
-            rc = hip_fail(e, "vacuum upload");
-            p->free_device();
-            delete p;
-            return rc;
-        }
-    }
-    // intermediate layers 1..n-1
-    if (p->keep) {
-        p->keep_off.assign(n + 1, 0);
-        uint64_t tot = 0;
-        for (int k = 0; k < n; ++k) {
-            p->keep_off[k] = tot;
-            tot += (p->Nk[k] + 15) / 16 * 16;  // 128-byte aligned layers
-        }
-        p->keep_off[n] = tot;
-        p->keep_stride = tot;
-        if ((rc = alloc_dev(&p->d_keep, tot * es * p->batch_cap + SLOS_BUFFER_SLACK, "kept layers"))) {
-            p->free_device();
-            delete p;
-            return rc;
-        }
-        for (int b = 0; b < p->batch_cap; ++b) {
-            e = hipMemcpy((char *)p->d_keep + (size_t)b * tot * es, p->d_vac, es, hipMemcpyDeviceToDevice);
-            if (e != hipSuccess) {
-                rc = hip_fail(e, "kept vacuum layer");
-                p->free_device();
-                delete p;
-                return rc;
-            }
-        }
-    } else {
-        uint64_t need[2] = {0, 0};
-        for (int k = 1; k < n; ++k) need[k & 1] = std::max(need[k & 1], p->Nk[k]);
-        for (int b = 0; b < 2; ++b) {
-            need[b] = (need[b] + 31) / 32 * 32;  // 256-byte aligned instances
-            p->buf_stride[b] = need[b];
-        }
-        for (int b = 0; b < 2; ++b)
-            if (need[b] && (rc = alloc_dev(&p->d_buf[b], need[b] * es * p->batch_cap + SLOS_BUFFER_SLACK,
-                                           "layer buffer"))) {
-                p->free_device();
-                delete p;
-                return rc;
-            }
-    }
-    p->n_partials = n > 0 ? (int64_t)p->leaves[n].size() * (p->opts.block_threads / 64) : 1;
-    if (p->last_flat()) {
-        // one per workgroup of the last layer's launch (a call on fewer unitaries has the most)
-        int threads = 0, groups = 0;
-        p->head_shape(1, threads, groups);
-        p->n_partials = p->flat_h + 1 == n ? groups : (int64_t)((p->Nk[n] + SLOS_FLAT_THREADS - 1) / SLOS_FLAT_THREADS);
-    }
-    if ((rc = alloc_dev((void **)&p->d_partials,
-                        (size_t)(p->n_partials + SLOS_REDUCE_STAGE) * p->batch_cap * sizeof(double), "partial sums")) ||
-        (rc = alloc_dev((void **)&p->d_tickets,
-                        (size_t)p->ticket_words() * p->batch_cap * sizeof(uint32_t), "ticket counters")) ||
-        (rc = clear_dev(p->d_tickets, (size_t)p->ticket_words() * p->batch_cap * sizeof(uint32_t)))) {
-        p->free_device();
-        delete p;
-        return rc;
-    }
-    {
-        const uint64_t nb = (p->Nk[n] + SLOS_CDF_BLOCK - 1) / SLOS_CDF_BLOCK;
-        const uint64_t nsup = (nb + SLOS_CDF_BLOCK - 1) / SLOS_CDF_BLOCK;
-        std::vector<int64_t> ends(m);
-        for (int K = 1; K <= m; ++K) ends[K - 1] = (int64_t)p->B(K + n - 1, n);
-        if ((rc = alloc_dev((void **)&p->d_cdf,
-                            (nb + 1 + nsup + 1 + (uint64_t)(SLOS_CDF_BLOCK / 64) * nb +
-                             (uint64_t)cdf_tree_layout((int64_t)nb).total) * sizeof(double),
-                            "cumulative probability table")) ||
-            (rc = dev_upload(&p->d_pk_ends, ends.data(), ends.size(), "marginal bounds")) ||
-            (rc = alloc_dev((void **)&p->d_ps_partials, (SLOS_PS_MAX_WAVES + SLOS_REDUCE_STAGE) * sizeof(double),
-                            "post-selection partial sums"))) {
-            p->free_device();
-            delete p;
-            return rc;
-        }
-    }
-    if (n > 0) {
-        // post-selection tables: one run of low states per inner shape of
-        // its leaves, in the order the shapes were met (ascending off)
-        std::vector<uint32_t> off(p->ps_type_list.size(), 0);
-        std::vector<PsType> pt = p->ps_type_list;
-        uint64_t entries = 0;
-        for (size_t i = 0; i < pt.size(); ++i) {
-            off[i] = (uint32_t)entries;
-            pt[i].off = (uint32_t)entries;
-            entries += pt[i].size;
-        }
-        if (entries >= (1ull << 32)) {
-            p->free_device();
-            delete p;
-            return fail(SLOS_ERR_SIZE_OVERFLOW, "post-selection table exceeds 2^32 entries");
-        }
-        p->ps_ntypes = (uint32_t)pt.size();
-        p->ps_entries = (uint32_t)entries;
-        if ((rc = dev_upload(&p->d_ps_types, pt.data(), pt.size(), "post-selection types")) ||
-            (rc = dev_upload(&p->d_ps_type_off, off.data(), off.size(), "post-selection offsets")) ||
-            (rc = alloc_dev((void **)&p->d_ps_low, entries * SLOS_PS_MAX_GROUPS, "post-selection table"))) {
-            p->free_device();
-            delete p;
-            return rc;
-        }
-    }
-    if (p->keep && n > 0) {
-        std::vector<BwdUnit> allu;
-        p->unit_off.assign(n + 2, 0);
-        p->bpart_off.assign(n + 2, 0);
-        uint64_t bp = 0;
-        for (int k = 1; k <= n; ++k) {
-            p->unit_off[k] = allu.size();
-            p->bpart_off[k] = bp;
-            allu.insert(allu.end(), p->units[k].begin(), p->units[k].end());
-            // the tail keeps its layers' sums to itself
-            if (k > p->bwd_t) bp += p->bwd_rows(k) * (uint64_t)m;
-        }
-        p->bpart_off[n + 1] = bp;
-        uint64_t gmax = *std::max_element(p->Nk.begin(), p->Nk.end());
-        gmax = (gmax + 31) / 32 * 32;
-        p->g_stride = gmax;
-        p->bpart_stride = std::max<uint64_t>(bp, 1);
-        std::vector<int32_t> ph(p->photons.begin(), p->photons.end());
-        if ((rc = dev_upload(&p->d_units, allu.data(), allu.size(), "reverse units")) ||
-            (rc = dev_upload(&p->d_succ, p->succ.data(), p->succ.size(), "successor tables")) ||
-            (rc = dev_upload(&p->d_hbase, p->hbase.data(), p->hbase.size(), "successor bases")) ||
-            (rc = dev_upload(&p->d_photons, ph.data(), ph.size(), "photon list")) ||
-            (rc = alloc_dev(&p->d_g[0], gmax * es * p->batch_cap, "adjoint layer")) ||
-            (rc = alloc_dev(&p->d_g[1], gmax * es * p->batch_cap, "adjoint layer")) ||
-            (rc = alloc_dev(&p->d_bpart, p->bpart_stride * 16 * p->batch_cap, "gradient partials"))) {
-            p->free_device();
-            delete p;
-            return rc;
-        }
-    }
-    if (p->flat_kf > 0 && (rc = build_flat(p))) {
+    tables = p->flat_kf > 0;
+    if (rc) {
         p->free_device();
         delete p;
         return rc;
@@ -2163,8 +2118,8 @@ static uint32_t select_pattern(slos_plan_s *p, const std::vector<uint8_t> &key, 
         }
     }
     pt.lstart[n + 1] = run;
-    p->sel_state.resize(p->sel_state.size() + R);
-    p->sel_mask.resize(p->sel_mask.size() + R);
+    p->sel_state.resize((size_t)pt.off + R);  // both: a call that ran out of memory may have left one longer
+    p->sel_mask.resize((size_t)pt.off + R);
     for (uint32_t x = 0; x < R; ++x) {
         const uint32_t pos = pt.off + cnt[layer[x]]++;
         p->sel_state[pos] = (uint16_t)x;

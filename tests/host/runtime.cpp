@@ -6,7 +6,7 @@
 
 #include <cstdlib>
 #include <cstring>
-#include <map>
+#include <new>
 
 #include "flat.h"
 
@@ -20,7 +20,7 @@
 #undef slos_prepare_batch_kernels
 
 FakeRuntime fake;
-static std::map<void *, size_t> blocks;
+static constexpr size_t kHead = 64;
 
 int slos_launch_select(const SelectParams &p, int, void *)
 {
@@ -30,6 +30,24 @@ int slos_launch_select(const SelectParams &p, int, void *)
 }
 int slos_launch_layer(const LayerParams &, const LayerLaunch &, void *) { return 0; }
 int slos_prepare_batch_kernels() { return 0; }
+
+// host memory that runs out once
+void *operator new(size_t n)
+{
+    if (fake.news.load(std::memory_order_relaxed) >= 0 && fake.news.fetch_sub(1) == 0) throw std::bad_alloc();
+    if (void *p = malloc(n ? n : 1)) return p;
+    throw std::bad_alloc();
+}
+void *operator new(size_t n, const std::nothrow_t &) noexcept
+{
+    try {
+        return operator new(n);
+    } catch (std::bad_alloc &) {
+        return nullptr;
+    }
+}
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
 
 extern "C" {
 
@@ -46,19 +64,20 @@ hipError_t hipMalloc(void **p, size_t bytes)
 {
     *p = nullptr;
     if (bytes > fake.budget || fake.used > fake.budget - bytes) return hipErrorOutOfMemory;
-    if (!(*p = malloc(bytes))) return hipErrorOutOfMemory;
-    blocks[*p] = bytes;
+    size_t *head = (size_t *)malloc(bytes + kHead);  // its size goes before the block
+    if (!head) return hipErrorOutOfMemory;
+    *head = bytes;
+    *p = (char *)head + kHead;
     fake.used += bytes;
     fake.peak = fake.peak < fake.used ? fake.used : fake.peak;
     return hipSuccess;
 }
 hipError_t hipFree(void *p)
 {
-    const auto it = blocks.find(p);
-    if (it == blocks.end()) return hipErrorInvalidValue;
-    fake.used -= it->second;
-    blocks.erase(it);
-    free(p);
+    if (!p) return hipSuccess;
+    size_t *head = (size_t *)((char *)p - kHead);
+    fake.used -= *head;
+    free(head);
     return hipSuccess;
 }
 hipError_t hipHostMalloc(void **p, size_t bytes, unsigned)

@@ -4,6 +4,7 @@
 // look at and do nothing.
 #pragma once
 
+#include <atomic>
 #include <cstddef>
 #include <cstdint>
 
@@ -15,6 +16,7 @@
 struct FakeRuntime {
     size_t used = 0, peak = 0, budget = ~size_t(0);  // bytes of device memory
     bool no_threads = false;                         // pthread_create fails
+    std::atomic<long> news{-1};                      // allocations until one fails, once (< 0: none does)
     SelectParams select{};                           // of the last slos_launch_select
     int selects = 0;
     size_t copied = 0;                               // bytes of the last asynchronous copy

@@ -250,6 +250,86 @@ static void noalloc_area()
     CHECK(held > 10, "only %d plans fit the area", held);
 }
 
+// `call` with each of its host allocations failing in turn: it returns OK or OOM (no
+// exception crosses the C entry) and, with `clean`, gives the device's memory back.
+template <typename F, typename G> static void fail_each(const char *what, F &&call, G &&after)
+{
+    for (long i = 0;; ++i) {
+        fake.news = i;
+        int rc = -100;
+        try {
+            rc = call();
+        } catch (...) {
+        }
+        const bool reached = fake.news.exchange(-1) < 0;
+        CHECK(rc == SLOS_OK || rc == SLOS_ERR_OOM, "%s, allocation %ld: %d", what, i, rc);
+        after(rc);
+        if (!reached || failures > 20) break;
+    }
+}
+
+static void allocation_failures()
+{
+    std::vector<int32_t> T(12, 0);
+    for (int i = 0; i < 6; ++i) T[i] = 1;
+    for (int flags : {SLOS_C64, SLOS_C128 | SLOS_KEEP_LAYERS}) {
+        slos_plan_t p = nullptr;
+        fake.used = 0;
+        fail_each("plan", [&] { return slos_plan(8, 4, T.data() + 2, flags, &p); },
+                  [&](int rc) {
+                      CHECK((p != nullptr) == (rc == SLOS_OK), "plan: a handle with an error");
+                      slos_plan_destroy(p);
+                      p = nullptr;
+                      CHECK(fake.used == 0, "plan: %zu bytes kept", fake.used);
+                  });
+    }
+    const int32_t ms[3] = {12, 12, 6};
+    std::vector<int32_t> in(T);
+    in.insert(in.end(), T.begin(), T.end());
+    in.insert(in.end(), T.begin() + 3, T.begin() + 9);
+    slos_batch_t b = nullptr;
+    fail_each("batch", [&] { return slos_batch_plan(3, ms, in.data(), SLOS_C64, nullptr, &b); },
+              [&](int) {
+                  slos_batch_destroy(b);
+                  b = nullptr;
+                  CHECK(fake.used == 0, "batch: %zu bytes kept", fake.used);
+              });
+    const slos_source_params_t sp{0.9, 0.05, 0.92};
+    slos_source_t s = nullptr;
+    fail_each("source", [&] { return slos_source_plan(6, T.data() + 3, &sp, -1, nullptr, &s); },
+              [&](int) {
+                  slos_source_destroy(s);
+                  s = nullptr;
+                  CHECK(fake.used == 0, "source: %zu bytes kept", fake.used);
+              });
+    // selected outputs on a new plan: after a failure the same call gives all its targets
+    const std::vector<int32_t> t = targets_of(4200, 1000);
+    float u[2], out[2];
+    slos_plan_t p = nullptr;
+    fail_each("select",
+              [&] {
+                  if (!p) {
+                      const long news = fake.news.exchange(-1);
+                      CHECK(slos_plan(12, 6, T.data(), SLOS_C64, &p) == SLOS_OK, "plan");
+                      fake.news = news;
+                  }
+                  return slos_select(p, u, t.data(), 4200, out, nullptr);
+              },
+              [&](int) {
+                  CHECK(slos_select(p, u, t.data(), 4200, out, nullptr) == SLOS_OK, "select after a failure");
+                  check_dealt(4200, "after a failure");
+                  for (int i = 0; i < 4200; ++i) {
+                      const SelectPattern &pt = fake.select.patterns[fake.select.order[i] & 0xFFFFu];
+                      if (pt.off + pt.R > (uint32_t)((const uint16_t *)fake.select.mask - fake.select.state)) {
+                          CHECK(false, "a pattern past the pools");
+                          break;
+                      }
+                  }
+                  slos_plan_destroy(p);
+                  p = nullptr;
+              });
+}
+
 int main(int argc, char **argv)
 {
     const char *what = argc > 1 ? argv[1] : "";
@@ -257,6 +337,7 @@ int main(int argc, char **argv)
     else if (!std::strcmp(what, "select-parts")) select_parts();
     else if (!std::strcmp(what, "table-memory")) table_memory();
     else if (!std::strcmp(what, "noalloc-area")) noalloc_area();
+    else if (!std::strcmp(what, "allocation-failures")) allocation_failures();
     else {
         std::printf("no check named '%s'\n", what);
         return 2;

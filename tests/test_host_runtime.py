@@ -35,6 +35,7 @@ def checks(tmp_path_factory):
     "select-parts",    # every multiset of occupations beside a small one
     "table-memory",    # plans, batches and sources in the memory they take without tables
     "noalloc-area",    # plans that slos_amplitudes_noalloc takes without tables
+    "allocation-failures",  # each host allocation of a call failing in turn
 ])
 def test_host_runtime(checks, name):
     res = subprocess.run([checks, name], capture_output=True, text=True, timeout=600)
