@@ -19,7 +19,9 @@
 // (c64), 1,081,575 31 against 15 (c64) and 37 against 18 (c128), 2,220,075 38
 // against 24 and 53 against 31, 3,124,550 55 against 42 and 78 against 53;
 // 4,686,825 66 against 70 (c64; c128 99 against 84, but its table alone is
-// 170 MB), 6,906,900 83 against 100.  Also keeps every rank within 24 bits.
+// 170 MB), 6,906,900 83 against 100.  The line holds for several instances as for
+// one (whole calls, c64, 8 and 64 instances of 3,124,550 states in the last layer:
+// 686 against 397 and 5143 against 2976).  Also keeps every rank within 24 bits.
 #define SLOS_FLAT_MAX_STATES 3200000u
 // Entries of a plan's successor tables: 512 MiB, as the tables of a batch (by the
 // line above its predecessor tables have at most 410 MiB).
@@ -178,10 +180,6 @@ int slos_launch_flat_batch(const FlatBatchParams &p, int c64, int grid, void *st
 // ---- adjoint of the table-driven layers (flat_bwd.hip) -------------------------
 
 #define SLOS_BWD_LDS_MAX (149u * 1024u)
-// Reverse layers of at most this many terms (states of layer k - 1 times modes)
-// run in the one-workgroup tail: 52,416 terms (m=12, n=6, layer 6) take it 9.8
-// us, and a launch of their own at least 5 with a seed or loss launch before it.
-#define SLOS_BWD_TAIL_TERMS 60000u
 #define SLOS_BWD_THREADS 512     // of a reverse layer
 // Threads of a tail workgroup.  With more instances than compute units
 // (SLOS_BWD_TAIL_MANY) small ones leave most of 1024 threads idle while no second
@@ -196,7 +194,8 @@ int slos_launch_flat_batch(const FlatBatchParams &p, int c64, int grid, void *st
 #define SLOS_BWD_TAIL_MANY 256
 #define SLOS_BWD_TAIL_LDS_256 (40u * 1024u)
 #define SLOS_BWD_TAIL_LDS_64 (10u * 1024u)
-// Modes whose gradient sums a thread of the tail keeps in registers.
+// Modes whose gradient sums a thread of the tail keeps in registers: the most that
+// the 128 registers of four waves a SIMD hold (8: none spilled, 12: 2 to 12, 16: 39 to 49).
 #define SLOS_BWD_TAIL_MODES 12
 
 // One reverse layer: g_{k-1} and, per workgroup, the gradient partials of every mode.

@@ -17,8 +17,9 @@
 // 4096 instances of m 6..14, n 2..7 (25.3 M outputs): c64 168 us, c128 319; the
 // tiled kernel takes 480 and 677, the outputs alone 43 and 86 at the rate of a
 // copy.  16 of m 6..14: c128 58 us against 376, 64 in c64 42 against 282.  What
-// bounds it is instruction issue (65 M wave instructions, 106 us on 1024 SIMDs)
-// and, in c128, the blocks of layers that no longer fit the LDS.
+// bounds it is instruction issue (65 M vector instructions, 106 us on 1024 SIMDs),
+// lane moves for 71 spilled scalar registers among them, and, in c128, the blocks of
+// layers that no longer fit the LDS (36 vector registers spill there).
 // Sixteen waves hide the gathers' latency; eight with twice the registers: 195 us
 // instead of 152 for 256 of (14, 7).
 #include <algorithm>

@@ -206,7 +206,7 @@ template <int NM> struct Modes {
 
 // Bound by instruction issue in the layers of thousands of states and by the
 // chain of one state's terms and the reductions in the others: m=12, n=6 (c64,
-// 64 instances) 27 us for the loss, six layers and G_U, of which layer 6 takes
+// 64 instances) 29 us for the loss, six layers and G_U, of which layer 6 takes
 // 9.8 and layers 3..1 1.4 each; the launches it replaces took 109 us.
 //
 // Layers t..1 of instance blockIdx.x in one workgroup: g_k and g_{k-1} in LDS,

@@ -541,7 +541,9 @@ struct slos_plan_s {
     // Reverse layers from tables: those whose layer k - 1 has a table-driven
     // size, up to the limit of all successor tables (4 m bytes a state: plans of 48
     // modes and more meet it, at a layer below the last); of these the tail takes
-    // what fits one workgroup's LDS and time.
+    // what fits one workgroup's LDS (which keeps a layer's terms below 60,000: the
+    // largest of 12 modes and 6 photons, 52,416, takes it 9.8 us, and a launch of its own at
+    // least 5 with a seed or loss launch before it).
     void choose_flat_bwd()
     {
         uint64_t entries = 0;
@@ -550,13 +552,7 @@ struct slos_plan_s {
             if (entries > SLOS_FLAT_MAX_SUCC) break;
             ++bwd_kb;
         }
-        while (bwd_t < bwd_kb) {
-            const int k = bwd_t + 1;
-            const uint64_t need = tail_lds(k, SLOS_BWD_TAIL_THREADS);
-            if (need > SLOS_BWD_LDS_MAX) break;
-            if (k > 1 && Nk[k - 1] * (uint64_t)m > SLOS_BWD_TAIL_TERMS) break;
-            bwd_t = k;
-        }
+        while (bwd_t < bwd_kb && tail_lds(bwd_t + 1, SLOS_BWD_TAIL_THREADS) <= SLOS_BWD_LDS_MAX) ++bwd_t;
         if (bwd_t == 0) bwd_kb = 0;
         bwd_threads = SLOS_BWD_TAIL_THREADS;
         if (batch_cap > SLOS_BWD_TAIL_MANY && bwd_t > 0) {
@@ -746,10 +742,10 @@ int build_flat(slos_plan_t p)
 // States per leaf of post-selection.  Leaves are dealt to 8192 waves, so few large
 // ones leave most waves idle, while many small ones share less of a table that is
 // made in every call: near the square root of the states both are small.  Whole
-// calls, with leaves of 32768 and by this rule: 20 modes, 10 photons, c128, masked
-// 184 and 112 us; 22 and 11, c64 387 and 323; 18 and 9, c128, six groups 291 and
-// 58; 15 and 7, c64 86 and 35; 24 and 12, c64 1764 with 32768 in both.  Below 1024
-// states a leaf takes no longer than its launch (8 and 4: 30 us, split 34).
+// calls, masked and with 1000 ranks, with leaves of 32768 and by this rule: 20 modes,
+// 10 photons, c128 184 and 120 us; 22 and 11, c64 386 and 343; 18 and 9, c128, six groups
+// 293 and 66; 15 and 7, c64 89 and 35; 24 and 12, c64, not masked 869 and 871.  Below
+// 1024 states a leaf takes no longer than its launch (8 and 4: 30 us, split 34).
 static uint64_t ps_leaf_cap(uint64_t states)
 {
     return (uint64_t)std::min((double)SLOS_PS_LEAF_MAX, std::max(1024.0, 1.2 * std::sqrt((double)states)));
